@@ -1,4 +1,4 @@
-// Attention backward, key-outer dK/dV kernel (bf16 MFMA and fp32 VALU variants).
+// Attention backward, key-outer dK/dV kernel (bf16 and fp32 MFMA variants).
 #include <algorithm>
 
 #include "attn_common.h"
@@ -188,76 +188,64 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_bf16_kernel(AttnArgs a) 
   }
 }
 
+// ====================================================================== backward dK dV, fp32
+// 16 keys per workgroup; wave w takes the query tiles of 16 w, w + 4, ... S and dP have the
+// key on the lane axis, so P and dS are the B operands of dV^T += dO^T P, dK^T += Q^T dS.
 template <int DH>
-__global__ __launch_bounds__(64) void attn_bwd_dkdv_f32_kernel(AttnArgs a) {
-  extern __shared__ float fsm[];
-  float* Kown = fsm;                       // [DH][65]
-  float* Vown = Kown + DH * 65;            // [DH][65]
-  float* Qs = Vown + DH * 65;              // [16][DH]
-  float* dOs = Qs + 16 * DH;               // [16][DH]
-  float* ls = dOs + 16 * DH;               // [16]
-  float* dls = ls + 16;                    // [16]
-  const int tid = threadIdx.x, h = blockIdx.y, b = blockIdx.z;
-  const int64_t S = a.S, k0 = (int64_t)blockIdx.x * 64, kv = k0 + tid;
+__global__ __launch_bounds__(256) void attn_bwd_dkdv_f32_kernel(AttnArgs a) {
+  constexpr int NC = DH / 16;
+  __shared__ __attribute__((aligned(16))) float red[4][DH][17];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, c16 = lane & 15;
+  const int h = blockIdx.y, b = blockIdx.z;
+  const int64_t S = a.S, k0 = (int64_t)blockIdx.x * 16, kv = k0 + c16;   // causal: low blocks have the most queries
   const float scale = rsqrtf((float)DH);
-  const float* Qp = (const float*)a.q + (int64_t)h * DH;
-  const float* Kp = (const float*)a.k + (int64_t)h * DH;
-  const float* Vp = (const float*)a.v + (int64_t)h * DH;
-  const float* dOp = (const float*)a.dout + (int64_t)h * DH;
+  const float* Qb = (const float*)a.q + (int64_t)b * S * a.ld_q + (int64_t)h * DH;
+  const float* Kb = (const float*)a.k + (int64_t)b * S * a.ld_k + (int64_t)h * DH;
+  const float* Vb = (const float*)a.v + (int64_t)b * S * a.ld_v + (int64_t)h * DH;
+  const float* dOb = (const float*)a.dout + (int64_t)b * S * a.ld_do + (int64_t)h * DH;
   const float* lse = a.lse + ((int64_t)b * a.H + h) * a.Sp;
   const float* ndelta = a.ndelta + ((int64_t)b * a.H + h) * a.Sp;
-  for (int d = 0; d < DH; ++d) {
-    Kown[d * 65 + tid] = kv < S ? Kp[(b * S + kv) * a.ld_k + d] : 0.0f;
-    Vown[d * 65 + tid] = kv < S ? Vp[(b * S + kv) * a.ld_v + d] : 0.0f;
-  }
-  float dk[DH], dv[DH];
+  const int64_t kr = kv < S ? kv : S - 1;
+  const RowFrag<DH> kf = row_frag<DH>(Kb + kr * a.ld_k, g), vf = row_frag<DH>(Vb + kr * a.ld_v, g);
+  f32x4 dk[NC], dv[NC];
 #pragma unroll
-  for (int d = 0; d < DH; ++d) dk[d] = dv[d] = 0.0f;
+  for (int t = 0; t < NC; ++t) dk[t] = dv[t] = f32x4{};
   const int64_t qstart = a.causal ? k0 : 0;
-  for (int64_t qt0 = qstart; qt0 < S; qt0 += 16) {
-    __syncthreads();
-    for (int i = tid; i < 16 * DH; i += 64) {
-      const int r = i / DH, d = i % DH;
-      const int64_t q = qt0 + r;
-      Qs[i] = q < S ? Qp[(b * S + q) * a.ld_q + d] : 0.0f;
-      dOs[i] = q < S ? dOp[(b * S + q) * a.ld_do + d] : 0.0f;
-    }
-    if (tid < 16) {
-      const int64_t q = qt0 + tid;
-      ls[tid] = q < S ? lse[q] : 0.0f;
-      dls[tid] = q < S ? ndelta[q] : 0.0f;
-    }
-    __syncthreads();
-    for (int i = 0; i < 16; ++i) {
-      const int64_t q = qt0 + i;
-      float sv = 0.0f, dpv = 0.0f;
+  if (k0 < S)
+    for (int64_t q0 = qstart + 16 * wave; q0 < S; q0 += 64) {
+      const int64_t qr = q0 + c16 < S ? q0 + c16 : S - 1;
+      const RowFrag<DH> qf = row_frag<DH>(Qb + qr * a.ld_q, g), of = row_frag<DH>(dOb + qr * a.ld_do, g);
+      const f32x4 l4 = *(const f32x4*)(lse + q0 + 4 * g), d4 = *(const f32x4*)(ndelta + q0 + 4 * g);   // rows < Sp
+      const ColFrag<DH> oc = col_frag<DH>(dOb, a.ld_do, q0, S - 1, g, c16);
+      f32x4 p = dot_frags<DH>(qf, kf), ds = dot_frags<DH>(of, vf);
 #pragma unroll
-      for (int d = 0; d < DH; ++d) {
-        sv = fmaf(Qs[i * DH + d], Kown[d * 65 + tid], sv);
-        dpv = fmaf(dOs[i * DH + d], Vown[d * 65 + tid], dpv);
+      for (int r = 0; r < 4; ++r) {
+        const int64_t q = q0 + 4 * g + r;
+        const bool ok = q < S && kv < S && !(a.causal && kv > q);
+        p[r] = ok ? fast_exp2((p[r] * scale - l4[r]) * LOG2E) : 0.0f;
+        ds[r] = ok ? p[r] * (ds[r] + d4[r]) : 0.0f;
       }
-      const bool ok = q < S && kv < S && !(a.causal && kv > q);
-      const float p = ok ? __expf(sv * scale - ls[i]) : 0.0f;
-      const float ds = p * (dpv + dls[i]);
-#pragma unroll
-      for (int d = 0; d < DH; ++d) {
-        dv[d] = fmaf(p, dOs[i * DH + d], dv[d]);
-        dk[d] = fmaf(ds, Qs[i * DH + d], dk[d]);
-      }
+      const ColFrag<DH> qc = col_frag<DH>(Qb, a.ld_q, q0, S - 1, g, c16);
+      add_outer<DH>(dv, oc, p);
+      add_outer<DH>(dk, qc, ds);
     }
-  }
-  if (kv < a.Sp) {
-    const int64_t col = (int64_t)b * a.Sp + kv;
-    float* dKt = (float*)a.dkt + (int64_t)h * DH * a.ld_dt + col;
-    float* dVt = (float*)a.dvt + (int64_t)h * DH * a.ld_dt + col;
+  // add the four waves' parts, dK then dV, and store them feature-major
 #pragma unroll
-    for (int d = 0; d < DH; ++d) {
-      dKt[(int64_t)d * a.ld_dt] = dk[d] * scale;
-      dVt[(int64_t)d * a.ld_dt] = dv[d];
+  for (int which = 0; which < 2; ++which) {
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < NC; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) red[wave][16 * t + 4 * g + r][c16] = which ? dv[t][r] : dk[t][r];
+    __syncthreads();
+    float* out = (float*)(which ? a.dvt : a.dkt) + (int64_t)h * DH * a.ld_dt + (int64_t)b * a.Sp + k0;
+    const float f = which ? 1.0f : scale;
+    for (int i = tid; i < 16 * DH; i += 256) {         // 16 consecutive keys of a feature
+      const int d = i >> 4, k = i & 15;
+      out[(int64_t)d * a.ld_dt + k] = (((red[0][d][k] + red[1][d][k]) + red[2][d][k]) + red[3][d][k]) * f;
     }
   }
 }
-
 
 template <int DH>
 static hipError_t dkdv_launch(Dt dt, const AttnArgs& a, hipStream_t s) {
@@ -269,10 +257,7 @@ static hipError_t dkdv_launch(Dt dt, const AttnArgs& a, hipStream_t s) {
     const int64_t nblk = (a.S + DkvCfg<DH>::KEYS - 1) / DkvCfg<DH>::KEYS;
     hipLaunchKernelGGL(k, dim3((unsigned)(nblk * a.H * a.B)), dim3(64 * DkvCfg<DH>::NW), DkvCfg<DH>::LDS, s, a);
   } else {
-    const int lds = (2 * DH * 65 + 2 * 16 * DH + 32) * 4;
-    hipError_t e = set_lds(attn_bwd_dkdv_f32_kernel<DH>, lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(attn_bwd_dkdv_f32_kernel<DH>, dim3((unsigned)(a.Sp / 64), a.H, a.B), dim3(64), lds, s, a);
+    hipLaunchKernelGGL(attn_bwd_dkdv_f32_kernel<DH>, dim3((unsigned)(a.Sp / 16), a.H, a.B), dim3(256), 0, s, a);
   }
   return hipGetLastError();
 }

@@ -1,4 +1,4 @@
-// Attention backward, query-outer dQ kernel (bf16 MFMA and fp32 VALU variants).
+// Attention backward, query-outer dQ kernel (bf16 and fp32 MFMA variants).
 #include <algorithm>
 
 #include "attn_common.h"
@@ -152,63 +152,53 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dq_bf16_kernel(AttnArgs a) {
   }
 }
 
+// ====================================================================== backward dQ, fp32
+// 16 queries per workgroup; wave w takes the key tiles of 16 w, w + 4, ... S^T and dP^T
+// have the query on the lane axis, so dS^T is the B operand of dQ^T += K^T dS^T.
 template <int DH>
-__global__ __launch_bounds__(64) void attn_bwd_dq_f32_kernel(AttnArgs a) {
-  extern __shared__ float fsm[];
-  float* Qown = fsm;                       // [DH][65]
-  float* dOown = Qown + DH * 65;           // [DH][65]
-  float* Ks = dOown + DH * 65;             // [16][DH]
-  float* Vs = Ks + 16 * DH;                // [16][DH]
-  const int tid = threadIdx.x, h = blockIdx.y, b = blockIdx.z;
-  const int64_t S = a.S, q0 = (int64_t)blockIdx.x * 64, q = q0 + tid;
+__global__ __launch_bounds__(256) void attn_bwd_dq_f32_kernel(AttnArgs a) {
+  constexpr int NC = DH / 16;
+  __shared__ __attribute__((aligned(16))) float red[4][DH][17];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, c16 = lane & 15;
+  const int h = blockIdx.y, b = blockIdx.z;
+  const int64_t S = a.S;
+  const int64_t blk = a.causal ? gridDim.x - 1 - blockIdx.x : blockIdx.x;   // causal: most keys first
+  const int64_t q0 = blk * 16, q = q0 + c16, qr = q < S ? q : S - 1;
   const float scale = rsqrtf((float)DH);
-  const float* Qp = (const float*)a.q + (int64_t)h * DH;
-  const float* Kp = (const float*)a.k + (int64_t)h * DH;
-  const float* Vp = (const float*)a.v + (int64_t)h * DH;
-  const float* dOp = (const float*)a.dout + (int64_t)h * DH;
-  const int64_t sidx = ((int64_t)b * a.H + h) * a.Sp + q;
-  const float lq = q < S ? a.lse[sidx] : 0.0f;
-  const float ndl = q < S ? a.ndelta[sidx] : 0.0f;
-  for (int d = 0; d < DH; ++d) {
-    Qown[d * 65 + tid] = q < S ? Qp[(b * S + q) * a.ld_q + d] : 0.0f;
-    dOown[d * 65 + tid] = q < S ? dOp[(b * S + q) * a.ld_do + d] : 0.0f;
+  const float* Qb = (const float*)a.q + (int64_t)b * S * a.ld_q + (int64_t)h * DH;
+  const float* Kb = (const float*)a.k + (int64_t)b * S * a.ld_k + (int64_t)h * DH;
+  const float* Vb = (const float*)a.v + (int64_t)b * S * a.ld_v + (int64_t)h * DH;
+  const float* dOb = (const float*)a.dout + (int64_t)b * S * a.ld_do + (int64_t)h * DH;
+  const RowFrag<DH> qf = row_frag<DH>(Qb + qr * a.ld_q, g), of = row_frag<DH>(dOb + qr * a.ld_do, g);
+  const int64_t sidx = ((int64_t)b * a.H + h) * a.Sp + qr;
+  const float lq = a.lse[sidx], ndl = a.ndelta[sidx];
+  f32x4 dq[NC];
+#pragma unroll
+  for (int t = 0; t < NC; ++t) dq[t] = f32x4{};
+  const int64_t kv_end = q0 >= S ? 0 : a.causal ? (q0 + 16 < S ? q0 + 16 : S) : S;
+  const int64_t kv_lim = q >= S ? 0 : a.causal && q + 1 < kv_end ? q + 1 : kv_end;   // keys this lane's query may see
+  for (int64_t kv0 = 16 * wave; kv0 < kv_end; kv0 += 64) {
+    const int64_t kr = kv0 + c16 < S ? kv0 + c16 : S - 1;
+    const RowFrag<DH> kf = row_frag<DH>(Kb + kr * a.ld_k, g), vf = row_frag<DH>(Vb + kr * a.ld_v, g);
+    const ColFrag<DH> kc = col_frag<DH>(Kb, a.ld_k, kv0, S - 1, g, c16);
+    const f32x4 s = dot_frags<DH>(kf, qf);
+    f32x4 ds = dot_frags<DH>(vf, of);
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      ds[r] = kv0 + 4 * g + r < kv_lim ? fast_exp2((s[r] * scale - lq) * LOG2E) * (ds[r] + ndl) : 0.0f;
+    add_outer<DH>(dq, kc, ds);
   }
-  float dq[DH];
 #pragma unroll
-  for (int d = 0; d < DH; ++d) dq[d] = 0.0f;
-  const int64_t kv_end = a.causal ? (q0 + 64 < S ? q0 + 64 : S) : S;
-  for (int64_t kv0 = 0; kv0 < kv_end; kv0 += 16) {
-    __syncthreads();
-    for (int i = tid; i < 16 * DH; i += 64) {
-      const int r = i / DH, d = i % DH;
-      const int64_t kv = kv0 + r;
-      Ks[i] = kv < S ? Kp[(b * S + kv) * a.ld_k + d] : 0.0f;
-      Vs[i] = kv < S ? Vp[(b * S + kv) * a.ld_v + d] : 0.0f;
-    }
-    __syncthreads();
-    for (int jj = 0; jj < 16; ++jj) {
-      const int64_t kv = kv0 + jj;
-      float sv = 0.0f, dpv = 0.0f;
+  for (int t = 0; t < NC; ++t)
 #pragma unroll
-      for (int d = 0; d < DH; ++d) {
-        sv = fmaf(Qown[d * 65 + tid], Ks[jj * DH + d], sv);
-        dpv = fmaf(dOown[d * 65 + tid], Vs[jj * DH + d], dpv);
-      }
-      const bool ok = q < S && kv < S && !(a.causal && kv > q);
-      const float p = ok ? __expf(sv * scale - lq) : 0.0f;
-      const float ds = p * (dpv + ndl);
-#pragma unroll
-      for (int d = 0; d < DH; ++d) dq[d] = fmaf(ds, Ks[jj * DH + d], dq[d]);
-    }
-  }
-  if (q < a.Sp) {
-    float* dQt = (float*)a.dqt + (int64_t)h * DH * a.ld_dt + (int64_t)b * a.Sp + q;
-    const bool real = q < S;
-#pragma unroll
-    for (int d = 0; d < DH; ++d) dQt[(int64_t)d * a.ld_dt] = real ? dq[d] * scale : 0.0f;
+    for (int r = 0; r < 4; ++r) red[wave][16 * t + 4 * g + r][c16] = dq[t][r];
+  __syncthreads();
+  float* out = (float*)a.dqt + (int64_t)h * DH * a.ld_dt + (int64_t)b * a.Sp + q0;
+  for (int i = tid; i < 16 * DH; i += 256) {           // 16 consecutive queries of a feature
+    const int d = i >> 4, k = i & 15;
+    out[(int64_t)d * a.ld_dt + k] = (((red[0][d][k] + red[1][d][k]) + red[2][d][k]) + red[3][d][k]) * scale;
   }
 }
-
 
 template <int DH>
 static hipError_t dq_launch(Dt dt, const AttnArgs& a, hipStream_t s) {
@@ -220,10 +210,7 @@ static hipError_t dq_launch(Dt dt, const AttnArgs& a, hipStream_t s) {
     const int64_t nblk = (a.S + DqCfg<DH>::QROWS - 1) / DqCfg<DH>::QROWS;
     hipLaunchKernelGGL(k, dim3((unsigned)(nblk * a.H * a.B)), dim3(64 * DqCfg<DH>::NW), DqCfg<DH>::LDS, s, a);
   } else {
-    const int lds = (2 * DH * 65 + 2 * 16 * DH) * 4;
-    hipError_t e = set_lds(attn_bwd_dq_f32_kernel<DH>, lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(attn_bwd_dq_f32_kernel<DH>, dim3((unsigned)(a.Sp / 64), a.H, a.B), dim3(64), lds, s, a);
+    hipLaunchKernelGGL(attn_bwd_dq_f32_kernel<DH>, dim3((unsigned)(a.Sp / 16), a.H, a.B), dim3(256), 0, s, a);
   }
   return hipGetLastError();
 }

@@ -178,6 +178,72 @@ BPT_DEV bf16x8 acc_to_b(const f32x16& s, int hf) {
   return r;
 }
 
+// ---------------------------------------------------------------- fp32 kernels
+// The fp32 kernels run on v_mfma_f32_16x16x4_f32 (fp32 operands and accumulation): lane l
+// supplies row (column) l % 16 of the A (B) operand at k = l / 16, and holds rows
+// 4 (l / 16) + r, r = 0..3, of column l % 16 of the result. 4 waves share a block of 16
+// query (or key) rows and split the tiles of the other axis among them, so that short
+// sequences still spread over the chip; their results are added at the end through LDS, in
+// wave order. Fragments come straight from global memory (L2): one 16-row tile is 64-byte
+// pieces either way, and a tile's MFMAs (32 cycles per 4-deep step) outlast its loads.
+BPT_DEV f32x4 mfma16x16x4(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+
+// Row fragment: row l % 16 of the tile (p points at it), features 16 c + 4 (l / 16) + j in
+// element j of chunk c: step j of chunk c contracts over those features.
+template <int DH>
+struct RowFrag {
+  f32x4 v[DH / 16];
+};
+template <int DH>
+BPT_DEV RowFrag<DH> row_frag(const float* p, int g) {
+  RowFrag<DH> f;
+#pragma unroll
+  for (int c = 0; c < DH / 16; ++c) f.v[c] = *(const f32x4*)(p + 16 * c + 4 * g);
+  return f;
+}
+template <int DH>
+BPT_DEV f32x4 dot_frags(const RowFrag<DH>& a, const RowFrag<DH>& b) {
+  f32x4 s = {};
+#pragma unroll
+  for (int c = 0; c < DH / 16; ++c)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) s = mfma16x16x4(a.v[c][j], b.v[c][j], s);
+  return s;
+}
+// Column fragment: feature 16 t + l % 16 of rows 4 (l / 16) + r (an accumulator's rows), the
+// A operand of a contraction over the tile's rows with an accumulator as B operand.
+template <int DH>
+struct ColFrag {
+  float v[4][DH / 16];
+};
+template <int DH>
+BPT_DEV ColFrag<DH> col_frag(const float* X, int64_t ld, int64_t row0, int64_t last, int g, int c16) {
+  ColFrag<DH> f;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int64_t row = row0 + 4 * g + r < last ? row0 + 4 * g + r : last;
+#pragma unroll
+    for (int t = 0; t < DH / 16; ++t) f.v[r][t] = X[row * ld + 16 * t + c16];
+  }
+  return f;
+}
+template <int DH>
+BPT_DEV void add_outer(f32x4 (&acc)[DH / 16], const ColFrag<DH>& f, const f32x4& p) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+#pragma unroll
+    for (int t = 0; t < DH / 16; ++t) acc[t] = mfma16x16x4(f.v[r][t], p[r], acc[t]);
+}
+// max / sum over the four lanes l, l ^ 16, l ^ 32, l ^ 48
+BPT_DEV float max_groups(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return max_halves(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
+}
+BPT_DEV float sum_groups(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return sum_halves(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+}
+
 // Row of accumulator register r for lane `lane` inside a 32x32 tile.
 BPT_DEV int acc_row(int r, int lane) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
 

@@ -20,8 +20,7 @@
 //    so scores are base-2 logits, and the score MFMAs start from minus the row's
 //    reference maximum: exp2 of the accumulator is the weight, and the backward
 //    kernels start them from minus the base-2 log-sum-exp in the same way.
-// fp32 kernels: one query (or key) row per thread with VALU FMAs; used by the
-// fp32 parity workload.
+// fp32 kernels: the same shape of computation on fp32 MFMAs (attn_common.h).
 #include <algorithm>
 
 #include "attn_common.h"
@@ -250,70 +249,110 @@ __global__ __launch_bounds__(512, 1) void attn_fwd_bf16_kernel(AttnArgs a) {
   }
 }
 
-// ====================================================================== fp32 kernels
+// ====================================================================== forward, fp32
+// 16 queries per workgroup; wave w takes the key tiles of 32 w, w + 4, ... with its own
+// running maximum and sum, merged at the end (exactly, as two blocks' summaries merge).
+// S^T = K Q^T has the query on the lane axis, so exp of it is the B operand of
+// O^T += V^T P^T as it stands. The next tile's K (V) is fetched once this one's is consumed.
 template <int DH>
-__global__ __launch_bounds__(64) void attn_fwd_f32_kernel(AttnArgs a) {
-  __shared__ float Ks[32][DH + 1], Vs[32][DH + 1];
-  const int tid = threadIdx.x, h = blockIdx.y, b = a.b_begin + blockIdx.z;
+__global__ __launch_bounds__(256) void attn_fwd_f32_kernel(AttnArgs a) {
+  constexpr int NC = DH / 16;
+  __shared__ __attribute__((aligned(16))) float red[4][16][DH + 4];
+  __shared__ float red_m[4][16], red_l[4][16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, c16 = lane & 15;
+  const int h = blockIdx.y, b = a.b_begin + blockIdx.z;
   const int64_t S = a.S;
-  const int64_t q0 = a.q_begin + (int64_t)blockIdx.x * 64, q = q0 + tid;
+  const int64_t blk = a.causal ? gridDim.x - 1 - blockIdx.x : blockIdx.x;   // causal: most keys first
+  const int64_t q0 = a.q_begin + blk * 16, q = q0 + c16;
   const float scale = rsqrtf((float)DH), c = scale * LOG2E;
-  const float* Qp = (const float*)a.q + (int64_t)h * DH;
-  const float* Kp = (const float*)a.k + (int64_t)h * DH;
-  const float* Vp = (const float*)a.v + (int64_t)h * DH;
-  float qr[DH], acc[DH];
+  const float* Qb = (const float*)a.q + (int64_t)b * S * a.ld_q + (int64_t)h * DH;
+  const float* Kb = (const float*)a.k + (int64_t)b * S * a.ld_k + (int64_t)h * DH;
+  const float* Vb = (const float*)a.v + (int64_t)b * S * a.ld_v + (int64_t)h * DH;
+  const RowFrag<DH> qf = row_frag<DH>(Qb + (q < S ? q : S - 1) * a.ld_q, g);
+  const int64_t kv_end = a.causal ? (q0 + 16 < S ? q0 + 16 : S) : S;
+  const int64_t kv_lim = a.causal && q + 1 < kv_end ? q + 1 : kv_end;   // keys this lane's query may see
+
+  f32x4 acc[NC];
 #pragma unroll
-  for (int d = 0; d < DH; ++d) {
-    qr[d] = q < S ? Qp[(b * S + q) * a.ld_q + d] : 0.0f;
-    acc[d] = 0.0f;
-  }
+  for (int t = 0; t < NC; ++t) acc[t] = f32x4{};
   float m_run = NEG_INF, l_run = 0.0f;
-  const int64_t kv_end = a.causal ? (q0 + 64 < S ? q0 + 64 : S) : S;
-  for (int64_t kv0 = 0; kv0 < kv_end; kv0 += 32) {
-    for (int i = tid; i < 32 * DH; i += 64) {
-      const int r = i / DH, d = i % DH;
-      const int64_t kv = kv0 + r;
-      Ks[r][d] = kv < S ? Kp[(b * S + kv) * a.ld_k + d] : 0.0f;
-      Vs[r][d] = kv < S ? Vp[(b * S + kv) * a.ld_v + d] : 0.0f;
+  RowFrag<DH> kf[2];
+  ColFrag<DH> vf[2];
+  auto load_k = [&](int64_t kv0) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int64_t kr = kv0 + 16 * u + c16;
+      kf[u] = row_frag<DH>(Kb + (kr < S ? kr : S - 1) * a.ld_k, g);
     }
-    __syncthreads();
-    float sc[32];
+  };
+  auto load_v = [&](int64_t kv0) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) vf[u] = col_frag<DH>(Vb, a.ld_v, kv0 + 16 * u, S - 1, g, c16);
+  };
+  int64_t kv0 = 32 * wave;
+  if (kv0 < kv_end) {
+    load_k(kv0);
+    load_v(kv0);
+  }
+  for (; kv0 < kv_end; kv0 += 128) {
+    f32x4 s[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) s[u] = dot_frags<DH>(kf[u], qf);
+    if (kv0 + 128 < kv_end) load_k(kv0 + 128);
     float mx = NEG_INF;
 #pragma unroll
-    for (int jj = 0; jj < 32; ++jj) {
-      float sv = 0.0f;
+    for (int u = 0; u < 2; ++u)
 #pragma unroll
-      for (int d = 0; d < DH; ++d) sv = fmaf(qr[d], Ks[jj][d], sv);
-      const int64_t kv = kv0 + jj;
-      if (kv >= S || (a.causal && kv > q)) sv = NEG_INF;
-      sc[jj] = sv;
-      mx = fmaxf(mx, sv);
+      for (int r = 0; r < 4; ++r) {
+        if (kv0 + 16 * u + 4 * g + r >= kv_lim) s[u][r] = NEG_INF;
+        mx = fmaxf(mx, s[u][r]);
+      }
+    const float m_new = fmaxf(m_run, max_groups(mx));
+    const float m_use = m_new == NEG_INF ? 0.0f : m_new;
+    if (__ballot(m_new > m_run)) {
+      const float corr = exp2f((m_run - m_use) * c);
+      l_run *= corr;
+#pragma unroll
+      for (int t = 0; t < NC; ++t) acc[t] *= corr;
+      m_run = m_new;
     }
-    const float m_new = fmaxf(m_run, mx);
-    const float m_use = (m_new == NEG_INF) ? 0.0f : m_new;
-    const float corr = exp2f((m_run - m_use) * c);
-    l_run *= corr;
 #pragma unroll
-    for (int d = 0; d < DH; ++d) acc[d] *= corr;
+    for (int u = 0; u < 2; ++u)
 #pragma unroll
-    for (int jj = 0; jj < 32; ++jj) {
-      const float p = exp2f((sc[jj] - m_use) * c);
-      l_run += p;
+      for (int r = 0; r < 4; ++r) {
+        s[u][r] = exp2f((s[u][r] - m_use) * c);
+        l_run += s[u][r];
+      }
 #pragma unroll
-      for (int d = 0; d < DH; ++d) acc[d] = fmaf(p, Vs[jj][d], acc[d]);
-    }
-    m_run = m_new;
-    __syncthreads();
+    for (int u = 0; u < 2; ++u) add_outer<DH>(acc, vf[u], s[u]);
+    if (kv0 + 128 < kv_end) load_v(kv0 + 128);
   }
-  if (q < a.q_end && q < S) {
-    float* Op = (float*)a.o + (b * S + q) * a.ld_o + (int64_t)h * DH;
-    const float inv = 1.0f / l_run;
+  l_run = sum_groups(l_run);
+  if (g == 0) {
+    red_m[wave][c16] = m_run;
+    red_l[wave][c16] = l_run;
+  }
 #pragma unroll
-    for (int d = 0; d < DH; ++d) Op[d] = acc[d] * inv;
-    a.lse[((int64_t)b * a.H + h) * a.Sp + q] = m_run * scale + logf(l_run);
+  for (int t = 0; t < NC; ++t) *(f32x4*)&red[wave][c16][16 * t + 4 * g] = acc[t];
+  __syncthreads();
+  for (int i = tid; i < 16 * (DH / 4); i += 256) {
+    const int qi = i / (DH / 4), d = 4 * (i % (DH / 4));
+    const int64_t qq = q0 + qi;
+    if (qq >= a.q_end || qq >= S) continue;
+    float m = NEG_INF, l = 0.0f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) m = fmaxf(m, red_m[w][qi]);      // finite: key 0 is visible
+    f32x4 o = {};
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const float f = exp2f((red_m[w][qi] - m) * c);
+      l = fmaf(red_l[w][qi], f, l);
+      o += f * *(const f32x4*)&red[w][qi][d];
+    }
+    *(f32x4*)((float*)a.o + ((int64_t)b * S + qq) * a.ld_o + (int64_t)h * DH + d) = o / l;
+    if (d == 0) a.lse[((int64_t)b * a.H + h) * a.Sp + qq] = m * scale + logf(l);
   }
 }
-
 
 template <int DH>
 static hipError_t fwd_launch(Dt dt, const AttnArgs& a, hipStream_t s) {
@@ -326,8 +365,8 @@ static hipError_t fwd_launch(Dt dt, const AttnArgs& a, hipStream_t s) {
     const int64_t nblk = (nq + FwdCfg<DH>::QROWS - 1) / FwdCfg<DH>::QROWS;
     hipLaunchKernelGGL(kern, dim3((unsigned)(nblk * a.H * a.nb)), dim3(64 * FwdCfg<DH>::NW), FwdCfg<DH>::LDS, s, a);
   } else {
-    hipLaunchKernelGGL(attn_fwd_f32_kernel<DH>, dim3((unsigned)((nq + 63) / 64), a.H, a.nb),
-                       dim3(64), 0, s, a);
+    hipLaunchKernelGGL(attn_fwd_f32_kernel<DH>, dim3((unsigned)((nq + 15) / 16), a.H, a.nb),
+                       dim3(256), 0, s, a);
   }
   return hipGetLastError();
 }

@@ -11,7 +11,7 @@
 // with 8 waves (2 along M x 4 along N, two per SIMD) or, where fewer than 256 such tiles
 // exist, 128 x 128 with 4 waves (2 x 2); K step 32 per stage through an LDS ring with
 // XOR-swizzled 16-byte chunks, so that the rows a fragment read touches fall in distinct
-// banks. fp32 path: plain VALU FMA tiles (used for the fp32 parity workload).
+// banks. fp32 path: the same structure on v_mfma_f32_16x16x4_f32 (gemm_f32_kernel).
 #include "common.h"
 #include "internal.h"
 #include <type_traits>
@@ -642,50 +642,127 @@ __global__ __launch_bounds__(128 * NWN, 1) void gemm_bf16_kernel(GemmArgs a) {
   }
 }
 
-// ------------------------------------------------------------------ fp32 VALU kernel
-template <int EPI, typename CT, typename RT>
+// ------------------------------------------------------------------ fp32 MFMA kernel
+// True fp32: v_mfma_f32_16x16x4_f32 (fp32 operands and accumulation), 4 waves (2 x 2) of
+// 16 TM x 16 TN outputs, K step 16 per stage through a 4-stage LDS ring of direct copies.
+// Both operand forms reach the MFMAs with the same k order: lane group g = lane / 16
+// supplies k = 4 g + j to step j, one 16-byte read of a K-contiguous tile or four 4-byte
+// reads of a K-major one. K-contiguous tiles are 64-byte rows whose 16-byte chunk c sits
+// at c ^ (row / 2 % 4), K-major tiles rows of BX floats whose 64-byte blocks swap places in
+// rows with odd k / 4: a wave's reads then cover all banks evenly. The operands are passed
+// to the MFMA swapped, so that a lane ends up with 4 consecutive columns of one row.
+//
+// Bound by the matrix cores' fp32 rate where the grid fills the chip, by the latency of a
+// stage elsewhere; hence three tile sizes (launch_f32).
+template <int BM, int BN>
+struct F32Cfg {
+  static constexpr int BK = 16, NW = 4, NS = 4;
+  static constexpr int TM = BM / 32, TN = BN / 32;        // 16x16 MFMA tiles per wave
+  static constexpr int ABYTES = BM * 64, BBYTES = BN * 64, STAGE = ABYTES + BBYTES;
+  static constexpr int ABLK = ABYTES / 1024, NBLK = STAGE / 1024;   // 1 KiB copy blocks
+  static constexpr int DPS = NBLK / NW;                   // copies per wave per stage
+  static constexpr int LDS = NS * STAGE;
+  static_assert(NBLK % NW == 0, "every wave issues the same number of copies");
+};
+
+template <int BM, int BN, int EPI, typename CT, typename RT, bool TA, bool TB>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a) {
-  __shared__ float As[16][64 + 4], Bs[16][64 + 4];
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int64_t tiles_m = (a.M + 63) / 64;
-  const int64_t m0 = (blockIdx.x % tiles_m) * 64, n0 = (blockIdx.x / tiles_m) * 64, z = blockIdx.z;
-  const float* A = (const float*)a.A + z * a.sA;
-  const float* B = (const float*)a.B + z * a.sB;
-  float acc[4][4] = {};
-  const int lr = tid >> 2, lk = (tid & 3) * 4;
-  const int64_t arows = a.trans_a && a.a_rows > 0 ? a.a_rows : a.K;
-  const int64_t brows = a.trans_b && a.b_rows > 0 ? a.b_rows : a.K;
-  for (int64_t k0 = 0; k0 < a.K; k0 += 16) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int64_t k = k0 + lk + e;
-      const int64_t ai = a.trans_a ? k * a.lda + m0 + lr : (m0 + lr) * a.lda + k;
-      const int64_t bi = a.trans_b ? k * a.ldb + n0 + lr : (n0 + lr) * a.ldb + k;
-      As[lk + e][lr] = (m0 + lr < a.M && k < arows) ? A[ai] : 0.0f;
-      Bs[lk + e][lr] = (n0 + lr < a.N && k < brows) ? B[bi] : 0.0f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      float av[4], bv[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) av[i] = As[kk][ty + 16 * i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) bv[j] = Bs[kk][tx + 16 * j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(av[i], bv[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
+  using C = F32Cfg<BM, BN>;
+  __shared__ __attribute__((aligned(1024))) char smem[C::LDS];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1, g = lane >> 4, c16 = lane & 15;
+  const int tiles_m = (int)((a.M + BM - 1) / BM);
   const int64_t ncols = a.Nstore > a.N ? a.Nstore : a.N;
+  const int64_t m0 = (int64_t)(blockIdx.x % tiles_m) * BM, n0 = (int64_t)(blockIdx.x / tiles_m) * BN, z = blockIdx.z;
+  const float* A = (const float*)a.A + z * a.sA + (TA ? m0 : m0 * a.lda);
+  const float* B = (const float*)a.B + z * a.sB + (TB ? n0 : n0 * a.ldb);
+  const int nk = (int)(a.K / C::BK);
+  const int64_t arows = a.a_rows > 0 ? a.a_rows : a.K, brows = a.b_rows > 0 ? a.b_rows : a.K;
+  const int acols = (int)((a.a_cols > 0 ? a.a_cols : a.M) - m0), bcols = (int)((a.b_cols > 0 ? a.b_cols : a.N) - n0);
+  const uint32_t ring = __builtin_amdgcn_readfirstlane(
+      (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem);
+
+  // source of this lane's 16 bytes of a copy block; rows and columns past the readable
+  // extent are clamped to the last one (K-major rows past x_rows meet zeros of the other
+  // operand, the rest is never stored)
+  auto src = [&](const float* X, int64_t ld, int64_t xrows, int cols, int last, int k0, int slot, auto TXc,
+                 auto BXc) -> const float* {
+    constexpr int BX = decltype(BXc)::value;
+    if constexpr (decltype(TXc)::value) {
+      const int row = slot / (BX / 4), lc = (slot % (BX / 4)) ^ (4 * ((row >> 2) & 1));
+      const int col = 4 * lc < cols - 4 ? 4 * lc : cols - 4;
+      const int64_t r = k0 + row < xrows ? k0 + row : xrows - 1;
+      return X + r * ld + col;
+    } else {
+      const int row = slot >> 2, ch = (slot & 3) ^ ((row >> 1) & 3);
+      return X + (int64_t)(row < last ? row : last) * ld + k0 + 4 * ch;
+    }
+  };
+  const int alast = (int)(a.M - 1 - m0), blast = (int)(a.N - 1 - n0);
+  auto issue = [&](int kt) {
+    const uint32_t st = ring + (kt % C::NS) * C::STAGE;
+    const int k0 = kt * C::BK;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < C::DPS; ++i) {
+      const int blk = wave + C::NW * i;
+      if (blk < C::ABLK)
+        lds_dma16(src(A, a.lda, arows, acols, alast, k0, blk * 64 + lane, std::integral_constant<bool, TA>{},
+                      std::integral_constant<int, BM>{}), st + blk * 1024);
+      else
+        lds_dma16(src(B, a.ldb, brows, bcols, blast, k0, (blk - C::ABLK) * 64 + lane, std::integral_constant<bool, TB>{},
+                      std::integral_constant<int, BN>{}), st + blk * 1024);
+    }
+  };
+  // fragment of 16 rows (A) or columns (B) from x0 on: k = 4 g + j in element j
+  auto frag = [&](const char* t, int x0, auto TXc, auto BXc) -> f32x4 {
+    constexpr int BX = decltype(BXc)::value;
+    if constexpr (decltype(TXc)::value) {
+      const float* p = (const float*)t + 4 * g * BX + ((x0 + c16) ^ (16 * (g & 1)));
+      return f32x4{p[0], p[BX], p[2 * BX], p[3 * BX]};
+    } else {
+      return *(const f32x4*)(t + (x0 + c16) * 64 + 16 * (g ^ ((c16 >> 1) & 3)));
+    }
+  };
+
+  f32x4 acc[C::TM][C::TN];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int64_t m = m0 + ty + 16 * i, n = n0 + tx + 16 * j;
-      if (m < a.M && n < ncols) epi_store<EPI, CT, RT>(a, z, m, n, acc[i][j]);
+  for (int i = 0; i < C::TM; ++i)
+#pragma unroll
+    for (int j = 0; j < C::TN; ++j) acc[i][j] = f32x4{};
+#pragma unroll
+  for (int s = 0; s < C::NS - 1; ++s)
+    if (s < nk) issue(s);
+  for (int kt = 0; kt < nk; ++kt) {
+    // stage kt has landed once at most the copies of the stages issued after it are pending
+    if (kt + 2 < nk) wait_vmcnt<2 * C::DPS>();
+    else if (kt + 1 < nk) wait_vmcnt<C::DPS>();
+    else wait_vmcnt<0>();
+    __syncthreads();                  // stage kt visible; every wave is done with stage kt-1
+    if (kt + C::NS - 1 < nk) issue(kt + C::NS - 1);      // into the slot of stage kt-1
+    const char* st = smem + (kt % C::NS) * C::STAGE;
+    f32x4 fa[C::TM], fb[C::TN];
+#pragma unroll
+    for (int i = 0; i < C::TM; ++i)
+      fa[i] = frag(st, wm * (BM / 2) + 16 * i, std::integral_constant<bool, TA>{}, std::integral_constant<int, BM>{});
+#pragma unroll
+    for (int j = 0; j < C::TN; ++j)
+      fb[j] = frag(st + C::ABYTES, wn * (BN / 2) + 16 * j, std::integral_constant<bool, TB>{},
+                   std::integral_constant<int, BN>{});
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+      for (int i = 0; i < C::TM; ++i)
+#pragma unroll
+        for (int j = 0; j < C::TN; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[j][k], fa[i][k], acc[i][j], 0, 0, 0);
+  }
+#pragma unroll
+  for (int i = 0; i < C::TM; ++i)
+#pragma unroll
+    for (int j = 0; j < C::TN; ++j) {
+      const int64_t m = m0 + wm * (BM / 2) + 16 * i + c16, n = n0 + wn * (BN / 2) + 16 * j + 4 * g;
+      if (m < a.M && n < ncols) epi_store4<EPI, CT, RT>(a, z, m, n, ncols, acc[i][j]);
     }
 }
 
@@ -712,16 +789,50 @@ static hipError_t launch_bf16(const GemmArgs& a, hipStream_t s) {
 // waves along N of the 256 x 256 tile configuration
 static constexpr int kNWN = 4;
 
+template <int BX, int EPI, typename CT, typename RT, bool TA, bool TB>
+static hipError_t launch_f32_tile(const GemmArgs& a, hipStream_t s) {
+  const int64_t ncols = a.Nstore > a.N ? a.Nstore : a.N;
+  const int64_t tiles = ((a.M + BX - 1) / BX) * ((ncols + BX - 1) / BX);
+  if (tiles <= 0 || a.batch <= 0) return hipSuccess;
+  hipLaunchKernelGGL((gemm_f32_kernel<BX, BX, EPI, CT, RT, TA, TB>), dim3((unsigned)tiles, 1, (unsigned)a.batch),
+                     dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
+// Square tiles of 128, 64 or 32: the largest that still gives every CU a workgroup (below
+// that the time of a stage is its latency, not its MFMAs, and smaller tiles have more of
+// them in flight).
+template <int EPI, typename CT, typename RT, bool TA, bool TB>
+static hipError_t launch_f32_ops(const GemmArgs& a, hipStream_t s) {
+  const int64_t ncols = a.Nstore > a.N ? a.Nstore : a.N;
+  auto tiles = [&](int64_t b) { return ((a.M + b - 1) / b) * ((ncols + b - 1) / b) * a.batch; };
+  if (tiles(128) >= 256) return launch_f32_tile<128, EPI, CT, RT, TA, TB>(a, s);
+  if (tiles(64) >= 256) return launch_f32_tile<64, EPI, CT, RT, TA, TB>(a, s);
+  return launch_f32_tile<32, EPI, CT, RT, TA, TB>(a, s);
+}
+
+template <int EPI, typename CT, typename RT>
+static hipError_t launch_f32(const GemmArgs& a, hipStream_t s) {
+  // 16-byte copies along the operands' contiguous extent, 16-byte stores of 4 columns
+  if (a.K % 16 || a.lda % 4 || a.ldb % 4 || a.ldc % 4 || (a.trans_a && (a.a_cols > 0 ? a.a_cols : a.M) % 4) ||
+      (a.trans_b && (a.b_cols > 0 ? a.b_cols : a.N) % 4))
+    return hipErrorInvalidValue;
+  if (a.trans_a && a.trans_b) {
+    if constexpr (EPI == EPI_STORE) return launch_f32_ops<EPI, CT, RT, true, true>(a, s);
+    return hipErrorInvalidValue;
+  }
+  if (a.trans_a) {
+    if constexpr (EPI == EPI_STORE || kAct<EPI> || EPI == EPI_XENT_T) return launch_f32_ops<EPI, CT, RT, true, false>(a, s);
+    return hipErrorInvalidValue;
+  }
+  if (a.trans_b) return launch_f32_ops<EPI, CT, RT, false, true>(a, s);
+  return launch_f32_ops<EPI, CT, RT, false, false>(a, s);
+}
+
 template <int EPI, typename CT, typename RT>
 static hipError_t launch_typed(Dt ab, const GemmArgs& a, hipStream_t s) {
   const int64_t ncols = a.Nstore > a.N ? a.Nstore : a.N;
-  if (ab == F32) {
-    const int64_t tiles = ((a.M + 63) / 64) * ((ncols + 63) / 64);
-    if (tiles <= 0 || a.batch <= 0) return hipSuccess;
-    hipLaunchKernelGGL((gemm_f32_kernel<EPI, CT, RT>), dim3((unsigned)tiles, 1, (unsigned)a.batch),
-                       dim3(256), 0, s, a);
-    return hipGetLastError();
-  }
+  if (ab == F32) return launch_f32<EPI, CT, RT>(a, s);
   const int64_t big = ((a.M + 255) / 256) * ((ncols + 255) / 256) * a.batch;
   if (a.trans_a || a.trans_b) {
     // a transposed operand is read in 16-byte column chunks

@@ -459,11 +459,12 @@ size_t bpt_describe(const bpt_config* cfg, char* buf, size_t n) {
                    "dtype=%s attention: q-tile=%d kv-step=%d (%s); backward dK/dV kv-tile=%d q-step=%d, "
                    "dQ q-tile=%d kv-step=%d; gemm: %s; ffn %s, group rows=%lld (%lld sequence(s) x %lld rows; "
                    "query blocks of %lld)",
-                   bf ? "bf16" : "f32", bf ? 256 : 64, bf ? 64 : 32,
-                   bf ? "MFMA 32x32x16 bf16, fp32 accumulate, 32 rows per wave" : "fp32 VALU",
-                   bf ? 256 : 64, bf ? 64 : 16, bf ? 256 : 64, bf ? 64 : 16,
+                   bf ? "bf16" : "f32", bf ? 256 : 16, bf ? 64 : 128,
+                   bf ? "MFMA 32x32x16 bf16, fp32 accumulate, 32 rows per wave"
+                      : "MFMA 16x16x4 fp32, 4 waves sharing 16 rows",
+                   bf ? 256 : 16, 64, bf ? 256 : 16, 64,
                    bf ? "MFMA bf16 256x256 (8 waves) or 128x128 (4 waves) tiles, K-step 32"
-                      : "fp32 VALU 64x64 tiles",
+                      : "MFMA fp32 128x128, 64x64 or 32x32 tiles (4 waves), K-step 16",
                    cfg->activation == BPT_RELU ? "relu" : "gelu", (long long)d.R, (long long)d.nbg, (long long)d.Rs,
                    (long long)cfg->Bq);
   return w < 0 ? 0 : std::min((size_t)w, n - 1);
