@@ -270,9 +270,7 @@ bpt_status bpt_embed_fwd(const bpt_embed_config* cfg, const int32_t* tokens, con
 /* Gradients of the embedding for an upstream dX [B*S, D] (cfg->grad_dtype):
  * dWte [V, D] fp32 = per vocabulary row, the sum of dX over the tokens equal to it
  * (a token outside [0, V) adds nothing); dWpe [S, D] fp32 = sum over the batch.
- * Both are OVERWRITTEN; NULL skips. dWte's rows are summed with floating-point
- * atomics, so the order of the additions into a repeated token's row, and with it
- * the last bits of that row, may differ between runs. */
+ * Both are OVERWRITTEN; NULL skips. Every row is summed in a fixed order. */
 bpt_status bpt_embed_bwd(const bpt_embed_config* cfg, const int32_t* tokens, const void* dX, float* dWte,
                          float* dWpe, void* stream);
 
