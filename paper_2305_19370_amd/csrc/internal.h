@@ -96,17 +96,16 @@ hipError_t layer_norm(Dt ti, Dt to, const void* x, int64_t ldx, const float* g, 
                       float eps, int use_stats, hipStream_t s);
 
 // out = resid + LN^T(dout), per row (resid may be null: 0); out2 (optional, type t2) gets
-// the same values.
-hipError_t layer_norm_bwd(Dt ti, const void* x, const float* mu, const float* rstd, const float* g,
-                          const float* dout, Dt tr, const void* resid, Dt to, void* out,
-                          Dt t2, void* out2, int64_t rows, int64_t D, hipStream_t s);
-
-// dgamma[d] = sum_r dout[r,d] * xhat[r,d]; dbeta[d] = sum_r dout[r,d] (overwrite).
-// `partial` is workspace of layer_norm_param_grad_ws(D) floats.
+// the same values. Unless both are null, dgamma[d] = sum_r dout[r,d] * xhat[r,d] and
+// dbeta[d] = sum_r dout[r,d] (overwrite; either may be null), through `partial`, workspace of
+// at least layer_norm_param_grad_ws(D) floats (more are used if there). dout is fp32, or bf16
+// where layer_norm_bwd_fused(D).
 size_t layer_norm_param_grad_ws(int64_t D);
-hipError_t layer_norm_param_grad(Dt ti, const void* x, const float* mu, const float* rstd,
-                                 const float* dout, float* dgamma, float* dbeta, float* partial,
-                                 int64_t rows, int64_t D, hipStream_t s);
+bool layer_norm_bwd_fused(int64_t D);
+hipError_t layer_norm_bwd(Dt ti, const void* x, const float* mu, const float* rstd, const float* g, Dt td,
+                          const void* dout, Dt tr, const void* resid, Dt to, void* out, Dt t2, void* out2,
+                          float* dgamma, float* dbeta, float* partial, int64_t partial_floats, int64_t rows, int64_t D,
+                          hipStream_t s);
 
 // out[c, r] = in[r, c] for r < rows, 0 for rows <= r < rows_store; batched over z.
 hipError_t transpose(Dt t, const void* in, int64_t ld_in, int64_t s_in, void* out, int64_t ld_out,
@@ -140,7 +139,7 @@ hipError_t mean_of(const float* x, int64_t n, float* out, hipStream_t s);
 // X[t] = Wte[tok[t]] + Wpe[t mod S] (Wpe may be null); NaN row for tok outside [0, V). D % 8 == 0.
 hipError_t embed_fwd(Dt t, const int32_t* tok, const void* Wte, const void* Wpe, void* X, int64_t rows,
                      int64_t S, int64_t D, int64_t V, hipStream_t s);
-// dWte = 0, then dWte[tok[t]] += dX[t] (fp32 atomics)
+// dWte[v] = sum of dX[t] over the tokens t with tok[t] = v, in a fixed order (overwrite)
 hipError_t embed_dwte(Dt t, const int32_t* tok, const void* dX, float* dWte, int64_t rows, int64_t D, int64_t V,
                       hipStream_t s);
 // dWpe[s] = sum_b dX[b S + s] (overwrite)
@@ -167,8 +166,5 @@ hipError_t dropout_add(const float* acc, Dt tr, const void* R, const float* bias
 // out = f * in over rows x D
 hipError_t dropout_scale(Dt ti, const void* in, Dt to, void* out, int64_t rows, int64_t D, const DropArgs& a,
                          hipStream_t s);
-
-// bytes (a multiple of 4) of zeros at p, by a kernel (no memset node in captured graphs)
-hipError_t fill_zero(void* p, int64_t bytes, hipStream_t s);
 
 }  // namespace bpt

@@ -162,7 +162,7 @@ struct BwdWs {
   void *wcat;
   void *vg, *gT, *dzT;
   void* gpT;             // GELU'(Z^T): fp32 on the fp32 path, fp16 on the bf16 path
-  float *dv, *dh, *dU, *ndelta, *nlse2, *partial, *scratch;
+  float *dv, *dh, *dU, *ndelta, *nlse2, *partial;
   void *dhe, *dhT, *dO, *dqkvT, *u;
   float* kpart;          // K-slice partials of the D x D weight gradients (null: no split)
   float* fpart;          // K-slice partials of dW1 / dW2 (null: no split)
@@ -207,7 +207,6 @@ BwdWs bwd_ws(const Dims& d, void* base, int64_t* total) {
   w.u = bp.take(d.T * d.D * d.E);
   w.dU = (float*)bp.take(d.T * d.D * 4);
   w.partial = (float*)bp.take((int64_t)layer_norm_param_grad_ws(std::max(d.D, d.F)) * 4);
-  w.scratch = (float*)bp.take(2 * std::max(d.D, d.F) * 4);
   const int kz = d.S % 64 == 0 ? ksplit(d.D, d.D, d.T) : 1;   // the whole-batch GEMMs below
   w.kpart = kz > 1 ? (float*)bp.take(kz * d.D * d.D * 4) : nullptr;
   const int fz = ksplit_cap(d.D, d.F);                      // dW1 and dW2 per FFN group
@@ -736,13 +735,15 @@ bpt_status bpt_layer_bwd(const bpt_config* cfg, const void* X, const bpt_params*
       first = false;
     }
   }
+  // Block sums of the LayerNorm parameter gradients: the FFN group's buffers, done with by
+  // then, when they hold more blocks than `partial`
+  const int64_t ffn_n = ((char*)w.dv - (char*)w.gT) / 4, part_n = (int64_t)layer_norm_param_grad_ws(std::max(D, F));
+  float* ln_part = ffn_n > part_n ? (float*)w.gT : w.partial;
+  const int64_t ln_part_n = std::max(ffn_n, part_n);
   // dh = dY + LN2^T(dv)
   RUN("layernorm.bwd", 0, (double)T * D * (4 + 4 + E_ + 4 + E_),
-      layer_norm_bwd(F32, sv.h, sv.mu2, sv.rstd2, p->ln2_g, w.dv, E, dY, F32, w.dh, E, w.dhe, T, D, s));
-  if (G.dln2_g || G.dln2_b)
-    RUN("reduce.layernorm", 0, (double)T * D * 8,
-        layer_norm_param_grad(F32, sv.h, sv.mu2, sv.rstd2, w.dv, G.dln2_g ? G.dln2_g : w.scratch,
-                              G.dln2_b ? G.dln2_b : w.scratch + D, w.partial, T, D, s));
+      layer_norm_bwd(F32, sv.h, sv.mu2, sv.rstd2, p->ln2_g, F32, w.dv, E, dY, F32, w.dh, E, w.dhe, G.dln2_g, G.dln2_b,
+                     ln_part, ln_part_n, T, D, s));
   if (G.db2) RUN("reduce.bias", 0, (double)T * D * E_, col_sum(E, dYf, D, T, D, G.db2, 0, w.partial, s));
   if (d.drop)   // the output projection sees dh through its dropout
     RUN("dropout.bwd", 0, (double)T * D * (4 + E_), dropout_scale(F32, w.dh, E, w.dhe, T, D, drop_args(*cfg, 0, 0), s));
@@ -842,11 +843,8 @@ bpt_status bpt_layer_bwd(const bpt_config* cfg, const void* X, const bpt_params*
     RUN("gemm.bwd_du", gemm_flops(g), gemm_bytes(g, E_, 4), gemm(E, EPI_STORE, F32, F32, g, s));
   }
   RUN("layernorm.bwd", 0, (double)T * D * (E_ + 4 + 4 + EO),
-      layer_norm_bwd(E, X, sv.mu1, sv.rstd1, p->ln1_g, w.dU, F32, w.dh, OUT, dX, OUT, nullptr, T, D, s));
-  if (G.dln1_g || G.dln1_b)
-    RUN("reduce.layernorm", 0, (double)T * D * (E_ + 4),
-        layer_norm_param_grad(E, X, sv.mu1, sv.rstd1, w.dU, G.dln1_g ? G.dln1_g : w.scratch,
-                              G.dln1_b ? G.dln1_b : w.scratch + D, w.partial, T, D, s));
+      layer_norm_bwd(E, X, sv.mu1, sv.rstd1, p->ln1_g, F32, w.dU, F32, w.dh, OUT, dX, OUT, nullptr, G.dln1_g, G.dln1_b,
+                     ln_part, ln_part_n, T, D, s));
   return BPT_OK;
 }
 
@@ -1004,7 +1002,8 @@ static bpt_status ln_check(const bpt_ln_config* c) {
   return st != BPT_OK ? st : dtype_ok(c->out_dtype, "out_dtype");
 }
 
-// workspace of bpt_ln_bwd: column-sum partials, then (bf16 dY) an fp32 copy of dY
+// workspace of bpt_ln_bwd: column-sum partials, then (bf16 dY) room for an fp32 copy of dY,
+// which only rows too long for the fused kernel need; the others take it all for partials
 static int64_t ln_ws_parts(const bpt_ln_config& c, int64_t* dy_off) {
   const int64_t part = rup((int64_t)layer_norm_param_grad_ws(c.D) * 4, kAlign);
   *dy_off = part;
@@ -1056,18 +1055,17 @@ bpt_status bpt_ln_bwd(const bpt_ln_config* cfg, const void* X, const float* g, c
   const Dt TI = dt_of(cfg->in_dtype);
   const int64_t I_ = cfg->in_dtype == BPT_BF16 ? 2 : 4;
   float* partial = (float*)ws;
-  const float* dy32 = (const float*)dY;
-  if (cfg->out_dtype == BPT_BF16) {
+  Dt TD = dt_of(cfg->out_dtype);
+  int64_t partial_n = need / 4;          // all of it, unless dY has to be widened below
+  if (TD == BF16 && !layer_norm_bwd_fused(D)) {
     float* c = (float*)off(ws, dy_off);
     RUN("gpt.ln_f_dy32", 0, (double)R * D * 6, bf16_to_f32(dY, c, R * D, s));
-    dy32 = c;
+    dY = c;
+    TD = F32;
+    partial_n = dy_off / 4;
   }
-  RUN("gpt.ln_f_bwd", 0, (double)R * D * (2 * I_ + 4) + (double)R * 8,
-      layer_norm_bwd(TI, X, mean, rstd, g, dy32, F32, nullptr, TI, dX, TI, nullptr, R, D, s));
-  if (dg) {
-    RUN("gpt.ln_f_params", 0, (double)R * D * (I_ + 4),
-        layer_norm_param_grad(TI, X, mean, rstd, dy32, dg, db, partial, R, D, s));
-  }
+  RUN("gpt.ln_f_bwd", 0, (double)R * D * (2 * I_ + (TD == BF16 ? 2 : 4)) + (double)R * 8,
+      layer_norm_bwd(TI, X, mean, rstd, g, TD, dY, F32, nullptr, TI, dX, TI, nullptr, dg, db, partial, partial_n, R, D, s));
   return BPT_OK;
 }
 

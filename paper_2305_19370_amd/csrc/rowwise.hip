@@ -3,6 +3,8 @@
 // backward's per-row Delta = rowsum(dO * O), transposes into the feature-major
 // layouts the MFMA kernels read, and a strided copy. All are HBM-bound; each
 // reads and writes every element once (LayerNorm re-reads its row from cache).
+#include <algorithm>
+
 #include "common.h"
 #include "internal.h"
 
@@ -55,34 +57,39 @@ template <> struct Vec8<bf16> {
 };
 
 // ------------------------------------------------------------------ LayerNorm forward
-// Rows of D = 512 NC: one wave per row holds the whole row in registers (NC chunks of 8
-// consecutive elements per lane, chunk c of lane l at columns 8 (l + 64 c)), so every
-// element is read once and written once. Two-pass mean / variance over the registers.
+// Rows of D <= 512 NC (D % 8 == 0): one wave per row holds the whole row in registers (NC
+// chunks of 8 consecutive elements per lane, chunk c of lane l at columns 8 (l + 64 c)), so
+// every element is read once and written once. Two-pass mean / variance over the registers.
 template <typename TI, typename TO, int NC>
 __global__ __launch_bounds__(256) void ln_fwd_reg_kernel(const TI* x, int64_t ldx, const float* g,
                                                          const float* bb, TO* out, int64_t ldo, float* mu,
-                                                         float* rstd, int64_t rows, float eps, int use_stats) {
-  constexpr int D = 512 * NC;
+                                                         float* rstd, int64_t rows, int D, float eps, int use_stats) {
   const int lane = threadIdx.x & 63;
   const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= rows) return;
   const TI* xr = x + row * ldx;
   float v[NC][8];
 #pragma unroll
-  for (int c = 0; c < NC; ++c) Vec8<TI>::load(xr + 8 * (lane + 64 * c), v[c]);
+  for (int c = 0; c < NC; ++c) {
+    const int d = 8 * (lane + 64 * c);
+    if (d < D) Vec8<TI>::load(xr + d, v[c]);
+  }
   float mean, rs;
   if (!use_stats) {
     float sm = 0.0f;
 #pragma unroll
     for (int c = 0; c < NC; ++c)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) sm += v[c][e];
+      for (int e = 0; e < 8; ++e) sm += 8 * (lane + 64 * c) < D ? v[c][e] : 0.0f;
     mean = warp_sum(sm) / (float)D;
     float q = 0.0f;
 #pragma unroll
     for (int c = 0; c < NC; ++c)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) q = fmaf(v[c][e] - mean, v[c][e] - mean, q);
+      for (int e = 0; e < 8; ++e) {
+        const float dv = 8 * (lane + 64 * c) < D ? v[c][e] - mean : 0.0f;
+        q = fmaf(dv, dv, q);
+      }
     rs = 1.0f / sqrtf(warp_sum(q) / (float)D + eps);
     if (lane == 0) {
       mu[row] = mean;
@@ -96,6 +103,7 @@ __global__ __launch_bounds__(256) void ln_fwd_reg_kernel(const TI* x, int64_t ld
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
     const int d = 8 * (lane + 64 * c);
+    if (d >= D) continue;
     float gv[8], bv[8];
     if (g) Vec8<float>::load(g + d, gv);
     if (bb) Vec8<float>::load(bb + d, bv);
@@ -164,47 +172,123 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const TI* x, int64_t ldx, c
 
 // ------------------------------------------------------------------ LayerNorm backward
 // dz = rstd * (gd - mean(gd) - xhat * mean(gd * xhat)), gd = dout * gamma; out = resid + dz.
-// Rows of D = 512 NC, row of x and of dout held in registers as in ln_fwd_reg_kernel.
-template <typename TI, typename TR, typename TO, typename T2, int NC>
+// Rows of D <= 512 NC WPR (D % 8 == 0): WPR waves per row hold the row of x and of dout in
+// registers, wave w its chunks NC w .. NC w + NC - 1 of 512 columns.
+//
+// PARAM also sums the parameter gradients in the same pass: a workgroup walks rows
+// blockIdx.x, + gridDim.x, ... (four at a time with WPR = 1), its lanes keep the sums of
+// their columns, and the block's sums go to partial [2][gridDim.x][D] for chunk_reduce.
+// HBM-bound: x and dout are read once for all three gradients. Final LayerNorm of 16384 x
+// 2048 bf16 rows, dX and parameters: 45 us (4.5 TB/s) and 6.6 for the reduction, against
+// 124 us in four passes (dout widened to fp32, dX, partial sums, reduction).
+template <typename TI, typename TD, typename TR, typename TO, typename T2, int NC, int WPR, bool PARAM>
 __global__ __launch_bounds__(256) void ln_bwd_reg_kernel(const TI* x, const float* mu, const float* rstd,
-                                                         const float* g, const float* dout, const TR* resid,
-                                                         TO* out, T2* out2, int64_t rows) {
-  constexpr int D = 512 * NC;
-  const int lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= rows) return;
-  const float m = mu[row], rs = rstd[row];
-  float xh[NC][8], gd[NC][8];
+                                                         const float* g, const TD* dout, const TR* resid,
+                                                         TO* out, T2* out2, float* partial, int64_t rows, int D) {
+  static_assert(WPR == 1 || WPR == 4, "waves per row");
+  static_assert(WPR == 4 || !PARAM || NC <= 4, "LDS of the block sums");
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int col0 = 8 * (lane + (WPR == 4 ? 64 * NC * wave : 0));
+  __shared__ float red[2][4][2];
+  __shared__ __attribute__((aligned(16))) float sums[PARAM && WPR == 1 ? 2 * 512 * NC : 1];
+  float ag[PARAM ? NC : 1][8], ab[PARAM ? NC : 1][8];
+  if constexpr (PARAM) {
 #pragma unroll
-  for (int c = 0; c < NC; ++c) {
-    const int d = 8 * (lane + 64 * c);
-    Vec8<TI>::load(x + row * D + d, xh[c]);
-    Vec8<float>::load(dout + row * D + d, gd[c]);
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) ag[c][e] = ab[c][e] = 0.0f;
   }
-  float s1 = 0.0f, s2 = 0.0f;
+  const int64_t step = (int64_t)gridDim.x * (WPR == 4 ? 1 : 4);
+  int par = 0;
+  for (int64_t row = WPR == 4 ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * 4 + wave; row < rows; row += step) {
+    const float m = mu[row], rs = rstd[row];
+    float xh[NC][8], gd[NC][8];
 #pragma unroll
-  for (int c = 0; c < NC; ++c) {
-    float gv[8];
-    if (g) Vec8<float>::load(g + 8 * (lane + 64 * c), gv);
+    for (int c = 0; c < NC; ++c) {
+      const int d = col0 + 512 * c;
+      if (d < D) {
+        Vec8<TI>::load(x + row * D + d, xh[c]);
+        Vec8<TD>::load(dout + row * D + d, gd[c]);
+      }
+    }
+    float s1 = 0.0f, s2 = 0.0f;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      if (g) gd[c][e] *= gv[e];
-      xh[c][e] = (xh[c][e] - m) * rs;
-      s1 += gd[c][e];
-      s2 = fmaf(gd[c][e], xh[c][e], s2);
+    for (int c = 0; c < NC; ++c) {
+      const int d = col0 + 512 * c;
+      if (d < D) {
+        float gv[8];
+        if (g) Vec8<float>::load(g + d, gv);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          xh[c][e] = (xh[c][e] - m) * rs;
+          if constexpr (PARAM) {
+            ag[c][e] = fmaf(gd[c][e], xh[c][e], ag[c][e]);
+            ab[c][e] += gd[c][e];
+          }
+          if (g) gd[c][e] *= gv[e];
+          s1 += gd[c][e];
+          s2 = fmaf(gd[c][e], xh[c][e], s2);
+        }
+      }
+    }
+    s1 = warp_sum(s1);
+    s2 = warp_sum(s2);
+    if constexpr (WPR == 4) {                 // two buffers in turn: one barrier per row
+      if (lane == 0) {
+        red[par][wave][0] = s1;
+        red[par][wave][1] = s2;
+      }
+      __syncthreads();
+      s1 = ((red[par][0][0] + red[par][1][0]) + red[par][2][0]) + red[par][3][0];
+      s2 = ((red[par][0][1] + red[par][1][1]) + red[par][2][1]) + red[par][3][1];
+      par ^= 1;
+    }
+    s1 /= (float)D;
+    s2 /= (float)D;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const int d = col0 + 512 * c;
+      if (d < D) {
+        float rv[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        if (resid) Vec8<TR>::load(resid + row * D + d, rv);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) rv[e] += rs * (gd[c][e] - s1 - xh[c][e] * s2);
+        Vec8<TO>::store(out + row * D + d, rv);
+        if (out2) Vec8<T2>::store(out2 + row * D + d, rv);
+      }
     }
   }
-  s1 = warp_sum(s1) / (float)D;
-  s2 = warp_sum(s2) / (float)D;
+  if constexpr (PARAM) {
+    if constexpr (WPR == 1) {                 // the four waves' sums, in wave order
+      for (int w = 0; w < 4; ++w) {
+        if (wave == w) {
 #pragma unroll
-  for (int c = 0; c < NC; ++c) {
-    const int d = 8 * (lane + 64 * c);
-    float rv[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    if (resid) Vec8<TR>::load(resid + row * D + d, rv);
+          for (int c = 0; c < NC; ++c) {
+            float* sg = sums + 512 * c + 8 * lane;
+            float* sb = sg + 512 * NC;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) rv[e] += rs * (gd[c][e] - s1 - xh[c][e] * s2);
-    Vec8<TO>::store(out + row * D + d, rv);
-    if (out2) Vec8<T2>::store(out2 + row * D + d, rv);
+            for (int e = 0; e < 8; ++e) {
+              sg[e] = w ? sg[e] + ag[c][e] : ag[c][e];
+              sb[e] = w ? sb[e] + ab[c][e] : ab[c][e];
+            }
+          }
+        }
+        __syncthreads();
+      }
+      for (int d = 4 * threadIdx.x; d < D; d += 4 * 256) {
+        *(f32x4*)(partial + (int64_t)blockIdx.x * D + d) = *(const f32x4*)(sums + d);
+        *(f32x4*)(partial + ((int64_t)gridDim.x + blockIdx.x) * D + d) = *(const f32x4*)(sums + 512 * NC + d);
+      }
+    } else {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        const int d = col0 + 512 * c;
+        if (d < D) {
+          Vec8<float>::store(partial + (int64_t)blockIdx.x * D + d, ag[c]);
+          Vec8<float>::store(partial + ((int64_t)gridDim.x + blockIdx.x) * D + d, ab[c]);
+        }
+      }
+    }
   }
 }
 
@@ -270,37 +354,38 @@ __global__ __launch_bounds__(256) void ln_param_partial_kernel(const TI* x, cons
   partial[(int64_t)(kChunks + blockIdx.y) * D + d] = sb;
 }
 
-// Second stage: out0[d] (+)= sum_c partial[c D + d] and out1[d] (+)= sum_c partial[(kChunks + c) D + d].
-// A block of four waves per 64 columns; wave w sums chunks w, w + 4, ... (eight loads in flight
-// per lane) and the four wave sums are added through LDS in wave order.
-__global__ __launch_bounds__(256) void chunk_reduce_kernel(const float* partial, float* out0,
+// Second stage: out0[d] (+)= sum_c partial[c D + d] and out1[d] (+)= sum_c partial[(nch + c) D + d],
+// c < nch. A block per 16 columns: 16 lanes of 64 bytes, 16 groups of chunks; group k sums
+// chunks k, k + 16, ... (eight loads in flight) and the group sums are added through LDS in
+// group order.
+__global__ __launch_bounds__(256) void chunk_reduce_kernel(const float* partial, int nch, float* out0,
                                                            float* out1, int64_t D, int accumulate) {
-  __shared__ float red[2][4][64];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int64_t d = (int64_t)blockIdx.x * 64 + lane;
-  const bool ok = d < D;
+  __shared__ float red[2][16][17];
+  const int cl = threadIdx.x & 15, k = threadIdx.x >> 4;
+  const int64_t d = (int64_t)blockIdx.x * 16 + cl;
   float s0 = 0.0f, s1 = 0.0f;
-  if (ok) {
-    for (int c0 = wv; c0 < kChunks; c0 += 32) {
-      float v0[8], v1[8];
+  if (d < D) {
+    for (int c0 = k; c0 < nch; c0 += 64) {
+      float v0[4], v1[4];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int c = c0 + 4 * u;
-        v0[u] = c < kChunks ? partial[(int64_t)c * D + d] : 0.0f;
-        v1[u] = (out1 && c < kChunks) ? partial[(int64_t)(kChunks + c) * D + d] : 0.0f;
+      for (int u = 0; u < 4; ++u) {
+        const int c = c0 + 16 * u;
+        v0[u] = c < nch ? partial[(int64_t)c * D + d] : 0.0f;
+        v1[u] = (out1 && c < nch) ? partial[(int64_t)(nch + c) * D + d] : 0.0f;
       }
 #pragma unroll
-      for (int u = 0; u < 8; ++u) { s0 += v0[u]; s1 += v1[u]; }
+      for (int u = 0; u < 4; ++u) { s0 += v0[u]; s1 += v1[u]; }
     }
   }
-  red[0][wv][lane] = s0;
-  red[1][wv][lane] = s1;
+  red[0][k][cl] = s0;
+  red[1][k][cl] = s1;
   __syncthreads();
-  if (wv == 0 && ok) {
-    s0 = ((red[0][0][lane] + red[0][1][lane]) + red[0][2][lane]) + red[0][3][lane];
-    s1 = ((red[1][0][lane] + red[1][1][lane]) + red[1][2][lane]) + red[1][3][lane];
-    if (out0) out0[d] = accumulate ? out0[d] + s0 : s0;
-    if (out1) out1[d] = accumulate ? out1[d] + s1 : s1;
+  if (k < 2 && d < D) {
+    float s = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s += red[k][i][cl];
+    float* out = k ? out1 : out0;
+    if (out) out[d] = accumulate ? out[d] + s : s;
   }
 }
 
@@ -610,10 +695,6 @@ __global__ __launch_bounds__(1024) void mean_kernel(const float* x, int64_t n, f
   if (threadIdx.x == 0) out[0] = part[0] / (float)n;
 }
 
-__global__ __launch_bounds__(256) void fill_zero_kernel(uint32_t* p, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) p[i] = 0u;
-}
-
 #define BPT_T(dt, T, ...) \
   do {                   \
     if ((dt) == F32) {   \
@@ -630,20 +711,24 @@ hipError_t layer_norm(Dt ti, Dt to, const void* x, int64_t ldx, const float* g, 
                       int use_stats, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
   const dim3 grid((unsigned)((rows + 3) / 4));
-  // register-resident rows when D = 512 NC and every row starts 16-byte aligned
-  const bool vec = D % 512 == 0 && ldx % 8 == 0 && ldo % 8 == 0 && ((uintptr_t)x & 15) == 0 &&
+  // register-resident rows when D % 8 == 0, D <= 8192 and every row starts 16-byte aligned
+  const bool vec = D % 8 == 0 && D <= 8192 && ldx % 8 == 0 && ldo % 8 == 0 && ((uintptr_t)x & 15) == 0 &&
                    ((uintptr_t)out & 15) == 0 && ((uintptr_t)g & 15) == 0 && ((uintptr_t)b & 15) == 0;
 #define BPT_LN_FWD(NCV)                                                                                  \
   BPT_T(ti, TI, BPT_T(to, TO,                                                                            \
         hipLaunchKernelGGL((ln_fwd_reg_kernel<TI, TO, NCV>), grid, dim3(256), 0, s, (const TI*)x, ldx, g, \
-                           b, (TO*)out, ldo, mu, rstd, rows, eps, use_stats)))
-  switch (vec ? D / 512 : 0) {
-    case 1: BPT_LN_FWD(1); return hipGetLastError();
-    case 2: BPT_LN_FWD(2); return hipGetLastError();
-    case 4: BPT_LN_FWD(4); return hipGetLastError();
-    case 8: BPT_LN_FWD(8); return hipGetLastError();
-    case 10: BPT_LN_FWD(10); return hipGetLastError();
-    default: break;
+                           b, (TO*)out, ldo, mu, rstd, rows, (int)D, eps, use_stats)));                  \
+  return hipGetLastError()
+  if (vec) {                                // the least chunk count that holds the row
+    const int64_t nc = (D + 511) / 512;
+    if (nc <= 1) { BPT_LN_FWD(1); }
+    if (nc <= 2) { BPT_LN_FWD(2); }
+    if (nc <= 3) { BPT_LN_FWD(3); }
+    if (nc <= 4) { BPT_LN_FWD(4); }
+    if (nc <= 6) { BPT_LN_FWD(6); }
+    if (nc <= 8) { BPT_LN_FWD(8); }
+    if (nc <= 10) { BPT_LN_FWD(10); }
+    BPT_LN_FWD(16);
   }
 #undef BPT_LN_FWD
   BPT_T(ti, TI, BPT_T(to, TO,
@@ -652,38 +737,91 @@ hipError_t layer_norm(Dt ti, Dt to, const void* x, int64_t ldx, const float* g, 
   return hipGetLastError();
 }
 
-hipError_t layer_norm_bwd(Dt ti, const void* x, const float* mu, const float* rstd, const float* g,
-                          const float* dout, Dt tr, const void* resid, Dt to, void* out, Dt t2,
-                          void* out2, int64_t rows, int64_t D, hipStream_t s) {
-  if (rows <= 0) return hipSuccess;
-  const dim3 grid((unsigned)((rows + 3) / 4));
-  const bool vec = D % 512 == 0 && ((uintptr_t)x & 15) == 0 && ((uintptr_t)dout & 15) == 0 &&
-                   ((uintptr_t)resid & 15) == 0 && ((uintptr_t)out & 15) == 0 && ((uintptr_t)out2 & 15) == 0 &&
-                   ((uintptr_t)g & 15) == 0;
-#define BPT_LN_BWD(NCV)                                                                                  \
-  BPT_T(ti, TI, BPT_T(tr, TR, BPT_T(to, TO, BPT_T(t2, T2,                                               \
-        hipLaunchKernelGGL((ln_bwd_reg_kernel<TI, TR, TO, T2, NCV>), grid, dim3(256), 0, s, (const TI*)x, \
-                           mu, rstd, g, dout, (const TR*)resid, (TO*)out, (T2*)out2, rows)))))
-  switch (vec ? D / 512 : 0) {
-    case 1: BPT_LN_BWD(1); return hipGetLastError();
-    case 2: BPT_LN_BWD(2); return hipGetLastError();
-    case 4: BPT_LN_BWD(4); return hipGetLastError();
-    case 8: BPT_LN_BWD(8); return hipGetLastError();
-    case 10: BPT_LN_BWD(10); return hipGetLastError();
-    default: break;
-  }
+// Workgroups of a PARAM launch, each leaving one partial row per sum: about two per CU
+// (8 waves, enough loads in flight for HBM), never fewer than 8 rows each, and no more than
+// the partial buffer holds.
+static int ln_param_blocks(int64_t rows, int64_t D, int64_t partial_floats) {
+  const int64_t fit = partial_floats / (2 * D);
+  return (int)std::max<int64_t>(1, std::min<int64_t>({512, (rows + 7) / 8, fit}));
+}
+
+template <typename TI, typename TD, typename TR, typename TO, typename T2>
+static hipError_t ln_bwd_typed(const void* x, const float* mu, const float* rstd, const float* g, const void* dout,
+                               const void* resid, void* out, void* out2, float* dgamma, float* dbeta, float* partial,
+                               int64_t partial_floats, int64_t rows, int64_t D, hipStream_t s) {
+  const bool param = dgamma || dbeta;
+  const int nblk = param ? ln_param_blocks(rows, D, partial_floats) : 0;
+#define BPT_LN_BWD(NCV, WPRV)                                                                                     \
+  do {                                                                                                            \
+    if (param)                                                                                                    \
+      hipLaunchKernelGGL((ln_bwd_reg_kernel<TI, TD, TR, TO, T2, NCV, WPRV, true>), dim3(nblk), dim3(256), 0, s,   \
+                         (const TI*)x, mu, rstd, g, (const TD*)dout, (const TR*)resid, (TO*)out, (T2*)out2,       \
+                         partial, rows, (int)D);                                                                  \
+    else                                                                                                          \
+      hipLaunchKernelGGL((ln_bwd_reg_kernel<TI, TD, TR, TO, T2, NCV, WPRV, false>),                               \
+                         dim3((unsigned)(WPRV == 4 ? rows : (rows + 3) / 4)), dim3(256), 0, s, (const TI*)x, mu,  \
+                         rstd, g, (const TD*)dout, (const TR*)resid, (TO*)out, (T2*)out2, (float*)nullptr, rows,  \
+                         (int)D);                                                                                 \
+  } while (0)
+  const int64_t nc = (D + 511) / 512;       // up to 2048 columns a wave holds the row, beyond that four waves do
+  if (nc <= 1) BPT_LN_BWD(1, 1);
+  else if (nc <= 2) BPT_LN_BWD(2, 1);
+  else if (nc <= 4) BPT_LN_BWD(4, 1);
+  else if (nc <= 8) BPT_LN_BWD(2, 4);
+  else if (nc <= 12) BPT_LN_BWD(3, 4);
+  else BPT_LN_BWD(4, 4);
 #undef BPT_LN_BWD
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || !param) return e;
+  hipLaunchKernelGGL(chunk_reduce_kernel, dim3((unsigned)((D + 15) / 16)), dim3(256), 0, s, partial, nblk, dgamma,
+                     dbeta, D, 0);
+  return hipGetLastError();
+}
+
+static hipError_t layer_norm_param_grad(Dt ti, const void* x, const float* mu, const float* rstd, const float* dout,
+                                        float* dgamma, float* dbeta, float* partial, int64_t rows, int64_t D,
+                                        hipStream_t s);
+
+bool layer_norm_bwd_fused(int64_t D) { return D % 8 == 0 && D <= 8192; }
+
+hipError_t layer_norm_bwd(Dt ti, const void* x, const float* mu, const float* rstd, const float* g, Dt td,
+                          const void* dout, Dt tr, const void* resid, Dt to, void* out, Dt t2, void* out2,
+                          float* dgamma, float* dbeta, float* partial, int64_t partial_floats, int64_t rows, int64_t D,
+                          hipStream_t s) {
+  if (rows <= 0) return hipSuccess;
+  const bool param = dgamma || dbeta;
+  const uintptr_t all = (uintptr_t)x | (uintptr_t)dout | (uintptr_t)resid | (uintptr_t)out | (uintptr_t)out2 |
+                        (uintptr_t)g | (uintptr_t)partial;
+  if (layer_norm_bwd_fused(D) && (all & 15) == 0) {
+    // the type combinations in use: LN2 (dh and its rounded copy), LN1 (dX), the final LayerNorm
+#define BPT_LN_IF(A, TD_, R, O, O2, TI, TD, TR, TO, T2)                                                          \
+  if (ti == A && td == TD_ && (!resid || tr == R) && to == O && (!out2 || t2 == O2))                             \
+    return ln_bwd_typed<TI, TD, TR, TO, T2>(x, mu, rstd, g, dout, resid, out, out2, dgamma, dbeta, partial,      \
+                                            partial_floats, rows, D, s)
+    BPT_LN_IF(F32, F32, F32, F32, F32, float, float, float, float, float);
+    BPT_LN_IF(F32, F32, BF16, F32, BF16, float, float, bf16, float, bf16);
+    BPT_LN_IF(F32, F32, F32, BF16, BF16, float, float, float, bf16, bf16);
+    BPT_LN_IF(BF16, F32, F32, F32, F32, bf16, float, float, float, float);
+    BPT_LN_IF(BF16, F32, F32, BF16, BF16, bf16, float, float, bf16, bf16);
+    BPT_LN_IF(F32, BF16, F32, F32, F32, float, bf16, float, float, float);
+    BPT_LN_IF(BF16, BF16, F32, BF16, BF16, bf16, bf16, float, bf16, bf16);
+#undef BPT_LN_IF
+  }
+  if (td != F32) return hipErrorInvalidValue;       // the caller widens dout for rows this long
+  const dim3 grid((unsigned)((rows + 3) / 4));
   BPT_T(ti, TI, BPT_T(tr, TR, BPT_T(to, TO, BPT_T(t2, T2,
         hipLaunchKernelGGL((ln_bwd_kernel<TI, TR, TO, T2>), grid, dim3(256), 0, s, (const TI*)x, mu,
-                           rstd, g, dout, (const TR*)resid, (TO*)out, (T2*)out2, rows, D)))));
-  return hipGetLastError();
+                           rstd, g, (const float*)dout, (const TR*)resid, (TO*)out, (T2*)out2, rows, D)))));
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || !param) return e;
+  return layer_norm_param_grad(ti, x, mu, rstd, (const float*)dout, dgamma, dbeta, partial, rows, D, s);
 }
 
 size_t layer_norm_param_grad_ws(int64_t D) { return (size_t)2 * kChunks * (size_t)D; }
 
-hipError_t layer_norm_param_grad(Dt ti, const void* x, const float* mu, const float* rstd,
-                                 const float* dout, float* dgamma, float* dbeta, float* partial,
-                                 int64_t rows, int64_t D, hipStream_t s) {
+static hipError_t layer_norm_param_grad(Dt ti, const void* x, const float* mu, const float* rstd, const float* dout,
+                                        float* dgamma, float* dbeta, float* partial, int64_t rows, int64_t D,
+                                        hipStream_t s) {
   if (D % 8 == 0 && ((uintptr_t)x & 15) == 0 && ((uintptr_t)dout & 15) == 0 && ((uintptr_t)partial & 15) == 0) {
     const dim3 grid8((unsigned)((D + 511) / 512), kChunks);
     BPT_T(ti, TI, hipLaunchKernelGGL((ln_param_partial8_kernel<TI>), grid8, dim3(256), 0, s, (const TI*)x,
@@ -695,7 +833,7 @@ hipError_t layer_norm_param_grad(Dt ti, const void* x, const float* mu, const fl
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(chunk_reduce_kernel, dim3((unsigned)((D + 63) / 64)), dim3(256), 0, s, partial,
+  hipLaunchKernelGGL(chunk_reduce_kernel, dim3((unsigned)((D + 15) / 16)), dim3(256), 0, s, partial, kChunks,
                      dgamma, dbeta, D, 0);
   return hipGetLastError();
 }
@@ -713,7 +851,7 @@ hipError_t col_sum(Dt t, const void* in, int64_t ld, int64_t rows, int64_t cols,
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(chunk_reduce_kernel, dim3((unsigned)((cols + 63) / 64)), dim3(256), 0, s, partial,
+  hipLaunchKernelGGL(chunk_reduce_kernel, dim3((unsigned)((cols + 15) / 16)), dim3(256), 0, s, partial, kChunks,
                      out, (float*)nullptr, cols, accumulate);
   return hipGetLastError();
 }
@@ -797,15 +935,6 @@ hipError_t sum_slices(const float* part, int nz, int64_t n, float* out, int accu
   if (n % 4 != 0) return hipErrorInvalidValue;
   hipLaunchKernelGGL(sum_slices_kernel, dim3((unsigned)((n / 4 + 255) / 256)), dim3(256), 0, s, part, nz, n, out,
                      accumulate);
-  return hipGetLastError();
-}
-
-hipError_t fill_zero(void* p, int64_t bytes, hipStream_t s) {
-  if (bytes <= 0) return hipSuccess;
-  if (bytes % 4 != 0) return hipErrorInvalidValue;
-  const int64_t n = bytes / 4;
-  const unsigned g = (unsigned)((n + 255) / 256 < 1024 ? (n + 255) / 256 : 1024);
-  hipLaunchKernelGGL(fill_zero_kernel, dim3(g), dim3(256), 0, s, (uint32_t*)p, n);
   return hipGetLastError();
 }
 

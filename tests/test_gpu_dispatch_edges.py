@@ -1,9 +1,11 @@
 """Sizes at the edges of kernel tiles and of the rules that choose between kernels, against
 the float64 oracle under the gates of tests/gpu_util.py."""
 import pytest
+import torch
 
 from bpt_inputs import make_inputs, small_workload
 from gpu_util import run_gpu, run_oracle, say
+from paper_2305_19370_amd import bpt
 from test_gpu_parity import compare_all
 
 pytestmark = pytest.mark.gpu
@@ -21,3 +23,65 @@ def test_f32_tile_edges(B, S, D, H, F, causal):
     gpu = run_gpu(w, inp, qkv_grads=True)
     Yr, _, g = run_oracle(w, inp)
     compare_all(w, inp, gpu, Yr, g, "fp32", w.name)
+
+
+# token embedding gradient: rows owned by workgroups, tokens in chunks of 16384 and lists of 2048, rows named
+# by many tokens of a list spanning the waves, columns in slices of 512
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("T,D,V", [(1, 8, 1), (33, 504, 3), (8192, 520, 2), (8193, 64, 257), (16385, 1032, 50),
+                                   (3000, 512, 70001), (40000, 512, 3)])
+def test_embedding_gradient(dtype, T, D, V):
+    say(f"case embed {dtype} T={T} D={D} V={V}")
+    g = torch.Generator().manual_seed(5)
+    tok = torch.pow(float(V + 1), torch.rand(T, generator=g)).long().sub_(1).clamp_(0, V - 1)   # low ids frequent
+    tok[::7] = V                                      # outside the vocabulary: adds nothing
+    tok[3::11] = -1
+    dX = torch.randn(T, D, generator=g).to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    cfg = bpt.make_embed_config(1, T, D, V, dtype=dtype)
+    outs = []
+    for _ in range(2):
+        dWte = torch.full((V, D), float("nan"), device="cuda")
+        bpt.embed_bwd(cfg, tok.int().cuda(), dX.cuda(), dWte, None)
+        outs.append(dWte.cpu())
+    assert torch.equal(outs[0], outs[1])              # fixed order of the sums
+    ok = (tok >= 0) & (tok < V)
+    ref = torch.zeros(V, D, dtype=torch.float64).index_add_(0, tok[ok], dX[ok].double())
+    # n additions in float32: error <= n 2^-24 sum |terms|
+    mag = torch.zeros(V, D, dtype=torch.float64).index_add_(0, tok[ok], dX[ok].double().abs())
+    n = torch.bincount(tok[ok], minlength=V).double()[:, None]
+    assert ((outs[0].double() - ref).abs() <= n * 2.0 ** -24 * mag).all()
+
+
+# final LayerNorm: rows in one wave (up to 512, 1024, 1536 / 2048 columns), in four waves (up
+# to 4096, 6144, 8192), or walked (beyond); a partial last group of 512 columns; few rows and
+# more rows than workgroups
+@pytest.mark.parametrize("in_dtype,out_dtype", [("bf16", "bf16"), ("f32", "f32"), ("bf16", "f32"), ("f32", "bf16")])
+@pytest.mark.parametrize("rows,D,affine", [(1, 8, True), (4100, 512, True), (9, 520, True), (700, 1544, False),
+                                           (33, 2048, True), (4099, 2056, True), (5, 4104, True), (17, 6152, True),
+                                           (40, 8192, False), (40, 8200, True)])
+def test_final_layernorm(in_dtype, out_dtype, rows, D, affine):
+    say(f"case ln {in_dtype}->{out_dtype} rows={rows} D={D} affine={affine}")
+    dt = {"bf16": torch.bfloat16, "f32": torch.float32}
+    g = torch.Generator().manual_seed(7)
+    X = (torch.randn(rows, D, generator=g) + 0.5).to(dt[in_dtype])
+    dY = torch.randn(rows, D, generator=g).to(dt[out_dtype])
+    gam = torch.randn(D, generator=g) * 0.1 + 1 if affine else None
+    bet = torch.randn(D, generator=g) * 0.1 if affine else None
+    dev = lambda t: None if t is None else t.cuda()
+    cfg = bpt.make_ln_config(rows, D, in_dtype=in_dtype, out_dtype=out_dtype)
+    Xg, dYg, gg, bg = dev(X), dev(dY), dev(gam), dev(bet)
+    Y, dX = torch.empty_like(dYg), torch.empty_like(Xg)
+    mean, rstd, dg, db = (torch.empty(n, device="cuda") for n in (rows, rows, D, D))
+    ws = torch.empty(bpt.ln_workspace_bytes(cfg), dtype=torch.uint8, device="cuda")
+    bpt.ln_fwd(cfg, Xg, gg, bg, Y, mean, rstd)
+    bpt.ln_bwd(cfg, Xg, gg, mean, rstd, dYg, dX, dg, db, ws)
+    x = X.double().requires_grad_()
+    gr = (gam.double() if affine else torch.ones(D, dtype=torch.float64)).requires_grad_()
+    br = (bet.double() if affine else torch.zeros(D, dtype=torch.float64)).requires_grad_()
+    y = torch.nn.functional.layer_norm(x, (D,), gr, br, 1e-5)
+    y.backward(dY.double())
+    for name, got, ref, od in (("Y", Y, y.detach(), out_dtype), ("dX", dX, x.grad, in_dtype), ("dg", dg, gr.grad, "f32"),
+                               ("db", db, br.grad, "f32")):
+        # float32 sums (1e-4 of the RMS, the fp32 gate) and, for a bf16 result, half an ulp
+        lim = 1e-4 * ref.square().mean().sqrt() + (2.0 ** -8 * ref.abs() if od == "bf16" else 1e-5 * ref.abs())
+        assert ((got.cpu().double() - ref).abs() <= lim).all(), name
