@@ -14,6 +14,7 @@
 // banks. fp32 path: the same structure on v_mfma_f32_16x16x4_f32 (gemm_f32_kernel).
 #include "common.h"
 #include "internal.h"
+#include <cmath>
 #include <type_traits>
 
 namespace bpt {
@@ -288,7 +289,60 @@ BPT_DEV void tr_slot(int slot, int& row, int& col, int cols_left) {
   col = 8 * lc < cols_left - 8 ? 8 * lc : cols_left - 8;
 }
 
-template <int BM, int BN, int EPI, typename CT, typename RT, bool TA = false, bool TB = false, int NWN = 2>
+// Zeros that K-major operands read past the end of K when both are K-major.
+__device__ const u32x4 k_zero16 = {0u, 0u, 0u, 0u};
+
+// Forms of the operands that cost the main loop or the argument registers something, so that
+// they are kernels of their own: K-major A rows in segments (seg_pitch), B from three
+// matrices along K (kper), columns of three matrices (nper).
+enum KForm { KF_SEG = 1, KF_KPER = 2, KF_NPER = 4 };
+
+// The K range of grid slice z in stages of BK (ksplit: fp32 results that are only stored)
+template <int BK, int EPI, typename CT>
+BPT_DEV void k_range(const GemmArgs& a, int64_t z, int& kb, int& nk) {
+  const int total = (int)((a.K + BK - 1) / BK);
+  kb = 0;
+  nk = total;
+  if constexpr (EPI == EPI_STORE && sizeof(CT) == 4) {
+    if (a.ksplit > 1) {
+      const int per = (total + a.ksplit - 1) / a.ksplit;
+      kb = (int)z * per;
+      nk = total - kb < per ? (total - kb > 0 ? total - kb : 0) : per;
+    }
+  }
+}
+
+// The operand and result pointers of a tile whose columns belong to one of three matrices
+template <bool TB, typename T, typename CT>
+BPT_DEV void tile_of_three(GemmArgs& a, int64_t n0, const T*& B) {
+  const int w = n0 >= 2 * a.nper ? 2 : n0 >= a.nper ? 1 : 0;
+  const int64_t n = n0 - w * a.nper;
+  // selects, not an index: the arguments stay in scalar registers
+  if (a.Bx[0]) B = (const T*)(w == 2 ? a.Bx[2] : w ? a.Bx[1] : a.Bx[0]) + (TB ? n : n * a.ldb);
+  if (a.Cx[0]) a.C = (CT*)(w == 2 ? a.Cx[2] : w ? a.Cx[1] : a.Cx[0]) - w * a.nper;   // indexed by the global column
+  if (w) a.alpha = 1.0f;
+}
+
+// Rows of a K-major operand in segments (GemmArgs::seg_pitch): k index of the current segment
+// and how far its rows lie before their k index. Stages are visited in increasing order.
+struct KSegs {
+  int64_t k0 = 0, shift = 0;
+  BPT_DEV void init(const GemmArgs& a, int64_t k) {
+    const int64_t q = k / a.seg_pitch;
+    k0 = q * a.seg_pitch;
+    shift = q * (a.seg_pitch - a.seg_rows);
+  }
+  BPT_DEV void advance(const GemmArgs& a, int64_t k) {
+    if (k >= k0 + a.seg_pitch) {
+      k0 += a.seg_pitch;
+      shift += a.seg_pitch - a.seg_rows;
+    }
+  }
+  BPT_DEV int64_t limit(const GemmArgs& a) const { return k0 - shift + a.seg_rows; }   // past the last existing row
+};
+
+template <int BM, int BN, int EPI, typename CT, typename RT, bool TA = false, bool TB = false, int NWN = 2,
+          int KF = 0>
 __global__ __launch_bounds__(128 * NWN, 1) void gemm_bf16_kernel(GemmArgs a) {
   using Cfg = TileCfg<BM, BN, NWN>;
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -315,7 +369,9 @@ __global__ __launch_bounds__(128 * NWN, 1) void gemm_bf16_kernel(GemmArgs a) {
   const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN, z = blockIdx.z;
   const bf16* A = (const bf16*)a.A + z * a.sA + (TA ? m0 : m0 * a.lda);
   const bf16* B = (const bf16*)a.B + z * a.sB + (TB ? n0 : n0 * a.ldb);
-  const int nk = (int)(a.K / Cfg::BK);
+  int kb, nk;                                          // first stage and number of stages
+  k_range<Cfg::BK, EPI, CT>(a, z, kb, nk);
+  if constexpr (KF & KF_NPER) tile_of_three<TB, bf16, CT>(a, n0, B);
   // transposed operands: readable k rows and columns (from the tile's first column)
   const int64_t arows = a.a_rows > 0 ? a.a_rows : a.K, brows = a.b_rows > 0 ? a.b_rows : a.K;
   const int acols = (int)((a.a_cols > 0 ? a.a_cols : a.M) - m0);
@@ -360,28 +416,37 @@ __global__ __launch_bounds__(128 * NWN, 1) void gemm_bf16_kernel(GemmArgs a) {
   // LDS address of the tile ring (the copies take LDS addresses, not generic pointers)
   const uint32_t ring = __builtin_amdgcn_readfirstlane(
       (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem);
-  // A transposed operand's stage is k rows k0 .. k0+31; rows from x_rows on are clamped to
-  // the last readable row (the caller guarantees the other operand is zero there).
-  auto tr_src = [&](const bf16* X, int64_t ld, int64_t xrows, int cols, int k0, int blk, int64_t off,
+  // A transposed operand's stage is 32 rows from r0 on; rows from xrows on are clamped to
+  // the last readable row (the caller guarantees the other operand is zero there), or, with
+  // both operands transposed, read as zeros.
+  auto tr_src = [&](const bf16* X, int64_t ld, int64_t xrows, int cols, int64_t r0, int blk, int64_t off,
                     auto BXc) -> const bf16* {
     constexpr int BX = decltype(BXc)::value;
-    if (k0 + Cfg::BK <= xrows) return X + (int64_t)k0 * ld + off;
+    if (r0 + Cfg::BK <= xrows) return X + r0 * ld + off;
     int row, col;
     tr_slot<BX>(blk * 64 + lane, row, col, cols);
-    const int64_t r = k0 + row < xrows ? k0 + row : xrows - 1;
+    if (TA && TB && r0 + row >= xrows) return (const bf16*)&k_zero16;
+    const int64_t r = r0 + row < xrows ? r0 + row : xrows - 1;
     return X + r * ld + col;
   };
+  KSegs segs;
+  if constexpr (KF & KF_SEG) segs.init(a, (int64_t)kb * Cfg::BK);
   // FAST: a stage whose k rows all lie below arows and brows (no clamping of transposed rows)
   auto dma = [&](int kt, int d, auto FASTc) {
     constexpr bool FAST = decltype(FASTc)::value;
     const uint32_t st = ring + (kt % Cfg::NS) * Cfg::STAGE;
-    const int k0 = kt * Cfg::BK;
+    const int k0 = (kb + kt) * Cfg::BK;
     if (d < Cfg::APW) {
       int blk = wave + Cfg::NW * d;
       blk = blk < Cfg::ABLK ? blk : Cfg::ABLK - 1;
       if constexpr (TA) {
         if constexpr (FAST) lds_dma16(A + (int64_t)k0 * a.lda + aoff[d], st + blk * 1024);
-        else
+        else if constexpr (KF & KF_SEG) {
+          if (d == 0) segs.advance(a, k0);
+          lds_dma16(tr_src(A, a.lda, segs.limit(a), acols, k0 - segs.shift, blk, aoff[d],
+                           std::integral_constant<int, BM>{}),
+                    st + blk * 1024);
+        } else
           lds_dma16(tr_src(A, a.lda, arows, acols, k0, blk, aoff[d], std::integral_constant<int, BM>{}),
                     st + blk * 1024);
       } else
@@ -394,6 +459,11 @@ __global__ __launch_bounds__(128 * NWN, 1) void gemm_bf16_kernel(GemmArgs a) {
         else
           lds_dma16(tr_src(B, a.ldb, brows, bcols, k0, blk, boff[d - Cfg::APW], std::integral_constant<int, BN>{}),
                     st + Cfg::ABYTES + blk * 1024);
+      } else if constexpr (KF & KF_KPER) {
+        // stages are copied in order, so B moves on to the next matrix when k reaches it
+        if (d == Cfg::APW && (k0 == a.kper || k0 == 2 * a.kper))
+          B = (const bf16*)(k0 == a.kper ? a.Bx[1] : a.Bx[2]) + n0 * a.ldb - k0;
+        lds_dma16(B + k0 + boff[d - Cfg::APW], st + Cfg::ABYTES + blk * 1024);
       } else
         lds_dma16(B + k0 + boff[d - Cfg::APW], st + Cfg::ABYTES + blk * 1024);
     }
@@ -496,7 +566,8 @@ __global__ __launch_bounds__(128 * NWN, 1) void gemm_bf16_kernel(GemmArgs a) {
   int64_t kread = a.K;
   if constexpr (TA) kread = arows < kread ? arows : kread;
   if constexpr (TB) kread = brows < kread ? brows : kread;
-  const int kfast = (int)(kread / Cfg::BK);     // stages 0 .. kfast-1 are whole
+  int kfast = (int)(kread / Cfg::BK) - kb;      // stages 0 .. kfast-1 are whole
+  if (KF & KF_SEG) kfast = 0;                   // segments: each stage decides
   const int kc1 = kfast - (Cfg::NS - 1) < kcopy ? (kfast - (Cfg::NS - 1) > 0 ? kfast - (Cfg::NS - 1) : 0) : kcopy;
   int kt = 0;
   for (; kt < kc1; ++kt) {
@@ -665,7 +736,7 @@ struct F32Cfg {
   static_assert(NBLK % NW == 0, "every wave issues the same number of copies");
 };
 
-template <int BM, int BN, int EPI, typename CT, typename RT, bool TA, bool TB>
+template <int BM, int BN, int EPI, typename CT, typename RT, bool TA, bool TB, int KF>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a) {
   using C = F32Cfg<BM, BN>;
   __shared__ __attribute__((aligned(1024))) char smem[C::LDS];
@@ -677,7 +748,9 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a) {
   const int64_t m0 = (int64_t)(blockIdx.x % tiles_m) * BM, n0 = (int64_t)(blockIdx.x / tiles_m) * BN, z = blockIdx.z;
   const float* A = (const float*)a.A + z * a.sA + (TA ? m0 : m0 * a.lda);
   const float* B = (const float*)a.B + z * a.sB + (TB ? n0 : n0 * a.ldb);
-  const int nk = (int)(a.K / C::BK);
+  int kb, nk;                                          // first stage and number of stages
+  k_range<C::BK, EPI, CT>(a, z, kb, nk);
+  if constexpr (KF & KF_NPER) tile_of_three<TB, float, CT>(a, n0, B);
   const int64_t arows = a.a_rows > 0 ? a.a_rows : a.K, brows = a.b_rows > 0 ? a.b_rows : a.K;
   const int acols = (int)((a.a_cols > 0 ? a.a_cols : a.M) - m0), bcols = (int)((a.b_cols > 0 ? a.b_cols : a.N) - n0);
   const uint32_t ring = __builtin_amdgcn_readfirstlane(
@@ -686,12 +759,13 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a) {
   // source of this lane's 16 bytes of a copy block; rows and columns past the readable
   // extent are clamped to the last one (K-major rows past x_rows meet zeros of the other
   // operand, the rest is never stored)
-  auto src = [&](const float* X, int64_t ld, int64_t xrows, int cols, int last, int k0, int slot, auto TXc,
+  auto src = [&](const float* X, int64_t ld, int64_t xrows, int cols, int last, int64_t k0, int slot, auto TXc,
                  auto BXc) -> const float* {
     constexpr int BX = decltype(BXc)::value;
     if constexpr (decltype(TXc)::value) {
       const int row = slot / (BX / 4), lc = (slot % (BX / 4)) ^ (4 * ((row >> 2) & 1));
       const int col = 4 * lc < cols - 4 ? 4 * lc : cols - 4;
+      if (TA && TB && k0 + row >= xrows) return (const float*)&k_zero16;
       const int64_t r = k0 + row < xrows ? k0 + row : xrows - 1;
       return X + r * ld + col;
     } else {
@@ -700,14 +774,25 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a) {
     }
   };
   const int alast = (int)(a.M - 1 - m0), blast = (int)(a.N - 1 - n0);
+  KSegs segs;
+  if constexpr (KF & KF_SEG) segs.init(a, (int64_t)kb * C::BK);
   auto issue = [&](int kt) {
     const uint32_t st = ring + (kt % C::NS) * C::STAGE;
-    const int k0 = kt * C::BK;
+    const int k0 = (kb + kt) * C::BK;
+    int64_t ka = k0, alim = arows;
+    if constexpr (KF & KF_SEG) {
+      segs.advance(a, k0);
+      ka = k0 - segs.shift;
+      alim = segs.limit(a);
+    }
+    if constexpr (KF & KF_KPER) {   // stages are copied in order: on to the next matrix when k reaches it
+      if (k0 == a.kper || k0 == 2 * a.kper) B = (const float*)(k0 == a.kper ? a.Bx[1] : a.Bx[2]) + n0 * a.ldb - k0;
+    }
 #pragma unroll
     for (int i = 0; i < C::DPS; ++i) {
       const int blk = wave + C::NW * i;
       if (blk < C::ABLK)
-        lds_dma16(src(A, a.lda, arows, acols, alast, k0, blk * 64 + lane, std::integral_constant<bool, TA>{},
+        lds_dma16(src(A, a.lda, alim, acols, alast, ka, blk * 64 + lane, std::integral_constant<bool, TA>{},
                       std::integral_constant<int, BM>{}), st + blk * 1024);
       else
         lds_dma16(src(B, a.ldb, brows, bcols, blast, k0, (blk - C::ABLK) * 64 + lane, std::integral_constant<bool, TB>{},
@@ -767,10 +852,10 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a) {
 }
 
 // ------------------------------------------------------------------ dispatch
-template <int BM, int BN, int EPI, typename CT, typename RT, bool TA = false, bool TB = false, int NWN = 2>
+template <int BM, int BN, int EPI, typename CT, typename RT, bool TA = false, bool TB = false, int NWN = 2, int KF = 0>
 static hipError_t launch_bf16(const GemmArgs& a, hipStream_t s) {
   using Cfg = TileCfg<BM, BN, NWN>;
-  auto kern = gemm_bf16_kernel<BM, BN, EPI, CT, RT, TA, TB, NWN>;
+  auto kern = gemm_bf16_kernel<BM, BN, EPI, CT, RT, TA, TB, NWN, KF>;
   static bool attr_set = false;
   if (!attr_set) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -781,59 +866,88 @@ static hipError_t launch_bf16(const GemmArgs& a, hipStream_t s) {
   const int64_t ncols = a.Nstore > a.N ? a.Nstore : a.N;
   const int64_t tiles = ((a.M + BM - 1) / BM) * ((ncols + BN - 1) / BN);
   if (tiles <= 0 || a.batch <= 0) return hipSuccess;
-  if (a.K % Cfg::BK != 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(kern, dim3((unsigned)tiles, 1, (unsigned)a.batch), dim3(64 * Cfg::NW), Cfg::LDS, s, a);
+  if (a.K % Cfg::BK != 0 && !(TA && TB)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(kern, dim3((unsigned)tiles, 1, (unsigned)(a.ksplit > 1 ? a.ksplit : a.batch)), dim3(64 * Cfg::NW), Cfg::LDS, s, a);
   return hipGetLastError();
 }
 
 // waves along N of the 256 x 256 tile configuration
 static constexpr int kNWN = 4;
 
-template <int BX, int EPI, typename CT, typename RT, bool TA, bool TB>
+static int k_form(const GemmArgs& a) {
+  return (a.seg_pitch > 0 ? KF_SEG : 0) | (a.kper > 0 ? KF_KPER : 0) | (a.nper > 0 ? KF_NPER : 0);
+}
+
+template <int EPI, typename CT, typename RT, bool TA, bool TB, int KF = 0>
+static hipError_t launch_ops(int64_t big, const GemmArgs& a, hipStream_t s) {
+  return big >= 256 ? launch_bf16<256, 256, EPI, CT, RT, TA, TB, kNWN, KF>(a, s)
+                    : launch_bf16<128, 128, EPI, CT, RT, TA, TB, 2, KF>(a, s);
+}
+
+template <int BX, int EPI, typename CT, typename RT, bool TA, bool TB, int KF>
 static hipError_t launch_f32_tile(const GemmArgs& a, hipStream_t s) {
   const int64_t ncols = a.Nstore > a.N ? a.Nstore : a.N;
   const int64_t tiles = ((a.M + BX - 1) / BX) * ((ncols + BX - 1) / BX);
   if (tiles <= 0 || a.batch <= 0) return hipSuccess;
-  hipLaunchKernelGGL((gemm_f32_kernel<BX, BX, EPI, CT, RT, TA, TB>), dim3((unsigned)tiles, 1, (unsigned)a.batch),
-                     dim3(256), 0, s, a);
+  hipLaunchKernelGGL((gemm_f32_kernel<BX, BX, EPI, CT, RT, TA, TB, KF>),
+                     dim3((unsigned)tiles, 1, (unsigned)(a.ksplit > 1 ? a.ksplit : a.batch)), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
 // Square tiles of 128, 64 or 32: the largest that still gives every CU a workgroup (below
 // that the time of a stage is its latency, not its MFMAs, and smaller tiles have more of
 // them in flight).
-template <int EPI, typename CT, typename RT, bool TA, bool TB>
+template <int EPI, typename CT, typename RT, bool TA, bool TB, int KF = 0>
 static hipError_t launch_f32_ops(const GemmArgs& a, hipStream_t s) {
   const int64_t ncols = a.Nstore > a.N ? a.Nstore : a.N;
-  auto tiles = [&](int64_t b) { return ((a.M + b - 1) / b) * ((ncols + b - 1) / b) * a.batch; };
-  if (tiles(128) >= 256) return launch_f32_tile<128, EPI, CT, RT, TA, TB>(a, s);
-  if (tiles(64) >= 256) return launch_f32_tile<64, EPI, CT, RT, TA, TB>(a, s);
-  return launch_f32_tile<32, EPI, CT, RT, TA, TB>(a, s);
+  auto tiles = [&](int64_t b) { return ((a.M + b - 1) / b) * ((ncols + b - 1) / b) * a.batch * a.ksplit; };
+  if (a.nper % 128 == 0 && tiles(128) >= 256) return launch_f32_tile<128, EPI, CT, RT, TA, TB, KF>(a, s);
+  if (tiles(64) >= 256) return launch_f32_tile<64, EPI, CT, RT, TA, TB, KF>(a, s);
+  return launch_f32_tile<32, EPI, CT, RT, TA, TB, KF>(a, s);
 }
 
 template <int EPI, typename CT, typename RT>
 static hipError_t launch_f32(const GemmArgs& a, hipStream_t s) {
   // 16-byte copies along the operands' contiguous extent, 16-byte stores of 4 columns
-  if (a.K % 16 || a.lda % 4 || a.ldb % 4 || a.ldc % 4 || (a.trans_a && (a.a_cols > 0 ? a.a_cols : a.M) % 4) ||
+  if ((a.K % 16 && !(a.trans_a && a.trans_b)) || a.lda % 4 || a.ldb % 4 || a.ldc % 4 || (a.trans_a && (a.a_cols > 0 ? a.a_cols : a.M) % 4) ||
       (a.trans_b && (a.b_cols > 0 ? a.b_cols : a.N) % 4))
     return hipErrorInvalidValue;
   if (a.trans_a && a.trans_b) {
-    if constexpr (EPI == EPI_STORE) return launch_f32_ops<EPI, CT, RT, true, true>(a, s);
+    if constexpr (EPI == EPI_STORE)
+      if (!k_form(a)) return launch_f32_ops<EPI, CT, RT, true, true>(a, s);
     return hipErrorInvalidValue;
   }
   if (a.trans_a) {
+    if constexpr (EPI == EPI_STORE && std::is_same_v<CT, float>) {
+      switch (k_form(a)) {
+        case 0: break;
+        case KF_SEG: return launch_f32_ops<EPI, CT, RT, true, false, KF_SEG>(a, s);
+        case KF_KPER: return launch_f32_ops<EPI, CT, RT, true, false, KF_KPER>(a, s);
+        case KF_NPER: return launch_f32_ops<EPI, CT, RT, true, false, KF_NPER>(a, s);
+        case KF_SEG | KF_NPER: return launch_f32_ops<EPI, CT, RT, true, false, KF_SEG | KF_NPER>(a, s);
+        default: return hipErrorInvalidValue;
+      }
+    }
+    if (k_form(a)) return hipErrorInvalidValue;
     if constexpr (EPI == EPI_STORE || kAct<EPI> || EPI == EPI_XENT_T) return launch_f32_ops<EPI, CT, RT, true, false>(a, s);
     return hipErrorInvalidValue;
   }
-  if (a.trans_b) return launch_f32_ops<EPI, CT, RT, false, true>(a, s);
-  return launch_f32_ops<EPI, CT, RT, false, false>(a, s);
+  if (a.trans_b) {
+    if constexpr (EPI == EPI_STORE) {
+      if (k_form(a) == KF_NPER) return launch_f32_ops<EPI, CT, RT, false, true, KF_NPER>(a, s);
+    }
+    return k_form(a) ? hipErrorInvalidValue : launch_f32_ops<EPI, CT, RT, false, true>(a, s);
+  }
+  return k_form(a) ? hipErrorInvalidValue : launch_f32_ops<EPI, CT, RT, false, false>(a, s);
 }
 
 template <int EPI, typename CT, typename RT>
 static hipError_t launch_typed(Dt ab, const GemmArgs& a, hipStream_t s) {
   const int64_t ncols = a.Nstore > a.N ? a.Nstore : a.N;
   if (ab == F32) return launch_f32<EPI, CT, RT>(a, s);
-  const int64_t big = ((a.M + 255) / 256) * ((ncols + 255) / 256) * a.batch;
+  // 256 x 256 tiles where they give every CU one, 128 x 128 ones elsewhere (and where the
+  // columns of a tile would belong to two matrices)
+  const int64_t big = a.nper % 256 ? 0 : ((a.M + 255) / 256) * ((ncols + 255) / 256) * a.batch * a.ksplit;
   if (a.trans_a || a.trans_b) {
     // a transposed operand is read in 16-byte column chunks
     if ((a.trans_a && ((a.a_cols > 0 ? a.a_cols : a.M) % 8 || a.lda % 8)) ||
@@ -843,21 +957,63 @@ static hipError_t launch_typed(Dt ab, const GemmArgs& a, hipStream_t s) {
     // the plain store and the activation epilogues, both with the plain store
     if (a.trans_a && a.trans_b) {
       if constexpr (EPI == EPI_STORE)
-        return big >= 256 ? launch_bf16<256, 256, EPI, CT, RT, true, true, kNWN>(a, s)
-                          : launch_bf16<128, 128, EPI, CT, RT, true, true>(a, s);
+        if (!k_form(a)) return launch_ops<EPI, CT, RT, true, true>(big, a, s);
       return hipErrorInvalidValue;
     }
     if (a.trans_a) {
+      if constexpr (EPI == EPI_STORE && std::is_same_v<CT, float>) {
+        switch (k_form(a)) {
+          case 0: break;
+          case KF_SEG: return launch_ops<EPI, CT, RT, true, false, KF_SEG>(big, a, s);
+          case KF_KPER: return launch_ops<EPI, CT, RT, true, false, KF_KPER>(big, a, s);
+          case KF_NPER: return launch_ops<EPI, CT, RT, true, false, KF_NPER>(big, a, s);
+          case KF_SEG | KF_NPER: return launch_ops<EPI, CT, RT, true, false, KF_SEG | KF_NPER>(big, a, s);
+          default: return hipErrorInvalidValue;
+        }
+      }
+      if (k_form(a)) return hipErrorInvalidValue;
       if constexpr (EPI == EPI_STORE || kAct<EPI> || EPI == EPI_XENT_T)
-        return big >= 256 ? launch_bf16<256, 256, EPI, CT, RT, true, false, kNWN>(a, s)
-                          : launch_bf16<128, 128, EPI, CT, RT, true, false>(a, s);
+        return launch_ops<EPI, CT, RT, true, false>(big, a, s);
       return hipErrorInvalidValue;
     }
-    return big >= 256 ? launch_bf16<256, 256, EPI, CT, RT, false, true, kNWN>(a, s)
-                      : launch_bf16<128, 128, EPI, CT, RT, false, true>(a, s);
+    if constexpr (EPI == EPI_STORE) {
+      if (k_form(a) == KF_NPER) return launch_ops<EPI, CT, RT, false, true, KF_NPER>(big, a, s);
+    }
+    return k_form(a) ? hipErrorInvalidValue : launch_ops<EPI, CT, RT, false, true>(big, a, s);
   }
+  if (k_form(a)) return hipErrorInvalidValue;
   if (big >= 256) return launch_bf16<256, 256, EPI, CT, RT, false, false, kNWN>(a, s);
   return launch_bf16<128, 128, EPI, CT, RT>(a, s);
+}
+
+bool gemm_takes_nper(Dt ab, int64_t nper) { return nper % (ab == F32 ? 64 : 128) == 0; }
+
+// Times in microseconds, measured on weight-gradient shapes: a 32-deep stage of a full
+// round of 256 x 256 tiles (one per CU) takes 0.75, of 128 x 128 tiles 0.37 with one
+// workgroup on a CU and 0.55 with two; the slices are written and read at about 4 TB/s.
+// fp32 products are small here: slices of at least 16 stages, as many as fill the chip once.
+int gemm_ksplit(Dt ab, int64_t M, int64_t N, int64_t K, int cap) {
+  int best = 1;
+  if (ab == F32) {
+    const int64_t t = ((M + 31) / 32) * ((N + 31) / 32);
+    while (best * 2 <= cap && t * best * 2 <= 256 && K / (16 * best * 2) >= 16) best *= 2;
+    return best;
+  }
+  double tbest = 0;
+  for (int z = 1; z <= cap; ++z) {
+    const double stages = (double)((K + 31) / 32 + z - 1) / z;
+    if (z > 1 && stages < 8) break;
+    const double n256 = (double)(((M + 255) / 256) * ((N + 255) / 256)) * z;
+    const double n128 = (double)(((M + 127) / 128) * ((N + 127) / 128)) * z;
+    double t = n256 >= 256 ? std::ceil(n256 / 256) * (stages * 0.75 + 6)
+                           : n128 <= 256 ? stages * 0.37 + 4 : std::ceil(n128 / 512) * (stages * 0.55 + 6);
+    if (z > 1) t += 3.0 + (2.0 * z + 1) * 4.0 * M * N / 4.0e6;
+    if (z == 1 || t < tbest) {
+      tbest = t;
+      best = z;
+    }
+  }
+  return best;
 }
 
 hipError_t gemm(Dt ab, Epi epi, Dt ct, Dt rt, const GemmArgs& a, hipStream_t s) {

@@ -53,9 +53,31 @@ struct GemmArgs {
   // x_rows up to K are not read, and the other operand must be zero at those k), and
   // x_cols the number of columns that may be read from the pointer (>= M or N; a
   // multiple of 8). 0 means K and M (or N).
+  // With both operands K-major, K may be any length: rows past it are read as zeros.
   int trans_a = 0, trans_b = 0;
   int64_t a_rows = 0, b_rows = 0, a_cols = 0, b_cols = 0;
+  // A K-major (and B not): k counts rows in segments of seg_pitch of which the first seg_rows
+  // exist, stored one after the other (sequences padded in B but not in A); rows past a
+  // segment's end are not read, and B must be zero there. seg_pitch % 64 == 0; 0: none.
+  int64_t seg_rows = 0, seg_pitch = 0;
+  // ksplit > 1 (EPI_STORE, batch 1): grid z is a slice of K, a run of whole k stages, whose
+  // partial product goes to C + z * sC
+  int ksplit = 1;
+  // nper > 0: columns [w nper, (w + 1) nper), w = 0, 1, 2, take B from Bx[w] (B K-major) and go
+  // to Cx[w] where those are given; alpha applies to w = 0 only. A column tile lies in one w
+  // (gemm_takes_nper).
+  int64_t nper = 0;
+  // kper > 0 (A K-major, B not): B's columns k in [w kper, (w + 1) kper) come from Bx[w]
+  int64_t kper = 0;
+  const void* Bx[3] = {nullptr, nullptr, nullptr};
+  void* Cx[3] = {nullptr, nullptr, nullptr};
 };
+
+// Whether a GEMM of M x 3 nper may be given as one with nper > 0
+bool gemm_takes_nper(Dt ab, int64_t nper);
+// Slices of K (at most cap) for an M x N product stored in fp32 whose tiles alone would leave
+// CUs idle: the least estimated time of the tiles, the slices' stages and their addition.
+int gemm_ksplit(Dt ab, int64_t M, int64_t N, int64_t K, int cap);
 
 // ab: element type of A and B. ct: type of C; rt: type of R.
 hipError_t gemm(Dt ab, Epi epi, Dt ct, Dt rt, const GemmArgs& a, hipStream_t s);
@@ -99,22 +121,14 @@ hipError_t layer_norm(Dt ti, Dt to, const void* x, int64_t ldx, const float* g, 
 // the same values. Unless both are null, dgamma[d] = sum_r dout[r,d] * xhat[r,d] and
 // dbeta[d] = sum_r dout[r,d] (overwrite; either may be null), through `partial`, workspace of
 // at least layer_norm_param_grad_ws(D) floats (more are used if there). dout is fp32, or bf16
-// where layer_norm_bwd_fused(D).
+// where layer_norm_bwd_fused(D). With seg > 0, dout has a row pitch of `pitch` rows per seg
+// rows: row r is stored at r + r / seg * (pitch - seg).
 size_t layer_norm_param_grad_ws(int64_t D);
 bool layer_norm_bwd_fused(int64_t D);
 hipError_t layer_norm_bwd(Dt ti, const void* x, const float* mu, const float* rstd, const float* g, Dt td,
                           const void* dout, Dt tr, const void* resid, Dt to, void* out, Dt t2, void* out2,
                           float* dgamma, float* dbeta, float* partial, int64_t partial_floats, int64_t rows, int64_t D,
-                          hipStream_t s);
-
-// out[c, r] = in[r, c] for r < rows, 0 for rows <= r < rows_store; batched over z.
-hipError_t transpose(Dt t, const void* in, int64_t ld_in, int64_t s_in, void* out, int64_t ld_out,
-                     int64_t s_out, int64_t rows, int64_t cols, int64_t rows_store, int batch,
-                     hipStream_t s);
-
-// out[r, c] = in[r, c]
-hipError_t copy2d(Dt t, const void* in, int64_t ld_in, void* out, int64_t ld_out, int64_t rows,
-                  int64_t cols, hipStream_t s);
+                          int64_t seg, int64_t pitch, hipStream_t s);
 
 // out[c] (+)= sum_r in[r, c]  (in: [rows, cols] of type t)
 hipError_t col_sum(Dt t, const void* in, int64_t ld, int64_t rows, int64_t cols, float* out,
@@ -150,8 +164,10 @@ hipError_t bf16_to_f32(const void* in, float* out, int64_t n, hipStream_t s);
 hipError_t adamw(Dt tl, float* p, const float* g, float* m, float* v, void* pl, int64_t n, float lr, float b1,
                  float b2, float eps, float wd, float c1, float c2, hipStream_t s);
 
-// out[i] (+)= sum over z < nz of part[z n + i], added in slice order (n % 4 == 0)
-hipError_t sum_slices(const float* part, int nz, int64_t n, float* out, int accumulate, hipStream_t s);
+// out[m, c] (+)= sum over z < nz of part[z, m, c], rows x cols each, added in slice order; with
+// nper > 0 column c goes to outs[c / nper][m, c % nper], else all to outs[0] (cols, nper % 4 == 0)
+hipError_t sum_slices(const float* part, int nz, int64_t rows, int64_t cols, float* const outs[3], int64_t nper,
+                      int accumulate, hipStream_t s);
 // ---------------------------------------------------------------- residual-branch dropout
 // Element (t, n) of branch `site` is kept iff word n % 4 of Philox4x32-10 at counter
 // (n / 4, t, site, 0), key (k0, k1), is >= threshold; kept values are multiplied by scale.

@@ -159,39 +159,22 @@ FwdWs fwd_ws(const Dims& d, void* base, int64_t* total) {
 }
 
 struct BwdWs {
-  void *wcat;
   void *vg, *gT, *dzT;
   void* gpT;             // GELU'(Z^T): fp32 on the fp32 path, fp16 on the bf16 path
   float *dv, *dh, *dU, *ndelta, *nlse2, *partial;
-  void *dhe, *dhT, *dO, *dqkvT, *u;
+  void *dhe, *dO, *dqkvT, *u;
   float* kpart;          // K-slice partials of the D x D weight gradients (null: no split)
   float* fpart;          // K-slice partials of dW1 / dW2 (null: no split)
+  int zo, z1, z3, zf;    // slices of dWo; of one of dWq, dWk, dWv; of the three as one; of dW1, dW2
   void* dYm;             // dY through the FFN branch's dropout (null: no dropout)
 };
 
-// Slices of K for an M x N weight-gradient GEMM (fp32 C, plain store) over K tokens whose
-// 256 x 256 tile grid would leave most of the 256 CUs idle (a narrow layer: D < 4096, or
-// D x F < 256 tiles): the slices run as batch entries into fp32 partials that sum_slices
-// adds into C in a fixed order. Every slice is a multiple of 64 tokens.
+// Most slices of K of a weight-gradient GEMM (gemm_ksplit chooses): they bound the workspace
 constexpr int kMaxKSplit = 16;
-int ksplit_cap(int64_t M, int64_t N) {   // the most slices the tile grid allows
-  const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256);
-  int z = 1;
-  while (z < kMaxKSplit && tiles * 2 * z <= 256) z *= 2;
-  return z;
-}
-int ksplit(int64_t M, int64_t N, int64_t K) {
-  if (K % 64 != 0) return 1;
-  const int cap = ksplit_cap(M, N);
-  int z = 1;
-  while (z < cap && K % (64 * 2 * z) == 0) z *= 2;
-  return z;
-}
 
 BwdWs bwd_ws(const Dims& d, void* base, int64_t* total) {
   Bump bp(base);
   BwdWs w;
-  w.wcat = bp.take(3 * d.D * d.D * d.E);
   w.vg = bp.take(d.R * d.D * d.E);
   w.gT = bp.take(d.F * d.Rp * d.E);
   w.gpT = bp.take(d.F * d.Rp * (d.E == 2 ? 2 : 4));   // fp16 on the bf16 path, else fp32
@@ -199,18 +182,22 @@ BwdWs bwd_ws(const Dims& d, void* base, int64_t* total) {
   w.dv = (float*)bp.take(d.T * d.D * 4);
   w.dh = (float*)bp.take(d.T * d.D * 4);
   w.dhe = bp.take(d.T * d.D * d.E);
-  w.dhT = bp.take(d.D * d.Tp * d.E);
   w.dO = bp.take(d.T * d.D * d.E);
   w.ndelta = (float*)bp.take(d.B * d.H * d.Sp * 4);
   w.nlse2 = (float*)bp.take(d.B * d.H * d.Sp * 4);
   w.dqkvT = bp.take(3 * d.D * d.Tp * d.E);
   w.u = bp.take(d.T * d.D * d.E);
-  w.dU = (float*)bp.take(d.T * d.D * 4);
+  w.dU = (float*)bp.take(d.Tp * d.D * 4);   // rows of a sequence at a pitch of Sp
   w.partial = (float*)bp.take((int64_t)layer_norm_param_grad_ws(std::max(d.D, d.F)) * 4);
-  const int kz = d.S % 64 == 0 ? ksplit(d.D, d.D, d.T) : 1;   // the whole-batch GEMMs below
-  w.kpart = kz > 1 ? (float*)bp.take(kz * d.D * d.D * 4) : nullptr;
-  const int fz = ksplit_cap(d.D, d.F);                      // dW1 and dW2 per FFN group
-  w.fpart = fz > 1 ? (float*)bp.take(fz * d.D * d.F * 4) : nullptr;
+  // K slices: dWo, and dWq, dWk, dWv as one product or (nz, single) one at a time; dW1, dW2
+  const Dt E = d.E == 2 ? BF16 : F32;
+  w.zo = gemm_ksplit(E, d.D, d.D, d.T, kMaxKSplit);
+  w.z1 = gemm_ksplit(E, d.D, d.D, d.Tp, kMaxKSplit);
+  w.z3 = gemm_takes_nper(E, d.D) ? gemm_ksplit(E, d.D, 3 * d.D, d.Tp, kMaxKSplit) : 1;
+  const int64_t kn = std::max({w.zo > 1 ? w.zo : 0, w.z1 > 1 ? w.z1 : 0, w.z3 > 1 ? 3 * w.z3 : 0});
+  w.kpart = kn > 0 ? (float*)bp.take(kn * d.D * d.D * 4) : nullptr;
+  w.zf = gemm_ksplit(E, d.F, d.D, d.Rp, kMaxKSplit);
+  w.fpart = w.zf > 1 ? (float*)bp.take(w.zf * d.D * d.F * 4) : nullptr;
   w.dYm = d.drop ? bp.take(d.T * d.D * d.E) : nullptr;
   *total = rup(bp.off, kAlign);
   return w;
@@ -560,12 +547,17 @@ bpt_status bpt_layer_fwd(const bpt_config* cfg, const void* X, const bpt_params*
       layer_norm(E, E, X, D, p->ln1_g, p->ln1_b, w.u, D, sv.mu1, sv.rstd1, T, D, cfg->ln_eps, 0, s));
   // the weights [D_in, D_out] are read as they are: B operands stored K-major
   const void* wqkv[3] = {p->Wq, p->Wk, p->Wv};
-  for (int i = 0; i < 3; ++i) {
+  const bool one = gemm_takes_nper(E, D);              // all three in one launch
+  for (int i = 0; i < (one ? 1 : 3); ++i) {
     GemmArgs g;
     g.A = w.u; g.lda = D; g.B = wqkv[i]; g.ldb = D; g.trans_b = 1;
     // bf16 attention takes Q multiplied by log2(e)/sqrt(dh): scores in base-2 units
     if (i == 0 && E == BF16) g.alpha = (float)(1.4426950408889634 / std::sqrt((double)d.dh));
     g.C = off(sv.qkv, i * D * E_); g.ldc = 3 * D; g.M = T; g.N = D; g.K = D;
+    if (one) {
+      g.N = 3 * D; g.nper = D;
+      for (int k = 0; k < 3; ++k) g.Bx[k] = wqkv[k];
+    }
     RUN("gemm.qkv", gemm_flops(g), gemm_bytes(g, E_, E_), gemm(E, EPI_STORE, E, F32, g, s));
   }
 
@@ -657,15 +649,10 @@ bpt_status bpt_layer_bwd(const bpt_config* cfg, const void* X, const bpt_params*
   const int64_t D = d.D, F = d.F, T = d.T, Tp = d.Tp, Sp = d.Sp, S = d.S, E_ = (int64_t)d.E;
   const size_t EO = esize(cfg->out_dtype);
   const int B = (int)d.B;
-  const double tb = 2.0 * E_;   // bytes per element of a transpose / copy (read + write)
   // GELU'(Z) between the FFN recompute and dZ: fp16 on the bf16 path (its rounding,
   // 2^-11 relative, is far below the bf16 rounding of the dZ operand that follows)
   const Dt GP = E == BF16 ? F16 : F32;
   const int64_t GP_ = GP == F16 ? 2 : 4;
-
-  RUN("copy.weights", 0, tb * D * D, copy2d(E, p->Wq, D, w.wcat, 3 * D, D, D, s));
-  RUN("copy.weights", 0, tb * D * D, copy2d(E, p->Wk, D, off(w.wcat, D * E_), 3 * D, D, D, s));
-  RUN("copy.weights", 0, tb * D * D, copy2d(E, p->Wv, D, off(w.wcat, 2 * D * E_), 3 * D, D, D, s));
 
   // ---- FFN and LN2 backward, per group of query blocks, recomputing the FFN intermediate
   bool first = true;
@@ -697,20 +684,25 @@ bpt_status bpt_layer_bwd(const bpt_config* cfg, const void* X, const bpt_params*
         RUN("gemm.bwd_dz", gemm_flops(g), gemm_bytes(g, E_, E_ + GP_), gemm(E, EPI_MUL, E, GP, g, s));
       }
       if (G.db1) RUN("reduce.bias", 0, (double)F * r * E_, row_sum(E, w.dzT, d.Rp, F, r, G.db1, first ? 0 : 1, s));
-      // K slices of the FFN weight gradients for a group of whole 64-row blocks (every slice
-      // inside the group's rows, so no clamped rows)
-      const int fz = w.fpart && r % 64 == 0 ? ksplit(D, F, r) : 1;
+      // K slices of the FFN weight gradients (a shorter last group takes no more than fit)
+      const int fz = w.fpart ? std::min(w.zf, gemm_ksplit(E, F, D, rp, kMaxKSplit)) : 1;
+      auto fgrad = [&](const char* name, GemmArgs g, float* out) -> bpt_status {
+        g.accumulate = first ? 0 : 1;
+        g.C = out;
+        if (fz > 1) {
+          g.ksplit = fz; g.C = w.fpart; g.sC = F * D; g.accumulate = 0;
+        }
+        RUN(name, gemm_flops(g), gemm_bytes(g, E_, 4), gemm(E, EPI_STORE, F32, F32, g, s));
+        float* outs[3] = {out, nullptr, nullptr};
+        if (fz > 1)
+          RUN("reduce.ksplit", 0, (double)(fz + 1) * F * D * 4, sum_slices(w.fpart, fz, g.M, g.N, outs, 0, first ? 0 : 1, s));
+        return BPT_OK;
+      };
       if (G.dW2) {   // dW2 = G^T dY, dY read token-major (G^T is zero past the group's rows)
         GemmArgs g;
         g.A = w.gT; g.lda = d.Rp; g.B = dYg; g.ldb = D; g.trans_b = 1; g.b_rows = r;
-        g.C = G.dW2; g.ldc = D; g.M = F; g.N = D; g.K = rp; g.accumulate = first ? 0 : 1;
-        if (fz > 1) {
-          g.b_rows = 0; g.batch = fz; g.K = r / fz; g.sA = g.K; g.sB = g.K * D;
-          g.C = w.fpart; g.sC = F * D; g.accumulate = 0;
-        }
-        RUN("gemm.bwd_dw2", gemm_flops(g), gemm_bytes(g, E_, 4), gemm(E, EPI_STORE, F32, F32, g, s));
-        if (fz > 1)
-          RUN("reduce.ksplit", 0, (double)(fz + 1) * F * D * 4, sum_slices(w.fpart, fz, F * D, G.dW2, first ? 0 : 1, s));
+        g.ldc = D; g.M = F; g.N = D; g.K = rp;
+        if ((st = fgrad("gemm.bwd_dw2", g, G.dW2)) != BPT_OK) return st;
       }
       {   // dv = dZ W1^T, dZ read from its feature-major copy
         GemmArgs g;
@@ -722,15 +714,9 @@ bpt_status bpt_layer_bwd(const bpt_config* cfg, const void* X, const bpt_params*
       if (G.dW1) {   // dW1 = v^T dZ, v read token-major (dZ^T is zero past the group's rows)
         GemmArgs g;
         g.A = w.vg; g.lda = D; g.trans_a = 1; g.a_rows = r;
-        g.B = w.dzT; g.ldb = d.Rp; g.C = G.dW1; g.ldc = F;
-        g.M = D; g.N = F; g.K = rp; g.accumulate = first ? 0 : 1;
-        if (fz > 1) {
-          g.a_rows = 0; g.batch = fz; g.K = r / fz; g.sA = g.K * D; g.sB = g.K;
-          g.C = w.fpart; g.sC = D * F; g.accumulate = 0;
-        }
-        RUN("gemm.bwd_dw1", gemm_flops(g), gemm_bytes(g, E_, 4), gemm(E, EPI_STORE, F32, F32, g, s));
-        if (fz > 1)
-          RUN("reduce.ksplit", 0, (double)(fz + 1) * D * F * 4, sum_slices(w.fpart, fz, D * F, G.dW1, first ? 0 : 1, s));
+        g.B = w.dzT; g.ldb = d.Rp; g.ldc = F;
+        g.M = D; g.N = F; g.K = rp;
+        if ((st = fgrad("gemm.bwd_dw1", g, G.dW1)) != BPT_OK) return st;
       }
       first = false;
     }
@@ -743,7 +729,7 @@ bpt_status bpt_layer_bwd(const bpt_config* cfg, const void* X, const bpt_params*
   // dh = dY + LN2^T(dv)
   RUN("layernorm.bwd", 0, (double)T * D * (4 + 4 + E_ + 4 + E_),
       layer_norm_bwd(F32, sv.h, sv.mu2, sv.rstd2, p->ln2_g, F32, w.dv, E, dY, F32, w.dh, E, w.dhe, G.dln2_g, G.dln2_b,
-                     ln_part, ln_part_n, T, D, s));
+                     ln_part, ln_part_n, T, D, 0, 0, s));
   if (G.db2) RUN("reduce.bias", 0, (double)T * D * E_, col_sum(E, dYf, D, T, D, G.db2, 0, w.partial, s));
   if (d.drop)   // the output projection sees dh through its dropout
     RUN("dropout.bwd", 0, (double)T * D * (4 + E_), dropout_scale(F32, w.dh, E, w.dhe, T, D, drop_args(*cfg, 0, 0), s));
@@ -754,41 +740,23 @@ bpt_status bpt_layer_bwd(const bpt_config* cfg, const void* X, const bpt_params*
     g.A = w.dhe; g.lda = D; g.B = p->Wo; g.ldb = D; g.C = w.dO; g.ldc = D; g.M = T; g.N = D; g.K = D;
     RUN("gemm.bwd_do", gemm_flops(g), gemm_bytes(g, E_, E_), gemm(E, EPI_STORE, E, F32, g, s));
   }
-  // With S % 64 == 0 every sequence is whole 64-token rows (Sp == S): O, dh and u are
-  // token-major and the feature-major dQ^T, dK^T, dV^T unpadded over the whole batch, so
-  // each D x D weight gradient is one GEMM with K = T (split along K when D < 4096).
-  const bool whole = S % 64 == 0;
-  const int kz = whole && w.kpart ? ksplit(D, D, T) : 1;
-  auto wgrad = [&](const char* name, GemmArgs g, float* out, int64_t sa, int64_t sb) -> bpt_status {
-    if (kz > 1) {   // K slices of T / kz tokens; A and B step by sa and sb elements per slice
-      g.batch = kz; g.K = T / kz; g.sA = sa * g.K; g.sB = sb * g.K; g.C = w.kpart; g.sC = D * D;
+  // Each D x D weight gradient is one GEMM over the whole batch, K = its tokens, cut along K
+  // where its tiles would leave CUs idle; slices go to `kpart` and are added in order.
+  auto wgrad = [&](const char* name, GemmArgs g, int z, float* const outs[3]) -> bpt_status {
+    if (z > 1) {
+      g.ksplit = z; g.C = w.kpart; g.ldc = g.N; g.sC = g.M * g.N;
+      g.Cx[0] = nullptr;
     }
     RUN(name, gemm_flops(g), gemm_bytes(g, E_, 4), gemm(E, EPI_STORE, F32, F32, g, s));
-    if (kz > 1) RUN("reduce.ksplit", 0, (double)(kz + 1) * D * D * 4, sum_slices(w.kpart, kz, D * D, out, 0, s));
+    if (z > 1) RUN("reduce.ksplit", 0, (double)(z + 1) * g.M * g.N * 4, sum_slices(w.kpart, z, g.M, g.N, outs, g.nper, 0, s));
     return BPT_OK;
   };
-  if (G.dWo && whole) {
+  if (G.dWo) {   // O and dh are token-major and unpadded: both K-major, K = T
     GemmArgs g;
     g.A = sv.o; g.lda = D; g.trans_a = 1; g.B = w.dhe; g.ldb = D; g.trans_b = 1; g.C = G.dWo; g.ldc = D;
     g.M = D; g.N = D; g.K = T;
-    if ((st = wgrad("gemm.bwd_dwo", g, G.dWo, D, D)) != BPT_OK) return st;
-  } else if (G.dWo && S % 32 == 0) {   // per sequence: O and dh both read token-major (K = S exactly)
-    for (int b = 0; b < B; ++b) {
-      GemmArgs g;
-      g.A = off(sv.o, b * S * D * E_); g.lda = D; g.trans_a = 1;
-      g.B = off(w.dhe, b * S * D * E_); g.ldb = D; g.trans_b = 1; g.C = G.dWo; g.ldc = D;
-      g.M = D; g.N = D; g.K = S; g.accumulate = b > 0;
-      RUN("gemm.bwd_dwo", gemm_flops(g), gemm_bytes(g, E_, 4), gemm(E, EPI_STORE, F32, F32, g, s));
-    }
-  } else if (G.dWo) {   // O read token-major, dh from its zero-padded feature-major copy
-    RUN("transpose.act", 0, tb * T * D, transpose(E, w.dhe, D, S * D, w.dhT, Tp, Sp, S, D, Sp, B, s));
-    for (int b = 0; b < B; ++b) {
-      GemmArgs g;
-      g.A = off(sv.o, b * S * D * E_); g.lda = D; g.trans_a = 1; g.a_rows = S;
-      g.B = off(w.dhT, b * Sp * E_); g.ldb = Tp; g.C = G.dWo; g.ldc = D;
-      g.M = D; g.N = D; g.K = Sp; g.accumulate = b > 0;
-      RUN("gemm.bwd_dwo", gemm_flops(g), gemm_bytes(g, E_, 4), gemm(E, EPI_STORE, F32, F32, g, s));
-    }
+    float* outs[3] = {G.dWo, nullptr, nullptr};
+    if ((st = wgrad("gemm.bwd_dwo", g, w.zo, outs)) != BPT_OK) return st;
   }
 
   // ---- attention backward, probabilities rebuilt from the saved log-sum-exp
@@ -813,38 +781,39 @@ bpt_status bpt_layer_bwd(const bpt_config* cfg, const void* X, const bpt_params*
   if (G.dWq || G.dWk || G.dWv) {
     RUN("layernorm.fwd", 0, 2.0 * T * D * E_,
         layer_norm(E, E, X, D, p->ln1_g, p->ln1_b, w.u, D, sv.mu1, sv.rstd1, T, D, cfg->ln_eps, 1, s));
-    // per sequence: u read token-major; dQ^T, dK^T, dV^T are zero past the sequence end
+    // u read token-major; dQ^T, dK^T, dV^T have their sequences at a pitch of Sp columns, zero
+    // past each one's end. The three are rows of one matrix, so one GEMM if all are wanted.
     float* outs[3] = {G.dWq, G.dWk, G.dWv};
-    for (int i = 0; i < 3; ++i) {
+    const bool one = G.dWq && G.dWk && G.dWv && gemm_takes_nper(E, D);
+    for (int i = 0; i < (one ? 1 : 3); ++i) {
       if (!outs[i]) continue;
-      if (whole) {   // u rows and dQ^T / dK^T / dV^T columns contiguous over the batch
-        GemmArgs g;
-        g.A = w.u; g.lda = D; g.trans_a = 1;
-        g.B = off(w.dqkvT, i * D * Tp * E_); g.ldb = Tp; g.C = outs[i]; g.ldc = D;
-        g.M = D; g.N = D; g.K = T;
-        if ((st = wgrad("gemm.bwd_dwqkv", g, outs[i], D, 1)) != BPT_OK) return st;
-        continue;
+      GemmArgs g;
+      g.A = w.u; g.lda = D; g.trans_a = 1;
+      g.B = off(w.dqkvT, i * D * Tp * E_); g.ldb = Tp; g.C = outs[i]; g.ldc = D;
+      g.M = D; g.N = D; g.K = Tp;
+      if (Sp != S) {
+        g.seg_rows = S; g.seg_pitch = Sp;
       }
-      for (int b = 0; b < B; ++b) {
-        GemmArgs g;
-        g.A = off(w.u, b * S * D * E_); g.lda = D; g.trans_a = 1; g.a_rows = S;
-        g.B = off(w.dqkvT, (i * D * Tp + b * Sp) * E_); g.ldb = Tp; g.C = outs[i]; g.ldc = D;
-        g.M = D; g.N = D; g.K = Sp; g.accumulate = b > 0;
-        RUN("gemm.bwd_dwqkv", gemm_flops(g), gemm_bytes(g, E_, 4), gemm(E, EPI_STORE, F32, F32, g, s));
+      if (one) {
+        g.N = 3 * D; g.nper = D;
+        for (int k = 0; k < 3; ++k) g.Cx[k] = outs[k];
       }
+      float* o1[3] = {outs[i], nullptr, nullptr};
+      if ((st = wgrad("gemm.bwd_dwqkv", g, one ? w.z3 : w.z1, one ? outs : o1)) != BPT_OK) return st;
     }
   }
-  // dU = [dQ dK dV] [Wq Wk Wv]^T, [dQ dK dV] read feature-major: one GEMM over the batch
-  // when its columns are contiguous (S % 64 == 0), else one per sequence
-  for (int b = 0; b < (whole ? 1 : B); ++b) {
+  // dU = [dQ dK dV] [Wq Wk Wv]^T over the whole batch: [dQ dK dV] read feature-major, its rows
+  // at the padded pitch (padding rows are never read), K running through the three weights
+  {
     GemmArgs g;
-    g.A = off(w.dqkvT, b * Sp * E_); g.lda = Tp; g.trans_a = 1; g.a_cols = Tp - b * Sp;
-    g.B = w.wcat; g.ldb = 3 * D; g.C = w.dU + b * S * D; g.ldc = D; g.M = whole ? T : S; g.N = D; g.K = 3 * D;
+    g.A = w.dqkvT; g.lda = Tp; g.trans_a = 1;
+    g.B = p->Wq; g.ldb = D; g.kper = D; g.Bx[0] = p->Wq; g.Bx[1] = p->Wk; g.Bx[2] = p->Wv;
+    g.C = w.dU; g.ldc = D; g.M = Tp; g.N = D; g.K = 3 * D;
     RUN("gemm.bwd_du", gemm_flops(g), gemm_bytes(g, E_, 4), gemm(E, EPI_STORE, F32, F32, g, s));
   }
   RUN("layernorm.bwd", 0, (double)T * D * (E_ + 4 + 4 + EO),
       layer_norm_bwd(E, X, sv.mu1, sv.rstd1, p->ln1_g, F32, w.dU, F32, w.dh, OUT, dX, OUT, nullptr, G.dln1_g, G.dln1_b,
-                     ln_part, ln_part_n, T, D, s));
+                     ln_part, ln_part_n, T, D, S, Sp, s));
   return BPT_OK;
 }
 
@@ -1065,7 +1034,7 @@ bpt_status bpt_ln_bwd(const bpt_ln_config* cfg, const void* X, const float* g, c
     partial_n = dy_off / 4;
   }
   RUN("gpt.ln_f_bwd", 0, (double)R * D * (2 * I_ + (TD == BF16 ? 2 : 4)) + (double)R * 8,
-      layer_norm_bwd(TI, X, mean, rstd, g, TD, dY, F32, nullptr, TI, dX, TI, nullptr, dg, db, partial, partial_n, R, D, s));
+      layer_norm_bwd(TI, X, mean, rstd, g, TD, dY, F32, nullptr, TI, dX, TI, nullptr, dg, db, partial, partial_n, R, D, 0, 0, s));
   return BPT_OK;
 }
 

@@ -1,7 +1,6 @@
 // Row-wise and layout kernels of the BPT layer: LayerNorm forward / backward and
 // its parameter gradients, bias gradients (row / column sums), the softmax
-// backward's per-row Delta = rowsum(dO * O), transposes into the feature-major
-// layouts the MFMA kernels read, and a strided copy. All are HBM-bound; each
+// backward's per-row Delta = rowsum(dO * O), and the sum of K slices. All are HBM-bound; each
 // reads and writes every element once (LayerNorm re-reads its row from cache).
 #include <algorithm>
 
@@ -171,6 +170,14 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const TI* x, int64_t ldx, c
 }
 
 // ------------------------------------------------------------------ LayerNorm backward
+// Storage row of dout's row r (seg > 0: a pitch of `pitch` rows per seg rows)
+struct RowMap {
+  int64_t seg = 0, gap = 0;                          // gap = pitch - seg
+  BPT_DEV int64_t at(int64_t r) const {
+    if (gap == 0) return r;
+    return r + (r >> 31 ? r / seg : (int64_t)((uint32_t)r / (uint32_t)seg)) * gap;
+  }
+};
 // dz = rstd * (gd - mean(gd) - xhat * mean(gd * xhat)), gd = dout * gamma; out = resid + dz.
 // Rows of D <= 512 NC WPR (D % 8 == 0): WPR waves per row hold the row of x and of dout in
 // registers, wave w its chunks NC w .. NC w + NC - 1 of 512 columns.
@@ -184,7 +191,8 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const TI* x, int64_t ldx, c
 template <typename TI, typename TD, typename TR, typename TO, typename T2, int NC, int WPR, bool PARAM>
 __global__ __launch_bounds__(256) void ln_bwd_reg_kernel(const TI* x, const float* mu, const float* rstd,
                                                          const float* g, const TD* dout, const TR* resid,
-                                                         TO* out, T2* out2, float* partial, int64_t rows, int D) {
+                                                         TO* out, T2* out2, float* partial, int64_t rows, int D,
+                                                         RowMap map) {
   static_assert(WPR == 1 || WPR == 4, "waves per row");
   static_assert(WPR == 4 || !PARAM || NC <= 4, "LDS of the block sums");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -202,13 +210,14 @@ __global__ __launch_bounds__(256) void ln_bwd_reg_kernel(const TI* x, const floa
   int par = 0;
   for (int64_t row = WPR == 4 ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * 4 + wave; row < rows; row += step) {
     const float m = mu[row], rs = rstd[row];
+    const int64_t drow = map.at(row);
     float xh[NC][8], gd[NC][8];
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       const int d = col0 + 512 * c;
       if (d < D) {
         Vec8<TI>::load(x + row * D + d, xh[c]);
-        Vec8<TD>::load(dout + row * D + d, gd[c]);
+        Vec8<TD>::load(dout + drow * D + d, gd[c]);
       }
     }
     float s1 = 0.0f, s2 = 0.0f;
@@ -296,12 +305,12 @@ __global__ __launch_bounds__(256) void ln_bwd_reg_kernel(const TI* x, const floa
 template <typename TI, typename TR, typename TO, typename T2>
 __global__ __launch_bounds__(256) void ln_bwd_kernel(const TI* x, const float* mu, const float* rstd,
                                                      const float* g, const float* dout, const TR* resid,
-                                                     TO* out, T2* out2, int64_t rows, int64_t D) {
+                                                     TO* out, T2* out2, int64_t rows, int64_t D, RowMap map) {
   const int lane = threadIdx.x & 63;
   const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= rows) return;
   const TI* xr = x + row * D;
-  const float* dr = dout + row * D;
+  const float* dr = dout + map.at(row) * D;
   const float m = mu[row], rs = rstd[row];
   float s1 = 0.0f, s2 = 0.0f;
   for (int64_t d = 4 * lane; d < D; d += 256) {
@@ -335,24 +344,6 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const TI* x, const float* m
 
 // ------------------------------------------------------------------ column / row sums
 static constexpr int kChunks = 128;
-
-template <typename TI>
-__global__ __launch_bounds__(256) void ln_param_partial_kernel(const TI* x, const float* mu,
-                                                               const float* rstd, const float* dout,
-                                                               float* partial, int64_t rows, int64_t D) {
-  const int64_t d = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (d >= D) return;
-  const int64_t per = (rows + kChunks - 1) / kChunks;
-  const int64_t r0 = blockIdx.y * per, r1 = r0 + per < rows ? r0 + per : rows;
-  float sg = 0.0f, sb = 0.0f;
-  for (int64_t r = r0; r < r1; ++r) {
-    const float dv = dout[r * D + d];
-    sg = fmaf(dv, (to_f32<TI>(x[r * D + d]) - mu[r]) * rstd[r], sg);
-    sb += dv;
-  }
-  partial[(int64_t)blockIdx.y * D + d] = sg;
-  partial[(int64_t)(kChunks + blockIdx.y) * D + d] = sb;
-}
 
 // Second stage: out0[d] (+)= sum_c partial[c D + d] and out1[d] (+)= sum_c partial[(nch + c) D + d],
 // c < nch. A block per 16 columns: 16 lanes of 64 bytes, 16 groups of chunks; group k sums
@@ -437,7 +428,7 @@ __global__ __launch_bounds__(64) void col_partial8_kernel(const T* in, int64_t l
 template <typename TI>
 __global__ __launch_bounds__(256) void ln_param_partial8_kernel(const TI* x, const float* mu, const float* rstd,
                                                                 const float* dout, float* partial, int64_t rows,
-                                                                int64_t D) {
+                                                                int64_t D, RowMap map) {
   __shared__ float red[2][4][64 * 8];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int64_t d = ((int64_t)blockIdx.x * 64 + lane) * 8;
@@ -454,7 +445,7 @@ __global__ __launch_bounds__(256) void ln_param_partial8_kernel(const TI* x, con
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         Vec8<TI>::load(x + (r + u) * D + d, xv[u]);
-        Vec8<float>::load(dout + (r + u) * D + d, dv[u]);
+        Vec8<float>::load(dout + map.at(r + u) * D + d, dv[u]);
       }
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
@@ -469,7 +460,7 @@ __global__ __launch_bounds__(256) void ln_param_partial8_kernel(const TI* x, con
     for (; r < r1; ++r) {
       float xv[8], dv[8];
       Vec8<TI>::load(x + r * D + d, xv);
-      Vec8<float>::load(dout + r * D + d, dv);
+      Vec8<float>::load(dout + map.at(r) * D + d, dv);
       const float m = mu[r], rs = rstd[r];
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
@@ -580,46 +571,6 @@ __global__ __launch_bounds__(256) void delta_kernel(const T* dO, const T* O, int
       nlse2[i] = s < S ? -lse[i] * 1.4426950408889634f : 0.0f;
     }
   }
-}
-
-// ------------------------------------------------------------------ transpose / copy
-template <typename T>
-__global__ __launch_bounds__(256) void transpose_kernel(const T* in, int64_t ld_in, int64_t s_in, T* out,
-                                                        int64_t ld_out, int64_t s_out, int64_t rows,
-                                                        int64_t cols, int64_t rows_store) {
-  __shared__ T tile[64][65];
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  const int64_t r0 = (int64_t)blockIdx.x * 64, c0 = (int64_t)blockIdx.y * 64;   // rows on x: no 65535 limit
-  in += (int64_t)blockIdx.z * s_in;
-  out += (int64_t)blockIdx.z * s_out;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int64_t r = r0 + ty + 4 * i, c = c0 + tx;
-    tile[ty + 4 * i][tx] = (r < rows && c < cols) ? in[r * ld_in + c] : from_f32<T>(0.0f);
-  }
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int64_t c = c0 + ty + 4 * i, r = r0 + tx;
-    if (c < cols && r < rows_store) out[c * ld_out + r] = tile[tx][ty + 4 * i];
-  }
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void copy2d_kernel(const T* in, int64_t ld_in, T* out, int64_t ld_out,
-                                                     int64_t cols) {   // one row per grid row
-  const int64_t r = blockIdx.y;
-  for (int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x; c < cols; c += (int64_t)gridDim.x * 256)
-    out[r * ld_out + c] = in[r * ld_in + c];
-}
-
-// The same with 16-byte copies, for rows whose strides, width and base are multiples of 16
-// bytes.
-__global__ __launch_bounds__(256) void copy2d16_kernel(const u32x4* in, int64_t ld_in, u32x4* out, int64_t ld_out,
-                                                       int64_t cols) {   // strides and cols in 16-byte units
-  const int64_t r = blockIdx.y;
-  for (int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x; c < cols; c += (int64_t)gridDim.x * 256)
-    out[r * ld_out + c] = in[r * ld_in + c];
 }
 
 // ------------------------------------------------------------------ host launchers
@@ -748,7 +699,7 @@ static int ln_param_blocks(int64_t rows, int64_t D, int64_t partial_floats) {
 template <typename TI, typename TD, typename TR, typename TO, typename T2>
 static hipError_t ln_bwd_typed(const void* x, const float* mu, const float* rstd, const float* g, const void* dout,
                                const void* resid, void* out, void* out2, float* dgamma, float* dbeta, float* partial,
-                               int64_t partial_floats, int64_t rows, int64_t D, hipStream_t s) {
+                               int64_t partial_floats, int64_t rows, int64_t D, RowMap map, hipStream_t s) {
   const bool param = dgamma || dbeta;
   const int nblk = param ? ln_param_blocks(rows, D, partial_floats) : 0;
 #define BPT_LN_BWD(NCV, WPRV)                                                                                     \
@@ -756,12 +707,12 @@ static hipError_t ln_bwd_typed(const void* x, const float* mu, const float* rstd
     if (param)                                                                                                    \
       hipLaunchKernelGGL((ln_bwd_reg_kernel<TI, TD, TR, TO, T2, NCV, WPRV, true>), dim3(nblk), dim3(256), 0, s,   \
                          (const TI*)x, mu, rstd, g, (const TD*)dout, (const TR*)resid, (TO*)out, (T2*)out2,       \
-                         partial, rows, (int)D);                                                                  \
+                         partial, rows, (int)D, map);                                                             \
     else                                                                                                          \
       hipLaunchKernelGGL((ln_bwd_reg_kernel<TI, TD, TR, TO, T2, NCV, WPRV, false>),                               \
                          dim3((unsigned)(WPRV == 4 ? rows : (rows + 3) / 4)), dim3(256), 0, s, (const TI*)x, mu,  \
                          rstd, g, (const TD*)dout, (const TR*)resid, (TO*)out, (T2*)out2, (float*)nullptr, rows,  \
-                         (int)D);                                                                                 \
+                         (int)D, map);                                                                            \
   } while (0)
   const int64_t nc = (D + 511) / 512;       // up to 2048 columns a wave holds the row, beyond that four waves do
   if (nc <= 1) BPT_LN_BWD(1, 1);
@@ -780,15 +731,17 @@ static hipError_t ln_bwd_typed(const void* x, const float* mu, const float* rstd
 
 static hipError_t layer_norm_param_grad(Dt ti, const void* x, const float* mu, const float* rstd, const float* dout,
                                         float* dgamma, float* dbeta, float* partial, int64_t rows, int64_t D,
-                                        hipStream_t s);
+                                        RowMap map, hipStream_t s);
 
 bool layer_norm_bwd_fused(int64_t D) { return D % 8 == 0 && D <= 8192; }
 
 hipError_t layer_norm_bwd(Dt ti, const void* x, const float* mu, const float* rstd, const float* g, Dt td,
                           const void* dout, Dt tr, const void* resid, Dt to, void* out, Dt t2, void* out2,
                           float* dgamma, float* dbeta, float* partial, int64_t partial_floats, int64_t rows, int64_t D,
-                          hipStream_t s) {
+                          int64_t seg, int64_t pitch, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
+  RowMap map;
+  if (seg > 0) map.seg = seg, map.gap = pitch - seg;
   const bool param = dgamma || dbeta;
   const uintptr_t all = (uintptr_t)x | (uintptr_t)dout | (uintptr_t)resid | (uintptr_t)out | (uintptr_t)out2 |
                         (uintptr_t)g | (uintptr_t)partial;
@@ -797,7 +750,7 @@ hipError_t layer_norm_bwd(Dt ti, const void* x, const float* mu, const float* rs
 #define BPT_LN_IF(A, TD_, R, O, O2, TI, TD, TR, TO, T2)                                                          \
   if (ti == A && td == TD_ && (!resid || tr == R) && to == O && (!out2 || t2 == O2))                             \
     return ln_bwd_typed<TI, TD, TR, TO, T2>(x, mu, rstd, g, dout, resid, out, out2, dgamma, dbeta, partial,      \
-                                            partial_floats, rows, D, s)
+                                            partial_floats, rows, D, map, s)
     BPT_LN_IF(F32, F32, F32, F32, F32, float, float, float, float, float);
     BPT_LN_IF(F32, F32, BF16, F32, BF16, float, float, bf16, float, bf16);
     BPT_LN_IF(F32, F32, F32, BF16, BF16, float, float, float, bf16, bf16);
@@ -811,26 +764,20 @@ hipError_t layer_norm_bwd(Dt ti, const void* x, const float* mu, const float* rs
   const dim3 grid((unsigned)((rows + 3) / 4));
   BPT_T(ti, TI, BPT_T(tr, TR, BPT_T(to, TO, BPT_T(t2, T2,
         hipLaunchKernelGGL((ln_bwd_kernel<TI, TR, TO, T2>), grid, dim3(256), 0, s, (const TI*)x, mu,
-                           rstd, g, (const float*)dout, (const TR*)resid, (TO*)out, (T2*)out2, rows, D)))));
+                           rstd, g, (const float*)dout, (const TR*)resid, (TO*)out, (T2*)out2, rows, D, map)))));
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !param) return e;
-  return layer_norm_param_grad(ti, x, mu, rstd, (const float*)dout, dgamma, dbeta, partial, rows, D, s);
+  return layer_norm_param_grad(ti, x, mu, rstd, (const float*)dout, dgamma, dbeta, partial, rows, D, map, s);
 }
 
 size_t layer_norm_param_grad_ws(int64_t D) { return (size_t)2 * kChunks * (size_t)D; }
 
 static hipError_t layer_norm_param_grad(Dt ti, const void* x, const float* mu, const float* rstd, const float* dout,
                                         float* dgamma, float* dbeta, float* partial, int64_t rows, int64_t D,
-                                        hipStream_t s) {
-  if (D % 8 == 0 && ((uintptr_t)x & 15) == 0 && ((uintptr_t)dout & 15) == 0 && ((uintptr_t)partial & 15) == 0) {
-    const dim3 grid8((unsigned)((D + 511) / 512), kChunks);
-    BPT_T(ti, TI, hipLaunchKernelGGL((ln_param_partial8_kernel<TI>), grid8, dim3(256), 0, s, (const TI*)x,
-                                     mu, rstd, dout, partial, rows, D));
-  } else {
-    const dim3 grid((unsigned)((D + 255) / 256), kChunks);
-    BPT_T(ti, TI, hipLaunchKernelGGL((ln_param_partial_kernel<TI>), grid, dim3(256), 0, s, (const TI*)x,
-                                     mu, rstd, dout, partial, rows, D));
-  }
+                                        RowMap map, hipStream_t s) {
+  const dim3 grid8((unsigned)((D + 511) / 512), kChunks);
+  BPT_T(ti, TI, hipLaunchKernelGGL((ln_param_partial8_kernel<TI>), grid8, dim3(256), 0, s, (const TI*)x,
+                                   mu, rstd, dout, partial, rows, D, map));
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(chunk_reduce_kernel, dim3((unsigned)((D + 15) / 16)), dim3(256), 0, s, partial, kChunks,
@@ -879,34 +826,6 @@ hipError_t attn_delta(Dt t, const void* dout, const void* o, int64_t ld, const f
   return hipGetLastError();
 }
 
-hipError_t transpose(Dt t, const void* in, int64_t ld_in, int64_t s_in, void* out, int64_t ld_out,
-                     int64_t s_out, int64_t rows, int64_t cols, int64_t rows_store, int batch,
-                     hipStream_t s) {
-  if (cols <= 0 || rows_store <= 0 || batch <= 0) return hipSuccess;
-  const dim3 grid((unsigned)((rows_store + 63) / 64), (unsigned)((cols + 63) / 64), (unsigned)batch);
-  BPT_T(t, T, hipLaunchKernelGGL((transpose_kernel<T>), grid, dim3(256), 0, s, (const T*)in, ld_in, s_in,
-                                 (T*)out, ld_out, s_out, rows, cols, rows_store));
-  return hipGetLastError();
-}
-
-hipError_t copy2d(Dt t, const void* in, int64_t ld_in, void* out, int64_t ld_out, int64_t rows,
-                  int64_t cols, hipStream_t s) {
-  if (rows <= 0 || cols <= 0) return hipSuccess;
-  const int64_t per16 = 16 / (t == F32 ? 4 : 2);   // elements per 16 bytes
-  if (ld_in % per16 == 0 && ld_out % per16 == 0 && cols % per16 == 0 && ((uintptr_t)in & 15) == 0 &&
-      ((uintptr_t)out & 15) == 0) {
-    const int64_t c16 = cols / per16;
-    const unsigned gx = (unsigned)((c16 + 255) / 256 < 64 ? (c16 + 255) / 256 : 64);
-    hipLaunchKernelGGL(copy2d16_kernel, dim3(gx, (unsigned)rows), dim3(256), 0, s, (const u32x4*)in,
-                       ld_in / per16, (u32x4*)out, ld_out / per16, c16);
-    return hipGetLastError();
-  }
-  const unsigned gx = (unsigned)((cols + 255) / 256 < 64 ? (cols + 255) / 256 : 64);
-  BPT_T(t, T, hipLaunchKernelGGL((copy2d_kernel<T>), dim3(gx, (unsigned)rows), dim3(256), 0, s,
-                                 (const T*)in, ld_in, (T*)out, ld_out, cols));
-  return hipGetLastError();
-}
-
 hipError_t xent_rows(const float* z, int64_t ld, int64_t rows, int64_t V, const int32_t* tgt, float* lse,
                      float* tok, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
@@ -921,20 +840,39 @@ hipError_t mean_of(const float* x, int64_t n, float* out, hipStream_t s) {
   return hipGetLastError();
 }
 
-__global__ __launch_bounds__(256) void sum_slices_kernel(const float* part, int nz, int64_t n, float* out,
-                                                         int accumulate) {
+// Slices of K are added in order, four columns per thread; columns of up to three outputs.
+__global__ __launch_bounds__(256) void sum_slices_kernel(const float* part, int nz, int64_t n, int64_t cols4, float* o0,
+                                                         float* o1, float* o2, int64_t nper4, int accumulate) {
   const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;      // group of four
   if (4 * q >= n) return;
-  f32x4 acc = accumulate ? ((const f32x4*)out)[q] : f32x4{0, 0, 0, 0};
-  for (int z = 0; z < nz; ++z) acc += ((const f32x4*)(part + z * n))[q];
-  ((f32x4*)out)[q] = acc;
+  float* out = o0;
+  int64_t at = q;
+  if (nper4 > 0) {
+    const int64_t m = q / cols4, c = q - m * cols4;
+    const int w = c >= 2 * nper4 ? 2 : c >= nper4 ? 1 : 0;
+    out = w == 2 ? o2 : w ? o1 : o0;
+    at = m * nper4 + c - w * nper4;
+  }
+  f32x4 acc = accumulate ? ((const f32x4*)out)[at] : f32x4{0, 0, 0, 0};
+  int z = 0;
+  for (; z + 4 <= nz; z += 4) {                                   // four loads in flight
+    f32x4 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = ((const f32x4*)(part + (z + u) * n))[q];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) acc += v[u];
+  }
+  for (; z < nz; ++z) acc += ((const f32x4*)(part + z * n))[q];
+  ((f32x4*)out)[at] = acc;
 }
 
-hipError_t sum_slices(const float* part, int nz, int64_t n, float* out, int accumulate, hipStream_t s) {
+hipError_t sum_slices(const float* part, int nz, int64_t rows, int64_t cols, float* const outs[3], int64_t nper,
+                      int accumulate, hipStream_t s) {
+  const int64_t n = rows * cols;
   if (n <= 0) return hipSuccess;
-  if (n % 4 != 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(sum_slices_kernel, dim3((unsigned)((n / 4 + 255) / 256)), dim3(256), 0, s, part, nz, n, out,
-                     accumulate);
+  if (cols % 4 != 0 || nper % 4 != 0) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(sum_slices_kernel, dim3((unsigned)((n / 4 + 255) / 256)), dim3(256), 0, s, part, nz, n, cols / 4,
+                     outs[0], nper > 0 ? outs[1] : nullptr, nper > 0 ? outs[2] : nullptr, nper / 4, accumulate);
   return hipGetLastError();
 }
 

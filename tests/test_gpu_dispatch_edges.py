@@ -85,3 +85,34 @@ def test_final_layernorm(in_dtype, out_dtype, rows, D, affine):
         # float32 sums (1e-4 of the RMS, the fp32 gate) and, for a bf16 result, half an ulp
         lim = 1e-4 * ref.square().mean().sqrt() + (2.0 ** -8 * ref.abs() if od == "bf16" else 1e-5 * ref.abs())
         assert ((got.cpu().double() - ref).abs() <= lim).all(), name
+
+
+# bf16 weight gradients over the whole batch: sequences padded to 64 columns in one operand and
+# not in the other, K of any length (T not a multiple of 32), K cut into slices, dWq, dWk, dWv
+# as one product (D % 128 == 0) or three, sequences shorter than a stage
+@pytest.mark.parametrize("B,S,D,H,F,causal", [
+    (7, 1, 256, 2, 256, True), (5, 33, 256, 2, 512, True), (3, 100, 320, 5, 448, False), (9, 95, 128, 1, 192, True),
+    (2, 1000, 768, 6, 1536, True), (4, 320, 512, 8, 1024, False)])
+def test_bf16_weight_gradients_ragged(B, S, D, H, F, causal):
+    w = small_workload("bf16", B=B, S=S, D=D, H=H, F=F, causal=causal, Bq=min(S, 128), Bkv=min(S, 128))
+    inp = make_inputs(w, seed=11, affine=True, biases=True)
+    say(f"case {w.name}")
+    gpu = run_gpu(w, inp, qkv_grads=True)
+    Yr, _, g = run_oracle(w, inp)
+    compare_all(w, inp, gpu, Yr, g, "bf16", w.name)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_some_gradients_only(dtype):
+    """A gradient asked for alone equals the one of a full backward up to the order of its sums."""
+    w = small_workload(dtype, B=3, S=150, D=256, H=2, F=512)
+    inp = make_inputs(w, seed=2, affine=True, biases=True)
+    dev = {k: v.cuda() for k, v in inp.items()}
+    layer = bpt.Layer(bpt.make_config(w.B, w.S, w.D, w.H, w.F, w.Bq, w.Bkv, w.causal, dtype, "f32"))
+    _, saved = layer.forward(dev["X"], dev)
+    dX, full = layer.backward(dev["X"], dev, saved, dev["dY"])
+    for want in (("dWk",), ("dWq", "dWv", "dln1_g"), ("dln2_b", "db1", "dW2")):
+        dX1, some = layer.backward(dev["X"], dev, saved, dev["dY"], want=want)
+        assert torch.equal(dX, dX1) and set(some) == set(want)
+        for n in want:                # float32 sums of the same terms in another order
+            assert (some[n] - full[n]).abs().max() <= 1e-5 * full[n].abs().max(), n
