@@ -8,14 +8,16 @@
 // transposes on its way from LDS into the MFMA registers.
 //
 // bf16 path: gfx950 MFMA v_mfma_f32_32x32x16_bf16, fp32 accumulation; tiles of 256 x 256
-// with 8 waves (2 along M x 4 along N, two per SIMD) or, where fewer than 256 such tiles
-// exist, 128 x 128 with 4 waves (2 x 2); K step 32 per stage through an LDS ring with
+// with 8 waves (2 along M x 4 along N, two per SIMD), of 128 x 128 or 64 x 64 with 4 waves
+// (2 x 2), chosen by estimated time (tile_us); K step 32 per stage through an LDS ring with
 // XOR-swizzled 16-byte chunks, so that the rows a fragment read touches fall in distinct
 // banks. fp32 path: the same structure on v_mfma_f32_16x16x4_f32 (gemm_f32_kernel).
-#include "common.h"
-#include "internal.h"
+#include <algorithm>
 #include <cmath>
 #include <type_traits>
+
+#include "common.h"
+#include "internal.h"
 
 namespace bpt {
 
@@ -46,13 +48,7 @@ BPT_DEV void act_both(float z, float& g, float& gp) {
   }
 }
 
-// EPI_XENT: d loss / d logit of column n for a row with log-sum-exp lse and target y
-BPT_DEV float xent_grad(const GemmArgs& a, int64_t n, float v, float lse, int y) {
-  if (n >= a.nvalid) return 0.0f;
-  const float p = __builtin_amdgcn_exp2f((v - lse) * 1.4426950408889634f);
-  return a.alpha * (n == y ? p - 1.0f : p);
-}
-// EPI_XENT_T: the same for element (m, n) of the transposed logits, vocabulary index m
+// EPI_XENT_T: d loss / d logit for element (m, n) of the transposed logits, vocabulary index m
 // and token n. Edge tiles and full tiles (whose epilogue holds each column's base-2
 // log-sum-exp) evaluate the same expression, so a token's gradient does not depend on
 // where the tile boundaries fall.
@@ -91,8 +87,6 @@ BPT_DEV void epi_store(const GemmArgs& a, int64_t z, int64_t m, int64_t n, float
     act_both<EPI>(v, g, gp);
     C[idx] = from_f32<CT>(g);
     if (a.C2) c2_store(a, z * a.sC2 + m * a.ldc2 + n, gp);
-  } else if constexpr (EPI == EPI_XENT) {
-    C[idx] = from_f32<CT>(xent_grad(a, n, v, a.rowv[m], a.tgt[m]));
   } else if constexpr (EPI == EPI_XENT_T) {
     C[idx] = from_f32<CT>(xent_grad_t(a, m, n, v));
   } else {  // EPI_MUL
@@ -157,11 +151,6 @@ BPT_DEV void epi_store4(const GemmArgs& a, int64_t z, int64_t m, int64_t n, int6
       d[e] = gp;
     }
     if (a.C2) c2_store4(a, z * a.sC2 + m * a.ldc2 + n, d);
-  } else if constexpr (EPI == EPI_XENT) {
-    const float lse = a.rowv[m];
-    const int y = a.tgt[m];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = xent_grad(a, n + e, v[e], lse, y);
   } else if constexpr (EPI == EPI_XENT_T) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) v[e] = xent_grad_t(a, m, n + e, v[e]);
@@ -174,12 +163,9 @@ BPT_DEV void epi_store4(const GemmArgs& a, int64_t z, int64_t m, int64_t n, int6
 // Four consecutive columns n..n+3 of row m inside the stored width, from pointers
 // already at (m, n): c into C, r into R (EPI_RESID / EPI_MUL; for an fp32 C that
 // accumulates, the values of C already loaded); c2 is the element index of (m, n) in
-// C2 (EPI_GELU / EPI_RELU); bn at bias[n]; bm = bias[m] for a per-row bias, or the row's
-// log-sum-exp for EPI_XENT, whose column is n and target y; EPI_XENT_T takes row m
-// (passed as y) and column n.
+// C2 (EPI_GELU / EPI_RELU); bn at bias[n]; bm = bias[m] for a per-row bias.
 template <int EPI, typename CT, typename RT>
-BPT_DEV void epi_vec4(const GemmArgs& a, CT* c, const void* r, int64_t c2, const float* bn, float bm, f32x4 v,
-                      int64_t n = 0, int64_t y = 0) {
+BPT_DEV void epi_vec4(const GemmArgs& a, CT* c, const void* r, int64_t c2, const float* bn, float bm, f32x4 v) {
   if constexpr (EPI == EPI_STORE) {
     v *= a.alpha;
     if constexpr (sizeof(CT) == 4) {
@@ -202,12 +188,6 @@ BPT_DEV void epi_vec4(const GemmArgs& a, CT* c, const void* r, int64_t c2, const
       d[e] = gp;
     }
     if (a.C2) c2_store4(a, c2, d);
-  } else if constexpr (EPI == EPI_XENT) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = xent_grad(a, n + e, v[e], bm, (int)y);
-  } else if constexpr (EPI == EPI_XENT_T) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = xent_grad_t(a, y, n + e, v[e]);
   } else {
     v *= V4<RT>::ld((const RT*)r);
   }
@@ -222,11 +202,14 @@ BPT_DEV void epi_vec4(const GemmArgs& a, CT* c, const void* r, int64_t c2, const
 // touches over distinct bank groups. The copies apply the same permutation on the
 // global side, so a wave's 1 KiB copy block still lands contiguously. K must be a
 // multiple of 32 (host-checked).
-template <int BM, int BN, int NWN = 2>
+//
+// KG > 1: KG groups of 2 x NWN waves share a tile, each with its own ring and its own run of
+// K stages; group 0 adds the others' accumulators, in order, and runs the epilogue.
+template <int BM, int BN, int NWN = 2, int KG = 1>
 struct TileCfg {
   static constexpr int BK = 32;
   static constexpr int PITCH = 64;                     // bytes per tile row
-  static constexpr int NW = 2 * NWN;                  // waves: 2 along M x NWN along N
+  static constexpr int NW = 2 * NWN;                  // waves of a group: 2 along M x NWN along N
   static constexpr int WM = BM / 2, WN = BN / NWN;    // wave tile
   static constexpr int TM = WM / 32, TN = WN / 32;    // 32x32 MFMA tiles per wave
   static constexpr int ABYTES = BM * PITCH, BBYTES = BN * PITCH;
@@ -235,7 +218,8 @@ struct TileCfg {
   static constexpr int DPS = APW + BPW;               // copy instructions per wave per stage
   static constexpr int STAGE = ABYTES + BBYTES;
   static constexpr int NS = 4;                        // stages in the ring
-  static constexpr int LDS = NS * STAGE;
+  static constexpr int RING = NS * STAGE, LDS = KG * RING;
+  static_assert(KG == 1 || NW * TM * TN * 4096 <= RING, "a group's accumulators fit its ring");
   static_assert(ABYTES % 1024 == 0 && BBYTES % 1024 == 0, "whole copy blocks");
   static_assert(NW * (WN + 4) * 32 * 4 <= LDS, "epilogue staging fits");
 };
@@ -258,7 +242,8 @@ BPT_DEV int swz(int r) { return (((r >> 1) ^ (r >> 3)) & 1) | (r & 4) >> 1; }
 template <int N> BPT_DEV void wait_vmcnt() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 
 // Operand tiles stored transposed (source rows are k, the M or N extent contiguous):
-// 32 rows of 2 * BX bytes per stage, chunk c of row k at chunk position c ^ 4 (k % 4).
+// 32 rows of 2 * BX bytes per stage, chunk c of row k at chunk position c ^ 4 (k % 4) (k % 2
+// for the 128-byte rows of BX = 64).
 // A fragment (8 consecutive k of one column per lane) is two ds_read_b64_tr_b16: in each
 // group of 16 lanes, lane m addresses 4 columns of one row (row m / 4, columns 4 (m % 4)..)
 // and receives column m of the group's 4 rows. Over the 32 lanes the hardware serves
@@ -267,6 +252,7 @@ template <int BX>
 struct TrTile {
   static constexpr int RB = 2 * BX;                    // bytes per k row
   static constexpr int CPR = RB / 16;                  // 16-byte chunks per row
+  static constexpr int XM = BX / 32 < 4 ? BX / 32 - 1 : 3;   // bits of k that move its blocks of 64 bytes
 };
 
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short g_s16x4;
@@ -285,7 +271,7 @@ BPT_DEV bf16x8 tr_frag(const char* p, int second) {
 template <int BX>
 BPT_DEV void tr_slot(int slot, int& row, int& col, int cols_left) {
   row = slot / TrTile<BX>::CPR;
-  const int lc = (slot % TrTile<BX>::CPR) ^ (4 * (row & 3));
+  const int lc = (slot % TrTile<BX>::CPR) ^ (4 * (row & TrTile<BX>::XM));
   col = 8 * lc < cols_left - 8 ? 8 * lc : cols_left - 8;
 }
 
@@ -323,6 +309,13 @@ BPT_DEV void tile_of_three(GemmArgs& a, int64_t n0, const T*& B) {
   if (w) a.alpha = 1.0f;
 }
 
+// B for k stages from k on, where K runs through three matrices (kper); the copies move it on
+template <typename T>
+BPT_DEV const T* b_of_k(const GemmArgs& a, int64_t n0, int64_t k) {
+  const int w = k >= 2 * a.kper ? 2 : k >= a.kper ? 1 : 0;
+  return (const T*)(w == 2 ? a.Bx[2] : w ? a.Bx[1] : a.Bx[0]) + n0 * a.ldb - w * a.kper;
+}
+
 // Rows of a K-major operand in segments (GemmArgs::seg_pitch): k index of the current segment
 // and how far its rows lie before their k index. Stages are visited in increasing order.
 struct KSegs {
@@ -342,12 +335,14 @@ struct KSegs {
 };
 
 template <int BM, int BN, int EPI, typename CT, typename RT, bool TA = false, bool TB = false, int NWN = 2,
-          int KF = 0>
-__global__ __launch_bounds__(128 * NWN, 1) void gemm_bf16_kernel(GemmArgs a) {
-  using Cfg = TileCfg<BM, BN, NWN>;
-  extern __shared__ __attribute__((aligned(16))) char smem[];
+          int KF = 0, int KG = 1>
+__global__ __launch_bounds__(128 * NWN * KG, 1) void gemm_bf16_kernel(GemmArgs a) {
+  using Cfg = TileCfg<BM, BN, NWN, KG>;
+  extern __shared__ __attribute__((aligned(16))) char smem_all[];
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = KG > 1 ? wave_all % Cfg::NW : wave_all, kg = KG > 1 ? wave_all / Cfg::NW : 0;
+  char* smem = smem_all + kg * Cfg::RING;
   const int wm = wave / NWN, wn = wave % NWN;
   // Tile order. Workgroup i runs on XCD i % 8, and each XCD has its own L2. The ids are
   // renumbered so that every XCD owns a contiguous range of tiles; within the range,
@@ -371,7 +366,14 @@ __global__ __launch_bounds__(128 * NWN, 1) void gemm_bf16_kernel(GemmArgs a) {
   const bf16* B = (const bf16*)a.B + z * a.sB + (TB ? n0 : n0 * a.ldb);
   int kb, nk;                                          // first stage and number of stages
   k_range<Cfg::BK, EPI, CT>(a, z, kb, nk);
+  int nit = nk;                                        // stages of the longest group: barriers to pass
+  if constexpr (KG > 1) {
+    nit = (nk + KG - 1) / KG;
+    kb += kg * nit;
+    nk = nk - kg * nit < nit ? (nk - kg * nit > 0 ? nk - kg * nit : 0) : nit;
+  }
   if constexpr (KF & KF_NPER) tile_of_three<TB, bf16, CT>(a, n0, B);
+  if constexpr (KF & KF_KPER) B = b_of_k<bf16>(a, n0, (int64_t)kb * Cfg::BK);
   // transposed operands: readable k rows and columns (from the tile's first column)
   const int64_t arows = a.a_rows > 0 ? a.a_rows : a.K, brows = a.b_rows > 0 ? a.b_rows : a.K;
   const int acols = (int)((a.a_cols > 0 ? a.a_cols : a.M) - m0);
@@ -461,8 +463,7 @@ __global__ __launch_bounds__(128 * NWN, 1) void gemm_bf16_kernel(GemmArgs a) {
                     st + Cfg::ABYTES + blk * 1024);
       } else if constexpr (KF & KF_KPER) {
         // stages are copied in order, so B moves on to the next matrix when k reaches it
-        if (d == Cfg::APW && (k0 == a.kper || k0 == 2 * a.kper))
-          B = (const bf16*)(k0 == a.kper ? a.Bx[1] : a.Bx[2]) + n0 * a.ldb - k0;
+        if (d == Cfg::APW && (k0 == a.kper || k0 == 2 * a.kper)) B = b_of_k<bf16>(a, n0, k0);
         lds_dma16(B + k0 + boff[d - Cfg::APW], st + Cfg::ABYTES + blk * 1024);
       } else
         lds_dma16(B + k0 + boff[d - Cfg::APW], st + Cfg::ABYTES + blk * 1024);
@@ -493,12 +494,12 @@ __global__ __launch_bounds__(128 * NWN, 1) void gemm_bf16_kernel(GemmArgs a) {
     if constexpr (TA) {
 #pragma unroll
       for (int i = 0; i < Cfg::TM; ++i)
-        tra[i] = rowpart * TrTile<BM>::RB + 64 * (((wm * Cfg::WM) / 32 + i) ^ sx) + within;
+        tra[i] = rowpart * TrTile<BM>::RB + 64 * (((wm * Cfg::WM) / 32 + i) ^ (sx & TrTile<BM>::XM)) + within;
     }
     if constexpr (TB) {
 #pragma unroll
       for (int j = 0; j < Cfg::TN; ++j)
-        trb[j] = Cfg::ABYTES + rowpart * TrTile<BN>::RB + 64 * (((wn * Cfg::WN) / 32 + j) ^ sx) + within;
+        trb[j] = Cfg::ABYTES + rowpart * TrTile<BN>::RB + 64 * (((wn * Cfg::WN) / 32 + j) ^ (sx & TrTile<BN>::XM)) + within;
     }
   }
   bf16x8 fa[2][Cfg::TM], fb[2][Cfg::TN];
@@ -528,7 +529,14 @@ __global__ __launch_bounds__(128 * NWN, 1) void gemm_bf16_kernel(GemmArgs a) {
     for (int q = 0; q < TMN; ++q) {
       acc[q / Cfg::TN][q % Cfg::TN] = mfma32x32x16(fa[cur][q / Cfg::TN], fb[cur][q % Cfg::TN],
                                                     acc[q / Cfg::TN][q % Cfg::TN]);
-      if (rd && q < NR) read_frag(rst, rkk, 1 - cur, q);
+      if (rd) {
+        if constexpr (TMN >= NR) {
+          if (q < NR) read_frag(rst, rkk, 1 - cur, q);
+        } else {
+#pragma unroll
+          for (int r = q * NR / TMN; r < (q + 1) * NR / TMN; ++r) read_frag(rst, rkk, 1 - cur, r);
+        }
+      }
       if (cp) {
 #pragma unroll
         for (int d = (q * Cfg::DPS + TMN - 1) / TMN; d < ((q + 1) * Cfg::DPS + TMN - 1) / TMN; ++d) dma(dkt, d, fast_c);
@@ -592,7 +600,38 @@ __global__ __launch_bounds__(128 * NWN, 1) void gemm_bf16_kernel(GemmArgs a) {
     kstep(I0{}, T_{}, F_{}, nk - 1, 1, 0, F_{});
     kstep(I1{}, F_{}, F_{}, 0, 0, 0, F_{});
   }
+  if constexpr (KG > 1) {
+    // each stage but a group's last passed one barrier: catch up with the longest group
+    for (int i = nk > 0 ? nk : 1; i < nit; ++i) __syncthreads();
+  }
   __syncthreads();
+  if constexpr (KG > 1) {
+    if (kg > 0) {
+#pragma unroll
+      for (int i = 0; i < Cfg::TM; ++i)
+#pragma unroll
+        for (int j = 0; j < Cfg::TN; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; r += 4)
+            *(f32x4*)(smem + ((((wave * Cfg::TM + i) * Cfg::TN + j) * 4 + r / 4) * 64 + lane) * 16) =
+                f32x4{acc[i][j][r], acc[i][j][r + 1], acc[i][j][r + 2], acc[i][j][r + 3]};
+    }
+    __syncthreads();
+    if (kg > 0) return;                                // no barrier follows
+#pragma unroll
+    for (int k = 1; k < KG; ++k)
+#pragma unroll
+      for (int i = 0; i < Cfg::TM; ++i)
+#pragma unroll
+        for (int j = 0; j < Cfg::TN; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; r += 4) {
+            const f32x4 v = *(const f32x4*)(smem + k * Cfg::RING +
+                                            ((((wave * Cfg::TM + i) * Cfg::TN + j) * 4 + r / 4) * 64 + lane) * 16);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[i][j][r + e] += v[e];
+          }
+  }
 
   // Epilogue: each wave stages one 32-row strip of its accumulators in its own part of
   // the (now idle) LDS, then every lane applies the epilogue to groups of 4 consecutive
@@ -683,20 +722,13 @@ __global__ __launch_bounds__(128 * NWN, 1) void gemm_bf16_kernel(GemmArgs a) {
       for (int it = 0; it < 32 / RSTEP; ++it) {
         const int row = r0 + RSTEP * it;
         const f32x4 v = *(const f32x4*)(strip + row * PITCHF + c0);
-        float bm = (kAct<EPI> && a.bias && a.bias_on_m) ? a.bias[mrow + row] : 0.0f;
-        int64_t y = 0;
-        if constexpr (EPI == EPI_XENT) {
-          bm = a.rowv[mrow + row];
-          y = a.tgt[mrow + row];
-        } else if constexpr (EPI == EPI_XENT_T) {
-          y = mrow + row;                              // the row's vocabulary index
-        }
+        const float bm = (kAct<EPI> && a.bias && a.bias_on_m) ? a.bias[mrow + row] : 0.0f;
         if constexpr (PRE)
           epi_vec4<EPI, CT, RT>(a, cb + (int64_t)RSTEP * it * a.ldc, &pre[i % PD][it], 0, bb, bm, v);
         else
           epi_vec4<EPI, CT, RT>(a, cb + (int64_t)RSTEP * it * a.ldc,
                                 rb + (int64_t)RSTEP * it * a.ldr * RS,
-                                c2b + (int64_t)RSTEP * it * a.ldc2, bb, bm, v, ncol + c0, y);
+                                c2b + (int64_t)RSTEP * it * a.ldc2, bb, bm, v);
       }
       if (do_pre && i + PD < Cfg::TM) preload(i + PD);
     } else {
@@ -751,6 +783,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a) {
   int kb, nk;                                          // first stage and number of stages
   k_range<C::BK, EPI, CT>(a, z, kb, nk);
   if constexpr (KF & KF_NPER) tile_of_three<TB, float, CT>(a, n0, B);
+  if constexpr (KF & KF_KPER) B = b_of_k<float>(a, n0, (int64_t)kb * C::BK);
   const int64_t arows = a.a_rows > 0 ? a.a_rows : a.K, brows = a.b_rows > 0 ? a.b_rows : a.K;
   const int acols = (int)((a.a_cols > 0 ? a.a_cols : a.M) - m0), bcols = (int)((a.b_cols > 0 ? a.b_cols : a.N) - n0);
   const uint32_t ring = __builtin_amdgcn_readfirstlane(
@@ -786,7 +819,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a) {
       alim = segs.limit(a);
     }
     if constexpr (KF & KF_KPER) {   // stages are copied in order: on to the next matrix when k reaches it
-      if (k0 == a.kper || k0 == 2 * a.kper) B = (const float*)(k0 == a.kper ? a.Bx[1] : a.Bx[2]) + n0 * a.ldb - k0;
+      if (k0 == a.kper || k0 == 2 * a.kper) B = b_of_k<float>(a, n0, k0);
     }
 #pragma unroll
     for (int i = 0; i < C::DPS; ++i) {
@@ -852,10 +885,14 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a) {
 }
 
 // ------------------------------------------------------------------ dispatch
-template <int BM, int BN, int EPI, typename CT, typename RT, bool TA = false, bool TB = false, int NWN = 2, int KF = 0>
+static int k_form(const GemmArgs& a) {
+  return (a.seg_pitch > 0 ? KF_SEG : 0) | (a.kper > 0 ? KF_KPER : 0) | (a.nper > 0 ? KF_NPER : 0);
+}
+
+template <int BM, int BN, int NWN, int KG, int EPI, typename CT, typename RT, bool TA, bool TB, int KF>
 static hipError_t launch_bf16(const GemmArgs& a, hipStream_t s) {
-  using Cfg = TileCfg<BM, BN, NWN>;
-  auto kern = gemm_bf16_kernel<BM, BN, EPI, CT, RT, TA, TB, NWN, KF>;
+  using Cfg = TileCfg<BM, BN, NWN, KG>;
+  auto kern = gemm_bf16_kernel<BM, BN, EPI, CT, RT, TA, TB, NWN, KF, KG>;
   static bool attr_set = false;
   if (!attr_set) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -866,22 +903,79 @@ static hipError_t launch_bf16(const GemmArgs& a, hipStream_t s) {
   const int64_t ncols = a.Nstore > a.N ? a.Nstore : a.N;
   const int64_t tiles = ((a.M + BM - 1) / BM) * ((ncols + BN - 1) / BN);
   if (tiles <= 0 || a.batch <= 0) return hipSuccess;
-  if (a.K % Cfg::BK != 0 && !(TA && TB)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(kern, dim3((unsigned)tiles, 1, (unsigned)(a.ksplit > 1 ? a.ksplit : a.batch)), dim3(64 * Cfg::NW), Cfg::LDS, s, a);
+  hipLaunchKernelGGL(kern, dim3((unsigned)tiles, 1, (unsigned)(a.ksplit > 1 ? a.ksplit : a.batch)),
+                     dim3(64 * Cfg::NW * KG), Cfg::LDS, s, a);
   return hipGetLastError();
 }
 
-// waves along N of the 256 x 256 tile configuration
-static constexpr int kNWN = 4;
+// The bf16 tile forms: 256 x 256 (8 waves), 128 x 128 and 64 x 64 (4 waves), 64 x 64 with four
+// groups of 4 waves sharing K.
+enum Tile { T256, T128, T64, T64K4 };
 
-static int k_form(const GemmArgs& a) {
-  return (a.seg_pitch > 0 ? KF_SEG : 0) | (a.kper > 0 ? KF_KPER : 0) | (a.nper > 0 ? KF_NPER : 0);
+// Estimated microseconds of n tiles of `stages` k stages. Fitted to measurements of 25 shapes
+// of 64..24000 rows and K = 512..4096 with a residual, GELU or plain epilogue. A full round of
+// 256 x 256 tiles takes 0.75 per stage (0.45 while few CUs work) and 16 for prologue and
+// epilogue, whose stores all CUs issue at once; 128 x 128 tiles 0.26 with one workgroup on a
+// CU and 0.55 with two (they share the LDS, which is what bounds them); 64 x 64 tiles 0.108
+// alone and 0.13 each up to five on a CU; the K-sharing form takes a quarter of the stages at
+// 0.25 (few CUs) to 0.5. Beyond 8192 k the operands no longer stay in the L2s and the smaller
+// tiles, which read them more often, slow down (128 x 128: 0.37 at K = 24000 and 50304).
+static double tile_us(Tile t, int64_t n, double stages) {
+  const double full = t == T128 ? 512 : t == T64 ? 1280 : 256;
+  const double rounds = std::floor((double)n / full), rem = (double)n - rounds * full;
+  if (stages > 256 && t != T256) stages *= 1.35;
+  switch (t) {
+    case T256: return rounds * (stages * 0.75 + 16) + (rem > 0 ? stages * (0.45 + 0.3 * rem / 256) + 16 : 0);
+    case T128:
+      return rounds * (stages * 0.55 + 5) +
+             (rem > 256 ? stages * (0.26 + 0.29 * (rem - 256) / 256) + 5 : rem > 0 ? stages * 0.26 + 5 : 0);
+    case T64:
+      return rounds * (stages * 0.65 + 4) + (rem > 256 ? stages * 0.13 * rem / 256 + 4 : rem > 0 ? stages * 0.108 + 4 : 0);
+    case T64K4: {
+      const double it = std::ceil(stages / 4);
+      return rounds * (it * 0.5 + 6) + (rem > 0 ? it * (0.25 + 0.25 * rem / 256) + 6 : 0);
+    }
+  }
+  return 0;
+}
+
+// The cheapest tile form for M x ncols over nz batch entries or K slices of `stages` stages.
+// Columns of three matrices (nper) keep a tile inside one of them.
+static Tile best_tile(int64_t M, int64_t ncols, int64_t nz, double stages, int64_t nper, double* us) {
+  Tile best = T128;
+  double t = -1;
+  for (Tile c : {T128, T256, T64, T64K4}) {
+    const int64_t b = c == T256 ? 256 : c == T128 ? 128 : 64;
+    if (nper % b != 0) continue;
+    const double u = tile_us(c, ((M + b - 1) / b) * ((ncols + b - 1) / b) * nz, stages);
+    if (t < 0 || u < t) {
+      t = u;
+      best = c;
+    }
+  }
+  if (us) *us = t;
+  return best;
+}
+
+static Tile pick_tile(const GemmArgs& a) {
+  const int64_t ncols = a.Nstore > a.N ? a.Nstore : a.N, nk = (a.K + 31) / 32;
+  const int64_t z = std::max(a.ksplit, 1);
+  return best_tile(a.M, ncols, a.batch * z, (double)((nk + z - 1) / z), a.nper, nullptr);
 }
 
 template <int EPI, typename CT, typename RT, bool TA, bool TB, int KF = 0>
-static hipError_t launch_ops(int64_t big, const GemmArgs& a, hipStream_t s) {
-  return big >= 256 ? launch_bf16<256, 256, EPI, CT, RT, TA, TB, kNWN, KF>(a, s)
-                    : launch_bf16<128, 128, EPI, CT, RT, TA, TB, 2, KF>(a, s);
+static hipError_t launch_ops(const GemmArgs& a, hipStream_t s) {
+  if (a.K % 32 != 0 && !(TA && TB)) return hipErrorInvalidValue;
+  // a K-major operand is read in 16-byte column chunks
+  if ((TA && ((a.a_cols > 0 ? a.a_cols : a.M) % 8 || a.lda % 8)) || (TB && ((a.b_cols > 0 ? a.b_cols : a.N) % 8 || a.ldb % 8)))
+    return hipErrorInvalidValue;
+  switch (pick_tile(a)) {
+    case T256: return launch_bf16<256, 256, 4, 1, EPI, CT, RT, TA, TB, KF>(a, s);
+    case T128: return launch_bf16<128, 128, 2, 1, EPI, CT, RT, TA, TB, KF>(a, s);
+    case T64: return launch_bf16<64, 64, 2, 1, EPI, CT, RT, TA, TB, KF>(a, s);
+    case T64K4: return launch_bf16<64, 64, 2, 4, EPI, CT, RT, TA, TB, KF>(a, s);
+  }
+  return hipErrorInvalidValue;
 }
 
 template <int BX, int EPI, typename CT, typename RT, bool TA, bool TB, int KF>
@@ -899,6 +993,10 @@ static hipError_t launch_f32_tile(const GemmArgs& a, hipStream_t s) {
 // them in flight).
 template <int EPI, typename CT, typename RT, bool TA, bool TB, int KF = 0>
 static hipError_t launch_f32_ops(const GemmArgs& a, hipStream_t s) {
+  // 16-byte copies along the operands' contiguous extent, 16-byte stores of 4 columns
+  if ((a.K % 16 && !(TA && TB)) || a.lda % 4 || a.ldb % 4 || a.ldc % 4 ||
+      (TA && (a.a_cols > 0 ? a.a_cols : a.M) % 4) || (TB && (a.b_cols > 0 ? a.b_cols : a.N) % 4))
+    return hipErrorInvalidValue;
   const int64_t ncols = a.Nstore > a.N ? a.Nstore : a.N;
   auto tiles = [&](int64_t b) { return ((a.M + b - 1) / b) * ((ncols + b - 1) / b) * a.batch * a.ksplit; };
   if (a.nper % 128 == 0 && tiles(128) >= 256) return launch_f32_tile<128, EPI, CT, RT, TA, TB, KF>(a, s);
@@ -906,92 +1004,69 @@ static hipError_t launch_f32_ops(const GemmArgs& a, hipStream_t s) {
   return launch_f32_tile<32, EPI, CT, RT, TA, TB, KF>(a, s);
 }
 
+// Forms of one element type and epilogue, by which operands are K-major: those listed, and
+// only those, are instantiated.
+#define BPT_GEMM_FORM(ops, TA, TB, KF) \
+  if (a.trans_a == TA && a.trans_b == TB && k_form(a) == (KF)) return ops<EPI, CT, RT, TA, TB, KF>(a, s)
+
 template <int EPI, typename CT, typename RT>
-static hipError_t launch_f32(const GemmArgs& a, hipStream_t s) {
-  // 16-byte copies along the operands' contiguous extent, 16-byte stores of 4 columns
-  if ((a.K % 16 && !(a.trans_a && a.trans_b)) || a.lda % 4 || a.ldb % 4 || a.ldc % 4 || (a.trans_a && (a.a_cols > 0 ? a.a_cols : a.M) % 4) ||
-      (a.trans_b && (a.b_cols > 0 ? a.b_cols : a.N) % 4))
-    return hipErrorInvalidValue;
-  if (a.trans_a && a.trans_b) {
-    if constexpr (EPI == EPI_STORE)
-      if (!k_form(a)) return launch_f32_ops<EPI, CT, RT, true, true>(a, s);
-    return hipErrorInvalidValue;
+static hipError_t run_bf16(const GemmArgs& a, hipStream_t s) {
+  constexpr bool f32_out = std::is_same_v<CT, float>;
+  if constexpr (EPI == EPI_STORE && f32_out) {
+    BPT_GEMM_FORM(launch_ops, 0, 1, 0);                // logits, dW2, Wo and W2 with dropout
+    BPT_GEMM_FORM(launch_ops, 1, 0, 0);                // dv, dW1, head dW; dWq, dWk, dWv one by one
+    BPT_GEMM_FORM(launch_ops, 1, 0, KF_SEG);
+    BPT_GEMM_FORM(launch_ops, 1, 0, KF_NPER);          // dWq, dWk, dWv at once
+    BPT_GEMM_FORM(launch_ops, 1, 0, KF_SEG | KF_NPER);
+    BPT_GEMM_FORM(launch_ops, 1, 0, KF_KPER);          // dU
+    BPT_GEMM_FORM(launch_ops, 1, 1, 0);                // dWo
+  } else if constexpr (EPI == EPI_STORE) {
+    BPT_GEMM_FORM(launch_ops, 0, 0, 0);                // dO
+    BPT_GEMM_FORM(launch_ops, 0, 1, 0);                // Q, K, V
+    BPT_GEMM_FORM(launch_ops, 0, 1, KF_NPER);
+    BPT_GEMM_FORM(launch_ops, 1, 0, 0);                // head dh
+  } else if constexpr (EPI == EPI_RESID) {
+    BPT_GEMM_FORM(launch_ops, 0, 1, 0);                // Wo, FFN2
+  } else if constexpr (kAct<EPI>) {
+    BPT_GEMM_FORM(launch_ops, 0, 1, 0);                // FFN1
+    BPT_GEMM_FORM(launch_ops, 1, 0, 0);                // its recompute
+  } else if constexpr (EPI == EPI_MUL) {
+    BPT_GEMM_FORM(launch_ops, 0, 0, 0);                // dZ
+  } else {
+    BPT_GEMM_FORM(launch_ops, 1, 0, 0);                // head gradient
   }
-  if (a.trans_a) {
-    if constexpr (EPI == EPI_STORE && std::is_same_v<CT, float>) {
-      switch (k_form(a)) {
-        case 0: break;
-        case KF_SEG: return launch_f32_ops<EPI, CT, RT, true, false, KF_SEG>(a, s);
-        case KF_KPER: return launch_f32_ops<EPI, CT, RT, true, false, KF_KPER>(a, s);
-        case KF_NPER: return launch_f32_ops<EPI, CT, RT, true, false, KF_NPER>(a, s);
-        case KF_SEG | KF_NPER: return launch_f32_ops<EPI, CT, RT, true, false, KF_SEG | KF_NPER>(a, s);
-        default: return hipErrorInvalidValue;
-      }
-    }
-    if (k_form(a)) return hipErrorInvalidValue;
-    if constexpr (EPI == EPI_STORE || kAct<EPI> || EPI == EPI_XENT_T) return launch_f32_ops<EPI, CT, RT, true, false>(a, s);
-    return hipErrorInvalidValue;
-  }
-  if (a.trans_b) {
-    if constexpr (EPI == EPI_STORE) {
-      if (k_form(a) == KF_NPER) return launch_f32_ops<EPI, CT, RT, false, true, KF_NPER>(a, s);
-    }
-    return k_form(a) ? hipErrorInvalidValue : launch_f32_ops<EPI, CT, RT, false, true>(a, s);
-  }
-  return k_form(a) ? hipErrorInvalidValue : launch_f32_ops<EPI, CT, RT, false, false>(a, s);
+  return hipErrorInvalidValue;
 }
 
 template <int EPI, typename CT, typename RT>
-static hipError_t launch_typed(Dt ab, const GemmArgs& a, hipStream_t s) {
-  const int64_t ncols = a.Nstore > a.N ? a.Nstore : a.N;
-  if (ab == F32) return launch_f32<EPI, CT, RT>(a, s);
-  // 256 x 256 tiles where they give every CU one, 128 x 128 ones elsewhere (and where the
-  // columns of a tile would belong to two matrices)
-  const int64_t big = a.nper % 256 ? 0 : ((a.M + 255) / 256) * ((ncols + 255) / 256) * a.batch * a.ksplit;
-  if (a.trans_a || a.trans_b) {
-    // a transposed operand is read in 16-byte column chunks
-    if ((a.trans_a && ((a.a_cols > 0 ? a.a_cols : a.M) % 8 || a.lda % 8)) ||
-        (a.trans_b && ((a.b_cols > 0 ? a.b_cols : a.N) % 8 || a.ldb % 8)))
-      return hipErrorInvalidValue;
-    // instantiated combinations: B transposed with every epilogue, A transposed with
-    // the plain store and the activation epilogues, both with the plain store
-    if (a.trans_a && a.trans_b) {
-      if constexpr (EPI == EPI_STORE)
-        if (!k_form(a)) return launch_ops<EPI, CT, RT, true, true>(big, a, s);
-      return hipErrorInvalidValue;
-    }
-    if (a.trans_a) {
-      if constexpr (EPI == EPI_STORE && std::is_same_v<CT, float>) {
-        switch (k_form(a)) {
-          case 0: break;
-          case KF_SEG: return launch_ops<EPI, CT, RT, true, false, KF_SEG>(big, a, s);
-          case KF_KPER: return launch_ops<EPI, CT, RT, true, false, KF_KPER>(big, a, s);
-          case KF_NPER: return launch_ops<EPI, CT, RT, true, false, KF_NPER>(big, a, s);
-          case KF_SEG | KF_NPER: return launch_ops<EPI, CT, RT, true, false, KF_SEG | KF_NPER>(big, a, s);
-          default: return hipErrorInvalidValue;
-        }
-      }
-      if (k_form(a)) return hipErrorInvalidValue;
-      if constexpr (EPI == EPI_STORE || kAct<EPI> || EPI == EPI_XENT_T)
-        return launch_ops<EPI, CT, RT, true, false>(big, a, s);
-      return hipErrorInvalidValue;
-    }
-    if constexpr (EPI == EPI_STORE) {
-      if (k_form(a) == KF_NPER) return launch_ops<EPI, CT, RT, false, true, KF_NPER>(big, a, s);
-    }
-    return k_form(a) ? hipErrorInvalidValue : launch_ops<EPI, CT, RT, false, true>(big, a, s);
+static hipError_t run_f32(const GemmArgs& a, hipStream_t s) {
+  if constexpr (EPI == EPI_STORE) {
+    BPT_GEMM_FORM(launch_f32_ops, 0, 0, 0);
+    BPT_GEMM_FORM(launch_f32_ops, 0, 1, 0);
+    BPT_GEMM_FORM(launch_f32_ops, 0, 1, KF_NPER);
+    BPT_GEMM_FORM(launch_f32_ops, 1, 0, 0);
+    BPT_GEMM_FORM(launch_f32_ops, 1, 0, KF_SEG);
+    BPT_GEMM_FORM(launch_f32_ops, 1, 0, KF_NPER);
+    BPT_GEMM_FORM(launch_f32_ops, 1, 0, KF_SEG | KF_NPER);
+    BPT_GEMM_FORM(launch_f32_ops, 1, 0, KF_KPER);
+    BPT_GEMM_FORM(launch_f32_ops, 1, 1, 0);
+  } else if constexpr (EPI == EPI_RESID) {
+    BPT_GEMM_FORM(launch_f32_ops, 0, 1, 0);
+  } else if constexpr (kAct<EPI>) {
+    BPT_GEMM_FORM(launch_f32_ops, 0, 1, 0);
+    BPT_GEMM_FORM(launch_f32_ops, 1, 0, 0);
+  } else if constexpr (EPI == EPI_MUL) {
+    BPT_GEMM_FORM(launch_f32_ops, 0, 0, 0);
+  } else {
+    BPT_GEMM_FORM(launch_f32_ops, 1, 0, 0);
   }
-  if (k_form(a)) return hipErrorInvalidValue;
-  if (big >= 256) return launch_bf16<256, 256, EPI, CT, RT, false, false, kNWN>(a, s);
-  return launch_bf16<128, 128, EPI, CT, RT>(a, s);
+  return hipErrorInvalidValue;
 }
 
 bool gemm_takes_nper(Dt ab, int64_t nper) { return nper % (ab == F32 ? 64 : 128) == 0; }
 
-// Times in microseconds, measured on weight-gradient shapes: a 32-deep stage of a full
-// round of 256 x 256 tiles (one per CU) takes 0.75, of 128 x 128 tiles 0.37 with one
-// workgroup on a CU and 0.55 with two; the slices are written and read at about 4 TB/s.
-// fp32 products are small here: slices of at least 16 stages, as many as fill the chip once.
+// bf16: tile_us of the slices, and 4 TB/s to write and add them. fp32 products are small here:
+// slices of at least 16 stages, as many as fill the chip once.
 int gemm_ksplit(Dt ab, int64_t M, int64_t N, int64_t K, int cap) {
   int best = 1;
   if (ab == F32) {
@@ -1000,13 +1075,12 @@ int gemm_ksplit(Dt ab, int64_t M, int64_t N, int64_t K, int cap) {
     return best;
   }
   double tbest = 0;
+  const int64_t nk = (K + 31) / 32;
   for (int z = 1; z <= cap; ++z) {
-    const double stages = (double)((K + 31) / 32 + z - 1) / z;
+    const int64_t stages = (nk + z - 1) / z;
     if (z > 1 && stages < 8) break;
-    const double n256 = (double)(((M + 255) / 256) * ((N + 255) / 256)) * z;
-    const double n128 = (double)(((M + 127) / 128) * ((N + 127) / 128)) * z;
-    double t = n256 >= 256 ? std::ceil(n256 / 256) * (stages * 0.75 + 6)
-                           : n128 <= 256 ? stages * 0.37 + 4 : std::ceil(n128 / 512) * (stages * 0.55 + 6);
+    double t;
+    best_tile(M, N, z, (double)stages, 0, &t);
     if (z > 1) t += 3.0 + (2.0 * z + 1) * 4.0 * M * N / 4.0e6;
     if (z == 1 || t < tbest) {
       tbest = t;
@@ -1017,34 +1091,28 @@ int gemm_ksplit(Dt ab, int64_t M, int64_t N, int64_t K, int cap) {
 }
 
 hipError_t gemm(Dt ab, Epi epi, Dt ct, Dt rt, const GemmArgs& a, hipStream_t s) {
+  if (ab == F32) {
+    switch (epi) {
+      case EPI_STORE: return ct == F32 ? run_f32<EPI_STORE, float, float>(a, s) : hipErrorInvalidValue;
+      case EPI_GELU: return ct == F32 ? run_f32<EPI_GELU, float, float>(a, s) : hipErrorInvalidValue;
+      case EPI_RELU: return ct == F32 ? run_f32<EPI_RELU, float, float>(a, s) : hipErrorInvalidValue;
+      case EPI_XENT_T: return ct == F32 ? run_f32<EPI_XENT_T, float, float>(a, s) : hipErrorInvalidValue;
+      case EPI_MUL: return ct == F32 && rt == F32 ? run_f32<EPI_MUL, float, float>(a, s) : hipErrorInvalidValue;
+      case EPI_RESID:
+        if (rt != F32) return hipErrorInvalidValue;
+        return ct == F32 ? run_f32<EPI_RESID, float, float>(a, s) : run_f32<EPI_RESID, bf16, float>(a, s);
+    }
+    return hipErrorInvalidValue;
+  }
   switch (epi) {
-    case EPI_STORE:
-      return ct == F32 ? launch_typed<EPI_STORE, float, float>(ab, a, s)
-                       : launch_typed<EPI_STORE, bf16, float>(ab, a, s);
-    case EPI_GELU:
-      return ct == F32 ? launch_typed<EPI_GELU, float, float>(ab, a, s)
-                       : launch_typed<EPI_GELU, bf16, float>(ab, a, s);
-    case EPI_RELU:
-      return ct == F32 ? launch_typed<EPI_RELU, float, float>(ab, a, s)
-                       : launch_typed<EPI_RELU, bf16, float>(ab, a, s);
-    case EPI_XENT:
-      return ct == F32 ? launch_typed<EPI_XENT, float, float>(ab, a, s)
-                       : launch_typed<EPI_XENT, bf16, float>(ab, a, s);
-    case EPI_XENT_T:
-      return ct == F32 ? launch_typed<EPI_XENT_T, float, float>(ab, a, s)
-                       : launch_typed<EPI_XENT_T, bf16, float>(ab, a, s);
-    case EPI_MUL:
-      if (rt == F16)
-        return ct == F32 ? launch_typed<EPI_MUL, float, f16>(ab, a, s)
-                         : launch_typed<EPI_MUL, bf16, f16>(ab, a, s);
-      return ct == F32 ? launch_typed<EPI_MUL, float, float>(ab, a, s)
-                       : launch_typed<EPI_MUL, bf16, float>(ab, a, s);
+    case EPI_STORE: return ct == F32 ? run_bf16<EPI_STORE, float, float>(a, s) : run_bf16<EPI_STORE, bf16, float>(a, s);
+    case EPI_GELU: return ct == BF16 ? run_bf16<EPI_GELU, bf16, float>(a, s) : hipErrorInvalidValue;
+    case EPI_RELU: return ct == BF16 ? run_bf16<EPI_RELU, bf16, float>(a, s) : hipErrorInvalidValue;
+    case EPI_XENT_T: return ct == BF16 ? run_bf16<EPI_XENT_T, bf16, float>(a, s) : hipErrorInvalidValue;
+    case EPI_MUL: return ct == BF16 && rt == F16 ? run_bf16<EPI_MUL, bf16, f16>(a, s) : hipErrorInvalidValue;
     case EPI_RESID:
-      if (ct == F32)
-        return rt == F32 ? launch_typed<EPI_RESID, float, float>(ab, a, s)
-                         : launch_typed<EPI_RESID, float, bf16>(ab, a, s);
-      return rt == F32 ? launch_typed<EPI_RESID, bf16, float>(ab, a, s)
-                       : launch_typed<EPI_RESID, bf16, bf16>(ab, a, s);
+      if (ct == F32) return rt == F32 ? run_bf16<EPI_RESID, float, float>(a, s) : run_bf16<EPI_RESID, float, bf16>(a, s);
+      return rt == F32 ? run_bf16<EPI_RESID, bf16, float>(a, s) : hipErrorInvalidValue;
   }
   return hipErrorInvalidValue;
 }
