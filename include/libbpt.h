@@ -226,9 +226,11 @@ typedef struct {
 /* Host-only checks; D and ldw must be multiples of 64 (else BPT_ERR_UNSUPPORTED). */
 bpt_status bpt_xent_validate(const bpt_xent_config* cfg);
 
-/* Workspace of bpt_xent_fwd (backward = 0): block_rows * ldw fp32 logits + T floats;
- * of bpt_xent_bwd (backward = 1): ldw * block_rows (rounded up to 64) elements of
- * cfg->dtype (one block's logit gradient, vocabulary-major). Returns 0 for an invalid
+/* Workspace of bpt_xent_fwd (backward = 0): block_rows * ldw fp32 logits (dtype BF16: only
+ * their maximum and sum per 64 columns) + T floats; of bpt_xent_bwd (backward = 1): ldw *
+ * block_rows (rounded up to 64) elements of cfg->dtype (one block's logit gradient,
+ * vocabulary-major), and for a narrow D fp32 partial sums of dh, without which (a workspace
+ * of just the gradient block) dh is computed in one pass. Returns 0 for an invalid
  * configuration. Host-only. */
 size_t bpt_xent_workspace_bytes(const bpt_xent_config* cfg, int backward);
 

@@ -89,7 +89,7 @@ BPT_DEV void epi_store(const GemmArgs& a, int64_t z, int64_t m, int64_t n, float
     if (a.C2) c2_store(a, z * a.sC2 + m * a.ldc2 + n, gp);
   } else if constexpr (EPI == EPI_XENT_T) {
     C[idx] = from_f32<CT>(xent_grad_t(a, m, n, v));
-  } else {  // EPI_MUL
+  } else if constexpr (EPI == EPI_MUL) {
     const RT* R = (const RT*)a.R + z * a.sR;
     C[idx] = from_f32<CT>(v * to_f32<RT>(R[m * a.ldr + n]));
   }
@@ -154,7 +154,7 @@ BPT_DEV void epi_store4(const GemmArgs& a, int64_t z, int64_t m, int64_t n, int6
   } else if constexpr (EPI == EPI_XENT_T) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) v[e] = xent_grad_t(a, m, n + e, v[e]);
-  } else {
+  } else if constexpr (EPI == EPI_MUL) {
     v *= V4<RT>::ld((const RT*)a.R + z * a.sR + m * a.ldr + n);
   }
   V4<CT>::st(C, v);
@@ -188,7 +188,7 @@ BPT_DEV void epi_vec4(const GemmArgs& a, CT* c, const void* r, int64_t c2, const
       d[e] = gp;
     }
     if (a.C2) c2_store4(a, c2, d);
-  } else {
+  } else if constexpr (EPI == EPI_MUL) {
     v *= V4<RT>::ld((const RT*)r);
   }
   V4<CT>::st(c, v);
@@ -333,6 +333,24 @@ struct KSegs {
   }
   BPT_DEV int64_t limit(const GemmArgs& a) const { return k0 - shift + a.seg_rows; }   // past the last existing row
 };
+
+// v of lane l ^ 1, l ^ 2, then of the other quad and the other 8 lanes of 16: after the
+// steps before it a step's group holds one value, so mirrors serve as exchanges. No LDS.
+template <int CTRL> BPT_DEV float dpp16(float v) {
+  return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), CTRL, 0xF, 0xF, true));
+}
+BPT_DEV float max16(float v) {
+  v = fmaxf(v, dpp16<0xB1>(v));
+  v = fmaxf(v, dpp16<0x4E>(v));
+  v = fmaxf(v, dpp16<0x141>(v));
+  return fmaxf(v, dpp16<0x140>(v));
+}
+BPT_DEV float sum16(float v) {
+  v += dpp16<0xB1>(v);
+  v += dpp16<0x4E>(v);
+  v += dpp16<0x141>(v);
+  return v + dpp16<0x140>(v);
+}
 
 template <int BM, int BN, int EPI, typename CT, typename RT, bool TA = false, bool TB = false, int NWN = 2,
           int KF = 0, int KG = 1>
@@ -685,6 +703,40 @@ __global__ __launch_bounds__(128 * NWN * KG, 1) void gemm_bf16_kernel(GemmArgs a
         strip[(8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * PITCHF + 32 * j + (lane & 31)] = acc[i][j][r];
     const int64_t mrow = m0 + wm * Cfg::WM + 32 * i;
     const int64_t ncol = n0 + wn * Cfg::WN;
+    if constexpr (EPI == EPI_LSE) {
+      // 16 lanes per row of the strip, 4 columns each: maximum and sum over the wave's 64
+      // columns by exchanges inside the 16 lanes, so that the summary of 64 columns is the
+      // same in every tile form
+      static_assert(Cfg::WN == 64, "summaries of 64 columns");
+      const int c0 = 4 * (lane % C4);
+      const bool all = ncol + 64 <= a.nvalid;
+#pragma unroll 4
+      for (int it = 0; it < 32 / RSTEP; ++it) {
+        const int row = lane / C4 + RSTEP * it;
+        const int64_t m = mrow + row;
+        const f32x4 v = *(const f32x4*)(strip + row * PITCHF + c0);
+        float mx = -__builtin_inff(), sum = 0.0f;
+        if (all) {
+          mx = max16(fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])));
+#pragma unroll
+          for (int e = 0; e < 4; ++e) sum += __builtin_amdgcn_exp2f((v[e] - mx) * 1.4426950408889634f);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) mx = ncol + c0 + e < a.nvalid ? fmaxf(mx, v[e]) : mx;
+          mx = max16(mx);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            sum += ncol + c0 + e < a.nvalid ? __builtin_amdgcn_exp2f((v[e] - mx) * 1.4426950408889634f) : 0.0f;
+        }
+        sum = sum16(sum);
+        if (m < a.M && ncol < ncols) {
+          if (c0 == 0) *(u32x2*)((float*)a.C + 2 * (m * a.ldc + ncol / 64)) = u32x2{__float_as_uint(mx), __float_as_uint(sum)};
+          const int64_t y = (int64_t)a.tgt[m] - ncol - c0;
+          if (y >= 0 && y < 4 && ncol + c0 + y < a.nvalid) a.tlogit[m] = y == 0 ? v[0] : y == 1 ? v[1] : y == 2 ? v[2] : v[3];
+        }
+      }
+      continue;
+    }
     if (inside) {
       // rows are (lane / C4) + (64 / C4) * it; columns 4 * (lane % C4)
       const int r0 = lane / C4, c0 = 4 * (lane % C4);
@@ -941,12 +993,12 @@ static double tile_us(Tile t, int64_t n, double stages) {
 
 // The cheapest tile form for M x ncols over nz batch entries or K slices of `stages` stages.
 // Columns of three matrices (nper) keep a tile inside one of them.
-static Tile best_tile(int64_t M, int64_t ncols, int64_t nz, double stages, int64_t nper, double* us) {
+static Tile best_tile(int64_t M, int64_t ncols, int64_t nz, double stages, int64_t nper, int in_order, double* us) {
   Tile best = T128;
   double t = -1;
   for (Tile c : {T128, T256, T64, T64K4}) {
     const int64_t b = c == T256 ? 256 : c == T128 ? 128 : 64;
-    if (nper % b != 0) continue;
+    if (nper % b != 0 || (in_order && c == T64K4)) continue;
     const double u = tile_us(c, ((M + b - 1) / b) * ((ncols + b - 1) / b) * nz, stages);
     if (t < 0 || u < t) {
       t = u;
@@ -960,7 +1012,7 @@ static Tile best_tile(int64_t M, int64_t ncols, int64_t nz, double stages, int64
 static Tile pick_tile(const GemmArgs& a) {
   const int64_t ncols = a.Nstore > a.N ? a.Nstore : a.N, nk = (a.K + 31) / 32;
   const int64_t z = std::max(a.ksplit, 1);
-  return best_tile(a.M, ncols, a.batch * z, (double)((nk + z - 1) / z), a.nper, nullptr);
+  return best_tile(a.M, ncols, a.batch * z, (double)((nk + z - 1) / z), a.nper, a.in_order, nullptr);
 }
 
 template <int EPI, typename CT, typename RT, bool TA, bool TB, int KF = 0>
@@ -972,8 +1024,11 @@ static hipError_t launch_ops(const GemmArgs& a, hipStream_t s) {
   switch (pick_tile(a)) {
     case T256: return launch_bf16<256, 256, 4, 1, EPI, CT, RT, TA, TB, KF>(a, s);
     case T128: return launch_bf16<128, 128, 2, 1, EPI, CT, RT, TA, TB, KF>(a, s);
-    case T64: return launch_bf16<64, 64, 2, 1, EPI, CT, RT, TA, TB, KF>(a, s);
-    case T64K4: return launch_bf16<64, 64, 2, 4, EPI, CT, RT, TA, TB, KF>(a, s);
+    case T64:
+      if constexpr (EPI != EPI_LSE) return launch_bf16<64, 64, 2, 1, EPI, CT, RT, TA, TB, KF>(a, s);
+      else return launch_bf16<128, 128, 2, 1, EPI, CT, RT, TA, TB, KF>(a, s);   // waves of 64 columns
+    case T64K4:
+      if constexpr (EPI != EPI_LSE) return launch_bf16<64, 64, 2, 4, EPI, CT, RT, TA, TB, KF>(a, s);
   }
   return hipErrorInvalidValue;
 }
@@ -1013,8 +1068,8 @@ template <int EPI, typename CT, typename RT>
 static hipError_t run_bf16(const GemmArgs& a, hipStream_t s) {
   constexpr bool f32_out = std::is_same_v<CT, float>;
   if constexpr (EPI == EPI_STORE && f32_out) {
-    BPT_GEMM_FORM(launch_ops, 0, 1, 0);                // logits, dW2, Wo and W2 with dropout
-    BPT_GEMM_FORM(launch_ops, 1, 0, 0);                // dv, dW1, head dW; dWq, dWk, dWv one by one
+    BPT_GEMM_FORM(launch_ops, 0, 1, 0);                // dW2, Wo and W2 with dropout
+    BPT_GEMM_FORM(launch_ops, 1, 0, 0);                // dv, dW1, head dW and slices of dh; dWq, dWk, dWv one by one
     BPT_GEMM_FORM(launch_ops, 1, 0, KF_SEG);
     BPT_GEMM_FORM(launch_ops, 1, 0, KF_NPER);          // dWq, dWk, dWv at once
     BPT_GEMM_FORM(launch_ops, 1, 0, KF_SEG | KF_NPER);
@@ -1032,6 +1087,9 @@ static hipError_t run_bf16(const GemmArgs& a, hipStream_t s) {
     BPT_GEMM_FORM(launch_ops, 1, 0, 0);                // its recompute
   } else if constexpr (EPI == EPI_MUL) {
     BPT_GEMM_FORM(launch_ops, 0, 0, 0);                // dZ
+  } else if constexpr (EPI == EPI_LSE) {
+    if (!a.in_order) return hipErrorInvalidValue;
+    BPT_GEMM_FORM(launch_ops, 0, 1, 0);                // logits' row summaries
   } else {
     BPT_GEMM_FORM(launch_ops, 1, 0, 0);                // head gradient
   }
@@ -1080,7 +1138,7 @@ int gemm_ksplit(Dt ab, int64_t M, int64_t N, int64_t K, int cap) {
     const int64_t stages = (nk + z - 1) / z;
     if (z > 1 && stages < 8) break;
     double t;
-    best_tile(M, N, z, (double)stages, 0, &t);
+    best_tile(M, N, z, (double)stages, 0, 0, &t);
     if (z > 1) t += 3.0 + (2.0 * z + 1) * 4.0 * M * N / 4.0e6;
     if (z == 1 || t < tbest) {
       tbest = t;
@@ -1097,6 +1155,7 @@ hipError_t gemm(Dt ab, Epi epi, Dt ct, Dt rt, const GemmArgs& a, hipStream_t s) 
       case EPI_GELU: return ct == F32 ? run_f32<EPI_GELU, float, float>(a, s) : hipErrorInvalidValue;
       case EPI_RELU: return ct == F32 ? run_f32<EPI_RELU, float, float>(a, s) : hipErrorInvalidValue;
       case EPI_XENT_T: return ct == F32 ? run_f32<EPI_XENT_T, float, float>(a, s) : hipErrorInvalidValue;
+      case EPI_LSE: return hipErrorInvalidValue;
       case EPI_MUL: return ct == F32 && rt == F32 ? run_f32<EPI_MUL, float, float>(a, s) : hipErrorInvalidValue;
       case EPI_RESID:
         if (rt != F32) return hipErrorInvalidValue;
@@ -1108,6 +1167,7 @@ hipError_t gemm(Dt ab, Epi epi, Dt ct, Dt rt, const GemmArgs& a, hipStream_t s) 
     case EPI_STORE: return ct == F32 ? run_bf16<EPI_STORE, float, float>(a, s) : run_bf16<EPI_STORE, bf16, float>(a, s);
     case EPI_GELU: return ct == BF16 ? run_bf16<EPI_GELU, bf16, float>(a, s) : hipErrorInvalidValue;
     case EPI_RELU: return ct == BF16 ? run_bf16<EPI_RELU, bf16, float>(a, s) : hipErrorInvalidValue;
+    case EPI_LSE: return ct == F32 ? run_bf16<EPI_LSE, float, float>(a, s) : hipErrorInvalidValue;
     case EPI_XENT_T: return ct == BF16 ? run_bf16<EPI_XENT_T, bf16, float>(a, s) : hipErrorInvalidValue;
     case EPI_MUL: return ct == BF16 && rt == F16 ? run_bf16<EPI_MUL, bf16, f16>(a, s) : hipErrorInvalidValue;
     case EPI_RESID:

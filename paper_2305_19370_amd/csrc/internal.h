@@ -21,6 +21,9 @@ enum Epi {
   EPI_XENT_T = 6,  // cross-entropy gradient of transposed logits acc (rows m = vocabulary, columns
                    // n = tokens): for m < nvalid C = alpha (exp(acc - rowv[n]) - [m == tgt[n]]),
                    // rowv a token's log-sum-exp; C = 0 for nvalid <= m
+  EPI_LSE = 7,     // bf16 operands; row summaries of the logits acc instead of the logits: for
+                   // every 64 columns j, C[m, j] = (max, sum of exp(acc - max)) over columns
+                   // below nvalid, as two floats; tlogit[m] = acc[m, tgt[m]] for 0 <= tgt[m] < nvalid
 };
 
 struct GemmArgs {
@@ -41,7 +44,10 @@ struct GemmArgs {
                                // EPI_XENT_T: the gradient's scale
   const float* rowv = nullptr; // EPI_XENT_T: per-column log-sum-exp (natural log), [N]
   const int32_t* tgt = nullptr;// EPI_XENT_T: per-column target row, [N]
-  int64_t nvalid = 0;          // EPI_XENT_T: rows from nvalid on are not logits
+  int64_t nvalid = 0;          // EPI_XENT_T: rows from nvalid on are not logits; EPI_LSE: columns
+  float* tlogit = nullptr;     // EPI_LSE: the target's logit of each row (tgt per row there), [M]
+  int in_order = 0;            // every element adds its products in the order of k, so that it is
+                               // the same for any M and N (no tile form that shares K)
   int bias_on_m = 0;           // EPI_GELU / EPI_RELU: bias indexed by row instead of column
   // Transposed operands (which ones go with which epilogue: gemm.hip's lists): trans_a means A is stored K-major, element
   // (m, k) at A[k * lda + m]; likewise trans_b for B (element (n, k) at B[k * ldb + n]).
@@ -143,6 +149,10 @@ hipError_t attn_delta(Dt t, const void* dout, const void* o, int64_t ld, const f
 // the token loss lse[t] - z[t, tgt[t]] (NaN for a target outside [0, V)).
 hipError_t xent_rows(const float* z, int64_t ld, int64_t rows, int64_t V, const int32_t* tgt, float* lse,
                      float* tok, hipStream_t s);
+// The same from EPI_LSE's summaries part [rows, ng] (two floats each, merged in order) and the
+// targets' logits.
+hipError_t xent_merge(const float* part, int64_t ng, int64_t rows, int64_t V, const int32_t* tgt, const float* tlogit,
+                      float* lse, float* tok, hipStream_t s);
 // out[0] = mean of x[0..n), summed in a fixed order
 hipError_t mean_of(const float* x, int64_t n, float* out, hipStream_t s);
 // ---------------------------------------------------------------- GPT step pieces
@@ -164,6 +174,8 @@ hipError_t adamw(Dt tl, float* p, const float* g, float* m, float* v, void* pl, 
 // nper > 0 column c goes to outs[c / nper][m, c % nper], else all to outs[0] (cols, nper % 4 == 0)
 hipError_t sum_slices(const float* part, int nz, int64_t rows, int64_t cols, float* const outs[3], int64_t nper,
                       int accumulate, hipStream_t s);
+// out[i] = sum over z < nz of part[z n + i] in slice order, rounded once (n % 4 == 0)
+hipError_t sum_slices_bf16(const float* part, int nz, int64_t n, void* out, hipStream_t s);
 // ---------------------------------------------------------------- residual-branch dropout
 // Element (t, n) of branch `site` is kept iff word n % 4 of Philox4x32-10 at counter
 // (n / 4, t, site, 0), key (k0, k1), is >= threshold; kept values are multiplied by scale.

@@ -306,6 +306,7 @@ bpt_status xent_check(const bpt_xent_config* c) {
 struct XentDims {
   int64_t T, D, V, ldw, R, Rp;   // R: rows per block; Rp: R rounded up to 64
   size_t E;
+  int zdh;                       // slices of dh = G W^T along the vocabulary
 };
 
 XentDims xent_dims(const bpt_xent_config& c) {
@@ -314,13 +315,19 @@ XentDims xent_dims(const bpt_xent_config& c) {
   d.R = std::min(c.block_rows > 0 ? c.block_rows : kDefaultXentRows, c.T);
   d.Rp = rup(d.R, 64);
   d.E = esize(c.dtype);
+  // the vocabulary is a long K for a narrow dh; chosen for the default block so that dh does
+  // not depend on block_rows
+  d.zdh = d.E == 2 ? gemm_ksplit(BF16, std::min(d.T, kDefaultXentRows), d.D, d.ldw, kMaxKSplit) : 1;
   return d;
 }
 
 struct XentWs {
-  float* logits;   // forward: [R, ldw] fp32
+  float* logits;   // forward, fp32 path: [R, ldw] logits; bf16 path: their summaries per 64 columns
+  float* tlogit;   // forward, bf16 path: [R] the targets' logits
   float* tok;      // forward: [T] token losses
   void* g;         // backward: [ldw, Rp] in dtype, the logits' gradient of one block, transposed
+  float* part;     // backward, bf16 path: slices of dh along the vocabulary (zdh > 1)
+  int64_t least;   // backward: bytes without `part`, enough for dh in one slice
 };
 
 XentWs xent_ws(const XentDims& d, void* base, int backward, int64_t* total) {
@@ -328,8 +335,12 @@ XentWs xent_ws(const XentDims& d, void* base, int backward, int64_t* total) {
   XentWs w{};
   if (backward) {
     w.g = bp.take(d.Rp * d.ldw * (int64_t)d.E);
+    w.least = rup(bp.off, kAlign);
+    if (d.zdh > 1) w.part = (float*)bp.take(d.zdh * d.R * d.D * 4);
   } else {
-    w.logits = (float*)bp.take(d.R * d.ldw * 4);
+    const bool f32 = d.E == 4;
+    w.logits = (float*)bp.take(f32 ? d.R * d.ldw * 4 : d.R * (d.ldw / 64) * 8);
+    if (!f32) w.tlogit = (float*)bp.take(d.R * 4);
     w.tok = (float*)bp.take(d.T * 4);
   }
   *total = rup(bp.off, kAlign);
@@ -848,8 +859,17 @@ bpt_status bpt_xent_fwd(const bpt_xent_config* cfg, const void* h, const void* W
     const int64_t r = std::min(d.R, d.T - t0);
     GemmArgs g;   // logits of the block: h W, W read as it is stored (B operand K-major)
     g.A = (const char*)h + t0 * d.D * E_; g.lda = d.D;
-    g.B = W; g.ldb = d.ldw; g.trans_b = 1;
+    g.B = W; g.ldb = d.ldw; g.trans_b = 1; g.in_order = 1;
     g.C = w.logits; g.ldc = d.ldw; g.M = r; g.N = d.ldw; g.K = d.D;
+    if (E == BF16) {   // only their summaries are stored
+      const int64_t ng = d.ldw / 64;
+      g.ldc = ng; g.nvalid = d.V; g.tgt = targets + t0; g.tlogit = w.tlogit;
+      RUN("xent.logits", gemm_flops(g), ((double)r * d.D + (double)d.ldw * d.D) * E_ + (double)r * ng * 8,
+          gemm(E, EPI_LSE, F32, F32, g, s));
+      RUN("xent.rows", 0, (double)r * ng * 8,
+          xent_merge(w.logits, ng, r, d.V, targets + t0, w.tlogit, lse + t0, w.tok + t0, s));
+      continue;
+    }
     RUN("xent.logits", gemm_flops(g), gemm_bytes(g, E_, 4), gemm(E, EPI_STORE, F32, F32, g, s));
     RUN("xent.rows", 0, (double)r * d.ldw * 4,
         xent_rows(w.logits, d.ldw, r, d.V, targets + t0, lse + t0, w.tok + t0, s));
@@ -872,8 +892,9 @@ bpt_status bpt_xent_bwd(const bpt_xent_config* cfg, const void* h, const void* W
   const XentDims d = xent_dims(*cfg);
   int64_t need;
   XentWs w = xent_ws(d, ws, 1, &need);
-  if ((int64_t)ws_bytes < need)
-    return fail(BPT_ERR_WORKSPACE, "workspace %zu bytes < required %lld", ws_bytes, (long long)need);
+  if ((int64_t)ws_bytes < w.least)
+    return fail(BPT_ERR_WORKSPACE, "workspace %zu bytes < required %lld", ws_bytes, (long long)w.least);
+  const int zdh = (int64_t)ws_bytes < need ? 1 : d.zdh;
   hipStream_t s = (hipStream_t)stream;
   const Dt E = cfg->dtype == BPT_BF16 ? BF16 : F32;
   const int64_t E_ = (int64_t)d.E;
@@ -886,15 +907,22 @@ bpt_status bpt_xent_bwd(const bpt_xent_config* cfg, const void* h, const void* W
       GemmArgs g;
       g.A = W; g.lda = d.ldw; g.trans_a = 1; g.B = hb; g.ldb = d.D;
       g.C = w.g; g.ldc = d.Rp; g.M = d.ldw; g.N = r; g.Nstore = rp; g.K = d.D;
-      g.alpha = dloss / (float)d.T; g.rowv = lse + t0; g.tgt = targets + t0; g.nvalid = d.V;
+      g.in_order = 1; g.alpha = dloss / (float)d.T; g.rowv = lse + t0; g.tgt = targets + t0; g.nvalid = d.V;
       RUN("xent.grad_logits", gemm_flops(g), gemm_bytes(g, E_, E_), gemm(E, EPI_XENT_T, E, F32, g, s));
     }
     {   // dh = G W^T: G read from its transposed copy (K-major A), W rows contiguous along
         // the vocabulary
       GemmArgs g;
       g.A = w.g; g.lda = d.Rp; g.trans_a = 1; g.a_cols = d.Rp; g.B = W; g.ldb = d.ldw;
-      g.C = (char*)dh + t0 * d.D * E_; g.ldc = d.D; g.M = r; g.N = d.D; g.K = d.ldw;
-      RUN("xent.dh", gemm_flops(g), gemm_bytes(g, E_, E_), gemm(E, EPI_STORE, E, F32, g, s));
+      g.C = (char*)dh + t0 * d.D * E_; g.ldc = d.D; g.M = r; g.N = d.D; g.K = d.ldw; g.in_order = 1;
+      if (zdh > 1) {
+        void* out = g.C;
+        g.ksplit = zdh; g.C = w.part; g.sC = r * d.D;
+        RUN("xent.dh", gemm_flops(g), gemm_bytes(g, E_, 4), gemm(E, EPI_STORE, F32, F32, g, s));
+        RUN("reduce.ksplit", 0, (double)r * d.D * (4 * zdh + E_), sum_slices_bf16(w.part, zdh, r * d.D, out, s));
+      } else {
+        RUN("xent.dh", gemm_flops(g), gemm_bytes(g, E_, E_), gemm(E, EPI_STORE, E, F32, g, s));
+      }
     }
     if (dW) {   // dW = h^T G: h read token-major (K-major A), G^T rows contiguous along the
                 // tokens (zero past row r)

@@ -632,6 +632,30 @@ __global__ __launch_bounds__(256) void xent_rows_kernel(const float* z, int64_t 
   }
 }
 
+// One wave per row: lane i merges summaries i, i + 64, ..., the lanes' merge by exchanges.
+__global__ __launch_bounds__(256) void xent_merge_kernel(const float* part, int64_t ng, int64_t rows, int64_t V,
+                                                         const int32_t* tgt, const float* tlogit, float* lse, float* tok) {
+  const int lane = threadIdx.x & 63;
+  const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (t >= rows) return;
+  float m = -__builtin_inff(), l = 0.0f;
+  for (int64_t j = lane; j < ng; j += 64) {
+    const u32x2 q = *(const u32x2*)(part + 2 * (t * ng + j));
+    lse_merge(m, l, __uint_as_float(q[0]), __uint_as_float(q[1]));
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    const float m2 = __shfl_xor(m, o, 64), l2 = __shfl_xor(l, o, 64);
+    lse_merge(m, l, m2, l2);
+  }
+  if (lane == 0) {
+    const float r = m + __logf(l);
+    lse[t] = r;
+    const int y = tgt[t];
+    tok[t] = (y >= 0 && y < V) ? r - tlogit[t] : __builtin_nanf("");
+  }
+}
+
 // out[0] = (sum of x[0..n)) / n, summed in a fixed order by one workgroup.
 __global__ __launch_bounds__(1024) void mean_kernel(const float* x, int64_t n, float* out) {
   __shared__ float part[1024];
@@ -834,6 +858,14 @@ hipError_t xent_rows(const float* z, int64_t ld, int64_t rows, int64_t V, const 
   return hipGetLastError();
 }
 
+hipError_t xent_merge(const float* part, int64_t ng, int64_t rows, int64_t V, const int32_t* tgt, const float* tlogit,
+                      float* lse, float* tok, hipStream_t s) {
+  if (rows <= 0) return hipSuccess;
+  hipLaunchKernelGGL(xent_merge_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, part, ng, rows, V, tgt, tlogit,
+                     lse, tok);
+  return hipGetLastError();
+}
+
 hipError_t mean_of(const float* x, int64_t n, float* out, hipStream_t s) {
   if (n <= 0) return hipErrorInvalidValue;
   hipLaunchKernelGGL(mean_kernel, dim3(1), dim3(1024), 0, s, x, n, out);
@@ -864,6 +896,24 @@ __global__ __launch_bounds__(256) void sum_slices_kernel(const float* part, int 
   }
   for (; z < nz; ++z) acc += ((const f32x4*)(part + z * n))[q];
   ((f32x4*)out)[at] = acc;
+}
+
+__global__ __launch_bounds__(256) void sum_slices_bf16_kernel(const float* part, int nz, int64_t n, bf16* out) {
+  const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;      // group of four
+  if (4 * q >= n) return;
+  f32x4 acc = ((const f32x4*)part)[q];
+#pragma unroll 4
+  for (int z = 1; z < nz; ++z) acc += ((const f32x4*)(part + z * n))[q];
+  const float v[4] = {acc[0], acc[1], acc[2], acc[3]};
+  Vec4<bf16>::store(out + 4 * q, v);
+}
+
+hipError_t sum_slices_bf16(const float* part, int nz, int64_t n, void* out, hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  if (n % 4 != 0) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(sum_slices_bf16_kernel, dim3((unsigned)((n / 4 + 255) / 256)), dim3(256), 0, s, part, nz, n,
+                     (bf16*)out);
+  return hipGetLastError();
 }
 
 hipError_t sum_slices(const float* part, int nz, int64_t rows, int64_t cols, float* const outs[3], int64_t nper,

@@ -116,3 +116,33 @@ def test_some_gradients_only(dtype):
         assert torch.equal(dX, dX1) and set(some) == set(want)
         for n in want:                # float32 sums of the same terms in another order
             assert (some[n] - full[n]).abs().max() <= 1e-5 * full[n].abs().max(), n
+
+
+# head: summaries of 64 columns in tiles of 256 and 128 (few and many rows), a last group with one
+# column of the vocabulary, dh cut along the vocabulary (narrow D) with and without the room for it
+@pytest.mark.parametrize("T,D,V", [(1, 64, 1), (70, 128, 449), (300, 192, 12801), (2100, 128, 8000)])
+def test_head_edges(T, D, V):
+    from bpt_inputs import make_xent_inputs
+    say(f"case head T={T} D={D} V={V}")
+    cfg = bpt.make_xent_config(T, D, V)
+    inp = {k: v.cuda() for k, v in make_xent_inputs(T, D, V, cfg.ldw, seed=4).items()}
+    h, W, y = inp["h"], inp["W"], inp["targets"]
+    head = bpt.LMHeadLoss(cfg)
+    loss, lse = head.forward(h, W, y)
+    dh, dW = head.backward(h, W, y, lse, dloss=0.5)
+    z = h.double() @ W.double()[:, :V].contiguous()
+    ref = torch.logsumexp(z, 1)
+    assert (lse.double() - ref).abs().max() <= 1e-4 * ref.abs().max().clamp_min(1.0)
+    tok = ref - z.gather(1, y.long()[:, None])[:, 0]
+    assert (loss.double() - tok.mean()).abs().max() <= 1e-4 * ref.abs().max().clamp_min(1.0)
+    G = torch.softmax(z, 1)
+    G[torch.arange(T, device="cuda"), y.long()] -= 1.0
+    G = (G * (0.5 / T)).to(torch.bfloat16).double()        # the operand of both products
+    # exp in float32 may round an element of G to the neighbouring bf16 value: 2^-8 of it
+    for got, want, mag in ((dh, G @ W.double()[:, :V].t(), G.abs() @ W.double()[:, :V].abs().t()),
+                           (dW[:, :V], h.double().t().contiguous() @ G, h.double().abs().t().contiguous() @ G.abs())):
+        assert ((got.double() - want).abs() <= 2.0 ** -8 * mag + 2.0 ** -8 * want.abs() + 1e-12).all()
+    small = torch.empty(cfg.ldw * ((min(T, 8192) + 63) // 64 * 64) * 2, dtype=torch.uint8, device="cuda")
+    dh1 = torch.empty_like(dh)
+    bpt.xent_bwd(cfg, h, W, y, lse, 0.5, dh1, None, small)
+    assert ((dh1.double() - dh.double()).abs() <= 2.0 ** -7 * dh.double().abs() + 1e-4 * dh.double().abs().max()).all()
