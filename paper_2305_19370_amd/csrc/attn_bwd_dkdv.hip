@@ -7,7 +7,7 @@ namespace bpt {
 
 // ====================================================================== backward dK dV, bf16
 // Key-outer: 8 waves (two per SIMD, so one wave's VALU work overlaps the other's
-// MFMAs) of 32 keys each, 256 keys per workgroup, loop over query tiles of 64 (two
+// MFMAs) of 32 keys each, 256 keys per workgroup (or 4 waves, 128: few_blocks), loop over query tiles of 64 (two
 // halves of 32). S = Q K^T and dP = dO V^T have the key on the lane axis, so P and dS
 // feed dV^T += dO^T P and dK^T += Q^T dS directly as B operands; dO^T and Q^T
 // fragments come from the token-major tiles by transposing LDS reads. Q carries
@@ -16,21 +16,21 @@ namespace bpt {
 // comes out as ln(2) dS^T (Q log2(e)/sqrt(dh)).
 // Query tiles are visited from the last one down, so all workgroups of a head start
 // on the same tiles (and share them in L2); the diagonal tiles come last.
-template <int DH>
+template <int DH, int NWAVES>
 struct DkvCfg {
   static constexpr int KSTEPS = DH / 16, DT = DH / 32;
-  static constexpr int NW = 8;                      // waves per workgroup
+  static constexpr int NW = NWAVES;                 // waves per workgroup: 8, or 4 (few_blocks)
   static constexpr int KEYS = 32 * NW;              // keys per workgroup
   static constexpr int TB = RmTile<DH>::BYTES;
   static constexpr int STAGE = 2 * TB + 2 * 64 * 4; // Q, dO tiles; -lse (base 2), -Delta
-  static constexpr int NS = 4;                      // stages in the ring
+  static constexpr int NS = NW == 8 || DH == 64 ? 4 : 2;   // stages in the ring
   static constexpr int LDS = NS * STAGE;
   static constexpr int DPS = Ring2<DH, NW>::DPW + 2;  // copies per wave per stage
 };
 
-template <int DH>
-__global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_bf16_kernel(AttnArgs a) {
-  using C = DkvCfg<DH>;
+template <int DH, int NWAVES>
+__global__ __launch_bounds__(64 * NWAVES, NWAVES == 8 ? 1 : 2) void attn_bwd_dkdv_bf16_kernel(AttnArgs a) {
+  using C = DkvCfg<DH, NWAVES>;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -149,8 +149,8 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_bf16_kernel(AttnArgs a) 
   const int it_a = ragged ? 1 : 0;
   const int it_b = k0 + C::KEYS > S ? it_a : std::max(it_a, ntiles - n_diag);
   auto step = [&](int it) {
-    if (it + 2 < ntiles) wait_vmcnt<2 * C::DPS>();
-    else if (it + 1 < ntiles) wait_vmcnt<C::DPS>();
+    if (C::NS == 4 && it + 2 < ntiles) wait_vmcnt<2 * C::DPS>();
+    else if (C::NS == 4 && it + 1 < ntiles) wait_vmcnt<C::DPS>();
     else wait_vmcnt<0>();
     __syncthreads();                  // stage it visible; every wave is done with stage it-1
     if (it + C::NS - 1 < ntiles) issue(it + C::NS - 1);  // into the slot of stage it-1
@@ -247,15 +247,22 @@ __global__ __launch_bounds__(256) void attn_bwd_dkdv_f32_kernel(AttnArgs a) {
   }
 }
 
+template <int DH, int NW>
+static hipError_t dkdv_launch_bf16(const AttnArgs& a, hipStream_t s) {
+  using C = DkvCfg<DH, NW>;
+  auto k = attn_bwd_dkdv_bf16_kernel<DH, NW>;
+  hipError_t e = set_lds(k, C::LDS);
+  if (e != hipSuccess) return e;
+  const int64_t nblk = (a.S + C::KEYS - 1) / C::KEYS;
+  hipLaunchKernelGGL(k, dim3((unsigned)(nblk * a.H * a.B)), dim3(64 * NW), C::LDS, s, a);
+  return hipGetLastError();
+}
+
 template <int DH>
 static hipError_t dkdv_launch(Dt dt, const AttnArgs& a, hipStream_t s) {
   if (a.S <= 0 || a.B <= 0) return hipSuccess;
   if (dt == BF16) {
-    auto k = attn_bwd_dkdv_bf16_kernel<DH>;
-    hipError_t e = set_lds(k, DkvCfg<DH>::LDS);
-    if (e != hipSuccess) return e;
-    const int64_t nblk = (a.S + DkvCfg<DH>::KEYS - 1) / DkvCfg<DH>::KEYS;
-    hipLaunchKernelGGL(k, dim3((unsigned)(nblk * a.H * a.B)), dim3(64 * DkvCfg<DH>::NW), DkvCfg<DH>::LDS, s, a);
+    return few_blocks(a.S, (int64_t)a.H * a.B, a.causal) ? dkdv_launch_bf16<DH, 4>(a, s) : dkdv_launch_bf16<DH, 8>(a, s);
   } else {
     hipLaunchKernelGGL(attn_bwd_dkdv_f32_kernel<DH>, dim3((unsigned)(a.Sp / 16), a.H, a.B), dim3(256), 0, s, a);
   }

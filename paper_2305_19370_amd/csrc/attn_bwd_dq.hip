@@ -7,26 +7,26 @@ namespace bpt {
 
 // ====================================================================== backward dQ, bf16
 // Query-outer: 8 waves (two per SIMD, so one wave's VALU work overlaps the other's
-// MFMAs) of 32 queries each, 256 per workgroup, loop over key tiles of 64:
+// MFMAs) of 32 queries each, 256 per workgroup (or 4 waves, 128: few_blocks), loop over key tiles of 64:
 // S^T = K Q^T, dP^T = V dO^T, dS^T = P^T (dP^T - Delta), dQ^T += K^T dS^T. K^T
 // fragments come from the K tile by transposing LDS reads. Q carries log2(e)/sqrt(dh),
 // and the score MFMAs start from minus the base-2 log-sum-exp of the lane's query, so
 // exp2 of the accumulator is P.
-template <int DH>
+template <int DH, int NWAVES>
 struct DqCfg {
   static constexpr int KSTEPS = DH / 16, DT = DH / 32;
-  static constexpr int NW = 8;                      // waves per workgroup
+  static constexpr int NW = NWAVES;                 // waves per workgroup: 8, or 4 (few_blocks)
   static constexpr int QROWS = 32 * NW;             // queries per workgroup
   static constexpr int TB = RmTile<DH>::BYTES;
   static constexpr int STAGE = 2 * TB;              // K and V tiles of 64 keys
-  static constexpr int NS = 4;                      // stages in the ring
+  static constexpr int NS = NW == 8 || DH == 64 ? 4 : 2;   // stages in the ring
   static constexpr int LDS = NS * STAGE;
   static constexpr int DPS = Ring2<DH, NW>::DPW;    // copies per wave per stage
 };
 
-template <int DH>
-__global__ __launch_bounds__(512, 1) void attn_bwd_dq_bf16_kernel(AttnArgs a) {
-  using C = DqCfg<DH>;
+template <int DH, int NWAVES>
+__global__ __launch_bounds__(64 * NWAVES, NWAVES == 8 ? 1 : 2) void attn_bwd_dq_bf16_kernel(AttnArgs a) {
+  using C = DqCfg<DH, NWAVES>;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -124,8 +124,8 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dq_bf16_kernel(AttnArgs a) {
     if (st < ntiles) issue(st);
   auto step = [&](int j) {
     // stage j has landed once at most the stages issued after it are pending
-    if (j + 2 < ntiles) wait_vmcnt<2 * C::DPS>();
-    else if (j + 1 < ntiles) wait_vmcnt<C::DPS>();
+    if (C::NS == 4 && j + 2 < ntiles) wait_vmcnt<2 * C::DPS>();
+    else if (C::NS == 4 && j + 1 < ntiles) wait_vmcnt<C::DPS>();
     else wait_vmcnt<0>();
     __syncthreads();                  // stage j visible; every wave is done with stage j-1
     if (j + C::NS - 1 < ntiles) issue(j + C::NS - 1);   // into the slot of stage j-1
@@ -200,15 +200,22 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_f32_kernel(AttnArgs a) {
   }
 }
 
+template <int DH, int NW>
+static hipError_t dq_launch_bf16(const AttnArgs& a, hipStream_t s) {
+  using C = DqCfg<DH, NW>;
+  auto k = attn_bwd_dq_bf16_kernel<DH, NW>;
+  hipError_t e = set_lds(k, C::LDS);
+  if (e != hipSuccess) return e;
+  const int64_t nblk = (a.S + C::QROWS - 1) / C::QROWS;
+  hipLaunchKernelGGL(k, dim3((unsigned)(nblk * a.H * a.B)), dim3(64 * NW), C::LDS, s, a);
+  return hipGetLastError();
+}
+
 template <int DH>
 static hipError_t dq_launch(Dt dt, const AttnArgs& a, hipStream_t s) {
   if (a.S <= 0 || a.B <= 0) return hipSuccess;
   if (dt == BF16) {
-    auto k = attn_bwd_dq_bf16_kernel<DH>;
-    hipError_t e = set_lds(k, DqCfg<DH>::LDS);
-    if (e != hipSuccess) return e;
-    const int64_t nblk = (a.S + DqCfg<DH>::QROWS - 1) / DqCfg<DH>::QROWS;
-    hipLaunchKernelGGL(k, dim3((unsigned)(nblk * a.H * a.B)), dim3(64 * DqCfg<DH>::NW), DqCfg<DH>::LDS, s, a);
+    return few_blocks(a.S, (int64_t)a.H * a.B, a.causal) ? dq_launch_bf16<DH, 4>(a, s) : dq_launch_bf16<DH, 8>(a, s);
   } else {
     hipLaunchKernelGGL(attn_bwd_dq_f32_kernel<DH>, dim3((unsigned)(a.Sp / 16), a.H, a.B), dim3(256), 0, s, a);
   }

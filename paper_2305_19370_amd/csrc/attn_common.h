@@ -49,6 +49,13 @@ BPT_DEV void dma16s(const void* sbase, uint32_t voff, char* lds_block) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                :: "v"(voff), "s"(sbase), "s"(lds_addr(lds_block)) : "memory");
 }
+// A wave-uniform address in scalar registers, also where the compiler has run out of them and
+// keeps it in a vector register
+BPT_DEV const void* scalar_ptr(const void* p) {
+  const uint64_t u = (uint64_t)(uintptr_t)p;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u), hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
+  return (const void*)(uintptr_t)((uint64_t)hi << 32 | lo);
+}
 BPT_DEV void dma4s(const void* sbase, uint32_t voff, char* lds_block) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1"
                :: "v"(voff), "s"(sbase), "s"(lds_addr(lds_block)) : "memory");
@@ -62,7 +69,7 @@ BPT_DEV float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }   // v_ex
 // wave issues the same number DPW (surplus slots repeat the last block, which writes
 // identical bytes), so a count of outstanding copies is the same on every wave. Pad
 // slots re-fetch a data chunk of the same row and are never read.
-template <int DH, int NW = 4>
+template <int DH, int NW>
 struct Ring2 {
   static constexpr int BL = RmTile<DH>::BLOCKS, NB = 2 * BL, DPW = (NB + NW - 1) / NW;
 };
@@ -76,7 +83,7 @@ BPT_DEV int ring_block(int wave, int i) {
 // Issue this wave's copies of one stage: rows row0 .. row0+63 of src0 into the first
 // tile, rows row1 .. row1+63 of src1 into the second. Rows past last_row are clamped
 // to it (the kernels mask them); row0, row1 <= last_row.
-template <int DH, int NW = 4>
+template <int DH, int NW>
 BPT_DEV void ring_issue(char* stage, const bf16* src0, int ld0, int row0, const bf16* src1, int ld1, int row1,
                         int last_row, int wave, int lane) {
   using T = RmTile<DH>;
@@ -94,7 +101,8 @@ BPT_DEV void ring_issue(char* stage, const bf16* src0, int ld0, int row0, const 
     int row = slot / T::SLOTS;
     row = row < lim ? row : lim;
     const uint32_t off = 2u * (uint32_t)(row * (t ? ld1 : ld0) + (col < DH / 8 ? col : 0) * 8);
-    dma16s(t ? org1 : org0, off, stage + t * T::BYTES + blk * 1024);
+    const void* org = t ? org1 : org0;
+    dma16s(NW == 4 ? scalar_ptr(org) : org, off, stage + t * T::BYTES + blk * 1024);
   }
 }
 
@@ -129,7 +137,8 @@ BPT_DEV void ring_issue_full(char* stage, const bf16* src0, int ld0, int row0, c
 #pragma unroll
   for (int i = 0; i < Ring2<DH, NW>::DPW; ++i) {
     const int b = ring_block<DH, NW>(wave, i), t = b >= T::BLOCKS, blk = b - t * T::BLOCKS;
-    dma16s(t ? org1 : org0, r.o[i], stage + t * T::BYTES + blk * 1024);
+    const void* org = t ? org1 : org0;
+    dma16s(NW == 4 ? scalar_ptr(org) : org, r.o[i], stage + t * T::BYTES + blk * 1024);
   }
 }
 
@@ -286,6 +295,17 @@ BPT_DEV void xcd_map_heads(int id, int NH, int nblk, int& hh, int& blk) {
   const int r = k - turn * hp * CHUNK;
   hh = x + 8 * (r / c);
   blk = turn * CHUNK + r % c;
+}
+
+// Whether `rows` rows of each of `heads` heads make too few blocks of 256 rows for one per CU,
+// so that the bf16 kernels run blocks of 128 (4 waves, two workgroups on a CU): with the causal
+// mask they even out blocks of unequal work (forward / dK dV / dQ of 4 x 1000 tokens, 12 heads
+// of 64: 24 / 41 / 33 -> 20 / 37 / 30 us; one of 4096 tokens, 16 heads of 128: 106 / 224 / 149
+// -> 102 / 201 / 128 us; with 512 blocks of 256 they lose up to 15 %). Without it all blocks
+// are alike and sharing tiles among 8 waves wins earlier (256 blocks: 127 -> 146 us forward).
+// The results are the same bit for bit.
+static inline bool few_blocks(int64_t rows, int64_t heads, int causal) {
+  return (rows + 255) / 256 * heads <= (causal ? 256 : 128);
 }
 
 template <typename K>

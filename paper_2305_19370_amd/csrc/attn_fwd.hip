@@ -28,16 +28,16 @@
 namespace bpt {
 
 // ====================================================================== forward, bf16
-// 8 waves (two per SIMD, so that one wave's softmax overlaps the other's MFMAs), 32
-// queries per wave, 256 per workgroup; all waves share the K/V stages of the ring.
-template <int DH>
+// 8 waves (two per SIMD, so that one wave's softmax overlaps the other's MFMAs), or two
+// workgroups of 4 on a CU; 32 queries per wave, 256 (128) per workgroup; all waves share the K/V stages of the ring.
+template <int DH, int NWAVES>
 struct FwdCfg {
   static constexpr int KSTEPS = DH / 16, DT = DH / 32;
-  static constexpr int NW = 8;                      // waves per workgroup
+  static constexpr int NW = NWAVES;                 // waves per workgroup: 8, or 4 (few_blocks)
   static constexpr int QROWS = 32 * NW;             // queries per workgroup
   static constexpr int TB = RmTile<DH>::BYTES;
   static constexpr int STAGE = 2 * TB;              // K and V tiles of 64 keys
-  static constexpr int NS = 4;                      // stages in the ring
+  static constexpr int NS = NW == 8 || DH == 64 ? 4 : 2;   // stages in the ring
   static constexpr int LDS = NS * STAGE;
   static constexpr int DPS = Ring2<DH, NW>::DPW;    // copies per wave per stage
 };
@@ -50,9 +50,9 @@ static constexpr float RESCALE_LOG2 = 8.0f;
 // the tile's maximum.
 static constexpr float SUM_MAX = 65536.0f;
 
-template <int DH>
-__global__ __launch_bounds__(512, 1) void attn_fwd_bf16_kernel(AttnArgs a) {
-  using C = FwdCfg<DH>;
+template <int DH, int NWAVES>
+__global__ __launch_bounds__(64 * NWAVES, NWAVES == 8 ? 1 : 2) void attn_fwd_bf16_kernel(AttnArgs a) {
+  using C = FwdCfg<DH, NWAVES>;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -208,8 +208,8 @@ __global__ __launch_bounds__(512, 1) void attn_fwd_bf16_kernel(AttnArgs a) {
     if (st < ntiles) issue(st);
   auto step = [&](int j) {
     // stage j has landed once at most the stages issued after it are pending
-    if (j + 2 < ntiles) wait_vmcnt<2 * C::DPS>();
-    else if (j + 1 < ntiles) wait_vmcnt<C::DPS>();
+    if (C::NS == 4 && j + 2 < ntiles) wait_vmcnt<2 * C::DPS>();
+    else if (C::NS == 4 && j + 1 < ntiles) wait_vmcnt<C::DPS>();
     else wait_vmcnt<0>();
     __syncthreads();                  // stage j visible; every wave is done with stage j-1
     if (j + C::NS - 1 < ntiles) issue(j + C::NS - 1);   // into the slot of stage j-1
@@ -354,16 +354,23 @@ __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(AttnArgs a) {
   }
 }
 
+template <int DH, int NW>
+static hipError_t fwd_launch_bf16(const AttnArgs& a, int64_t nq, hipStream_t s) {
+  using C = FwdCfg<DH, NW>;
+  auto kern = attn_fwd_bf16_kernel<DH, NW>;
+  hipError_t e = set_lds(kern, C::LDS);
+  if (e != hipSuccess) return e;
+  const int64_t nblk = (nq + C::QROWS - 1) / C::QROWS;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(nblk * a.H * a.nb)), dim3(64 * NW), C::LDS, s, a);
+  return hipGetLastError();
+}
+
 template <int DH>
 static hipError_t fwd_launch(Dt dt, const AttnArgs& a, hipStream_t s) {
   const int64_t nq = a.q_end - a.q_begin;
   if (nq <= 0 || a.nb <= 0) return hipSuccess;
   if (dt == BF16) {
-    auto kern = attn_fwd_bf16_kernel<DH>;
-    hipError_t e = set_lds(kern, FwdCfg<DH>::LDS);
-    if (e != hipSuccess) return e;
-    const int64_t nblk = (nq + FwdCfg<DH>::QROWS - 1) / FwdCfg<DH>::QROWS;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(nblk * a.H * a.nb)), dim3(64 * FwdCfg<DH>::NW), FwdCfg<DH>::LDS, s, a);
+    return few_blocks(nq, (int64_t)a.H * a.nb, a.causal) ? fwd_launch_bf16<DH, 4>(a, nq, s) : fwd_launch_bf16<DH, 8>(a, nq, s);
   } else {
     hipLaunchKernelGGL(attn_fwd_f32_kernel<DH>, dim3((unsigned)((nq + 15) / 16), a.H, a.nb),
                        dim3(256), 0, s, a);

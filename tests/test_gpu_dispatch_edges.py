@@ -146,3 +146,16 @@ def test_head_edges(T, D, V):
     dh1 = torch.empty_like(dh)
     bpt.xent_bwd(cfg, h, W, y, lse, 0.5, dh1, None, small)
     assert ((dh1.double() - dh.double()).abs() <= 2.0 ** -7 * dh.double().abs() + 1e-4 * dh.double().abs().max()).all()
+
+
+# bf16 attention blocks of 128 rows (few blocks) and of 256 (many): edges of both, ragged last
+# block and tile, heads of 64 and 128
+@pytest.mark.parametrize("B,S,D,H,causal", [(1, 127, 256, 2, True), (1, 129, 128, 2, True), (2, 385, 256, 2, False),
+                                            (1, 64, 128, 1, False), (20, 193, 896, 14, True), (11, 320, 768, 6, False)])
+def test_bf16_attention_blocks(B, S, D, H, causal):
+    w = small_workload("bf16", B=B, S=S, D=D, H=H, F=128, causal=causal, Bq=64, Bkv=64)
+    inp = make_inputs(w, seed=13)
+    say(f"case {w.name}")
+    gpu = run_gpu(w, inp, qkv_grads=True)
+    Yr, _, g = run_oracle(w, inp)
+    compare_all(w, inp, gpu, Yr, g, "bf16", w.name)
