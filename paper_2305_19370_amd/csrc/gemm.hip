@@ -808,7 +808,8 @@ __global__ __launch_bounds__(128 * NWN * KG, 1) void gemm_bf16_kernel(GemmArgs a
 // to the MFMA swapped, so that a lane ends up with 4 consecutive columns of one row.
 //
 // Bound by the matrix cores' fp32 rate where the grid fills the chip, by the latency of a
-// stage elsewhere; hence three tile sizes (launch_f32).
+// stage elsewhere; hence three tile sizes, and KG groups of 4 waves that share the K of a
+// tile, each with its own ring (f32_tile).
 template <int BM, int BN>
 struct F32Cfg {
   static constexpr int BK = 16, NW = 4, NS = 4;
@@ -820,12 +821,13 @@ struct F32Cfg {
   static_assert(NBLK % NW == 0, "every wave issues the same number of copies");
 };
 
-template <int BM, int BN, int EPI, typename CT, typename RT, bool TA, bool TB, int KF>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a) {
+template <int BM, int BN, int KG, int EPI, typename CT, typename RT, bool TA, bool TB, int KF>
+__global__ __launch_bounds__(256 * KG) void gemm_f32_kernel(GemmArgs a) {
   using C = F32Cfg<BM, BN>;
-  __shared__ __attribute__((aligned(1024))) char smem[C::LDS];
+  __shared__ __attribute__((aligned(1024))) char smem_all[KG * C::LDS];
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave_all = __builtin_amdgcn_readfirstlane(tid >> 6), wave = wave_all % C::NW, kg = wave_all / C::NW;
+  char* smem = smem_all + kg * C::LDS;
   const int wm = wave >> 1, wn = wave & 1, g = lane >> 4, c16 = lane & 15;
   const int tiles_m = (int)((a.M + BM - 1) / BM);
   const int64_t ncols = a.Nstore > a.N ? a.Nstore : a.N;
@@ -834,6 +836,12 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a) {
   const float* B = (const float*)a.B + z * a.sB + (TB ? n0 : n0 * a.ldb);
   int kb, nk;                                          // first stage and number of stages
   k_range<C::BK, EPI, CT>(a, z, kb, nk);
+  int nit = nk;                                        // stages of the longest group
+  if constexpr (KG > 1) {
+    nit = (nk + KG - 1) / KG;
+    kb += kg * nit;
+    nk = nk - kg * nit < nit ? (nk - kg * nit > 0 ? nk - kg * nit : 0) : nit;
+  }
   if constexpr (KF & KF_NPER) tile_of_three<TB, float, CT>(a, n0, B);
   if constexpr (KF & KF_KPER) B = b_of_k<float>(a, n0, (int64_t)kb * C::BK);
   const int64_t arows = a.a_rows > 0 ? a.a_rows : a.K, brows = a.b_rows > 0 ? a.b_rows : a.K;
@@ -926,6 +934,25 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a) {
 #pragma unroll
         for (int j = 0; j < C::TN; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[j][k], fa[i][k], acc[i][j], 0, 0, 0);
+  }
+  if constexpr (KG > 1) {                              // group 0 adds the others' parts, in order
+    for (int kt = nk; kt < nit; ++kt) __syncthreads();
+    __syncthreads();
+    if (kg > 0) {
+#pragma unroll
+      for (int i = 0; i < C::TM; ++i)
+#pragma unroll
+        for (int j = 0; j < C::TN; ++j) *(f32x4*)(smem + (((wave * C::TM + i) * C::TN + j) * 64 + lane) * 16) = acc[i][j];
+    }
+    __syncthreads();
+    if (kg > 0) return;                                // no barrier follows
+#pragma unroll
+    for (int k = 1; k < KG; ++k)
+#pragma unroll
+      for (int i = 0; i < C::TM; ++i)
+#pragma unroll
+        for (int j = 0; j < C::TN; ++j)
+          acc[i][j] += *(const f32x4*)(smem + k * C::LDS + (((wave * C::TM + i) * C::TN + j) * 64 + lane) * 16);
   }
 #pragma unroll
   for (int i = 0; i < C::TM; ++i)
@@ -1033,30 +1060,68 @@ static hipError_t launch_ops(const GemmArgs& a, hipStream_t s) {
   return hipErrorInvalidValue;
 }
 
-template <int BX, int EPI, typename CT, typename RT, bool TA, bool TB, int KF>
+template <int BX, int KG, int EPI, typename CT, typename RT, bool TA, bool TB, int KF>
 static hipError_t launch_f32_tile(const GemmArgs& a, hipStream_t s) {
   const int64_t ncols = a.Nstore > a.N ? a.Nstore : a.N;
   const int64_t tiles = ((a.M + BX - 1) / BX) * ((ncols + BX - 1) / BX);
   if (tiles <= 0 || a.batch <= 0) return hipSuccess;
-  hipLaunchKernelGGL((gemm_f32_kernel<BX, BX, EPI, CT, RT, TA, TB, KF>),
-                     dim3((unsigned)tiles, 1, (unsigned)(a.ksplit > 1 ? a.ksplit : a.batch)), dim3(256), 0, s, a);
+  hipLaunchKernelGGL((gemm_f32_kernel<BX, BX, KG, EPI, CT, RT, TA, TB, KF>),
+                     dim3((unsigned)tiles, 1, (unsigned)(a.ksplit > 1 ? a.ksplit : a.batch)), dim3(256 * KG), 0, s, a);
   return hipGetLastError();
 }
 
-// Square tiles of 128, 64 or 32: the largest that still gives every CU a workgroup (below
-// that the time of a stage is its latency, not its MFMAs, and smaller tiles have more of
-// them in flight).
+// The fp32 tile forms: squares of 128, 64 and 32, and 32 with four groups sharing K.
+enum F32Tile { F128, F64, F32T, F32K4 };
+
+// Estimated microseconds of n tiles of `stages` k stages of 16, as tile_us, from 21 shapes of
+// 64..2000 rows and K = 256..4096: w workgroups per CU take their share of the matrix cores
+// (0.98, 0.24, 0.06 per stage at the full rate) or, alone, the latency of a stage.
+static double f32_us(F32Tile t, int64_t n, double stages) {
+  const double w = (double)n / 256;
+  switch (t) {
+    case F128: return std::ceil(w) * 1.07 * stages + 6;
+    case F64: return std::max(0.40, 0.355 * std::ceil(w)) * stages + 3.3;
+    case F32T: return (w <= 1 ? 0.216 : 0.1 + 0.108 * w) * stages + 2.5;
+    case F32K4: return std::ceil(stages / 4) * std::max(0.48, 0.5 * w) + 3.5;
+  }
+  return 0;
+}
+
+static F32Tile best_f32_tile(int64_t M, int64_t ncols, int64_t nz, double stages, int64_t nper, int in_order, double* us) {
+  F32Tile best = F32T;
+  double t = -1;
+  for (F32Tile c : {F64, F128, F32T, F32K4}) {
+    const int64_t b = c == F128 ? 128 : c == F64 ? 64 : 32;
+    if (nper % b != 0 || (in_order && c == F32K4)) continue;
+    const double u = f32_us(c, ((M + b - 1) / b) * ((ncols + b - 1) / b) * nz, stages);
+    if (t < 0 || u < t) {
+      t = u;
+      best = c;
+    }
+  }
+  if (us) *us = t;
+  return best;
+}
+
+static F32Tile f32_tile(const GemmArgs& a) {
+  const int64_t ncols = a.Nstore > a.N ? a.Nstore : a.N, nk = (a.K + 15) / 16;
+  const int64_t z = std::max(a.ksplit, 1);
+  return best_f32_tile(a.M, ncols, a.batch * z, (double)((nk + z - 1) / z), a.nper, a.in_order, nullptr);
+}
+
 template <int EPI, typename CT, typename RT, bool TA, bool TB, int KF = 0>
 static hipError_t launch_f32_ops(const GemmArgs& a, hipStream_t s) {
   // 16-byte copies along the operands' contiguous extent, 16-byte stores of 4 columns
   if ((a.K % 16 && !(TA && TB)) || a.lda % 4 || a.ldb % 4 || a.ldc % 4 ||
       (TA && (a.a_cols > 0 ? a.a_cols : a.M) % 4) || (TB && (a.b_cols > 0 ? a.b_cols : a.N) % 4))
     return hipErrorInvalidValue;
-  const int64_t ncols = a.Nstore > a.N ? a.Nstore : a.N;
-  auto tiles = [&](int64_t b) { return ((a.M + b - 1) / b) * ((ncols + b - 1) / b) * a.batch * a.ksplit; };
-  if (a.nper % 128 == 0 && tiles(128) >= 256) return launch_f32_tile<128, EPI, CT, RT, TA, TB, KF>(a, s);
-  if (tiles(64) >= 256) return launch_f32_tile<64, EPI, CT, RT, TA, TB, KF>(a, s);
-  return launch_f32_tile<32, EPI, CT, RT, TA, TB, KF>(a, s);
+  switch (f32_tile(a)) {
+    case F128: return launch_f32_tile<128, 1, EPI, CT, RT, TA, TB, KF>(a, s);
+    case F64: return launch_f32_tile<64, 1, EPI, CT, RT, TA, TB, KF>(a, s);
+    case F32T: return launch_f32_tile<32, 1, EPI, CT, RT, TA, TB, KF>(a, s);
+    case F32K4: return launch_f32_tile<32, 4, EPI, CT, RT, TA, TB, KF>(a, s);
+  }
+  return hipErrorInvalidValue;
 }
 
 // Forms of one element type and epilogue, by which operands are K-major: those listed, and
@@ -1123,22 +1188,17 @@ static hipError_t run_f32(const GemmArgs& a, hipStream_t s) {
 
 bool gemm_takes_nper(Dt ab, int64_t nper) { return nper % (ab == F32 ? 64 : 128) == 0; }
 
-// bf16: tile_us of the slices, and 4 TB/s to write and add them. fp32 products are small here:
-// slices of at least 16 stages, as many as fill the chip once.
+// The estimate of the tiles, and 4 TB/s to write and add the slices.
 int gemm_ksplit(Dt ab, int64_t M, int64_t N, int64_t K, int cap) {
   int best = 1;
-  if (ab == F32) {
-    const int64_t t = ((M + 31) / 32) * ((N + 31) / 32);
-    while (best * 2 <= cap && t * best * 2 <= 256 && K / (16 * best * 2) >= 16) best *= 2;
-    return best;
-  }
   double tbest = 0;
-  const int64_t nk = (K + 31) / 32;
+  const int64_t bk = ab == F32 ? 16 : 32, nk = (K + bk - 1) / bk;
   for (int z = 1; z <= cap; ++z) {
     const int64_t stages = (nk + z - 1) / z;
     if (z > 1 && stages < 8) break;
     double t;
-    best_tile(M, N, z, (double)stages, 0, 0, &t);
+    if (ab == F32) best_f32_tile(M, N, z, (double)stages, 0, 0, &t);
+    else best_tile(M, N, z, (double)stages, 0, 0, &t);
     if (z > 1) t += 3.0 + (2.0 * z + 1) * 4.0 * M * N / 4.0e6;
     if (z == 1 || t < tbest) {
       tbest = t;

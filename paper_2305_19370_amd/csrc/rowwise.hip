@@ -64,7 +64,7 @@ __global__ __launch_bounds__(256) void ln_fwd_reg_kernel(const TI* x, int64_t ld
                                                          const float* bb, TO* out, int64_t ldo, float* mu,
                                                          float* rstd, int64_t rows, int D, float eps, int use_stats) {
   const int lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int64_t row = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (row >= rows) return;
   const TI* xr = x + row * ldx;
   float v[NC][8];
@@ -195,7 +195,7 @@ __global__ __launch_bounds__(256) void ln_bwd_reg_kernel(const TI* x, const floa
                                                          RowMap map) {
   static_assert(WPR == 1 || WPR == 4, "waves per row");
   static_assert(WPR == 4 || !PARAM || NC <= 4, "LDS of the block sums");
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // row in scalar registers
   const int col0 = 8 * (lane + (WPR == 4 ? 64 * NC * wave : 0));
   __shared__ float red[2][4][2];
   __shared__ __attribute__((aligned(16))) float sums[PARAM && WPR == 1 ? 2 * 512 * NC : 1];
