@@ -1133,7 +1133,8 @@ template <int EPI, typename CT, typename RT>
 static hipError_t run_bf16(const GemmArgs& a, hipStream_t s) {
   constexpr bool f32_out = std::is_same_v<CT, float>;
   if constexpr (EPI == EPI_STORE && f32_out) {
-    BPT_GEMM_FORM(launch_ops, 0, 1, 0);                // dW2, Wo and W2 with dropout
+    BPT_GEMM_FORM(launch_ops, 0, 0, 0);                // slices of dO
+    BPT_GEMM_FORM(launch_ops, 0, 1, 0);                // dW2; Wo and W2 with dropout or in slices
     BPT_GEMM_FORM(launch_ops, 1, 0, 0);                // dv, dW1, head dW and slices of dh; dWq, dWk, dWv one by one
     BPT_GEMM_FORM(launch_ops, 1, 0, KF_SEG);
     BPT_GEMM_FORM(launch_ops, 1, 0, KF_NPER);          // dWq, dWk, dWv at once

@@ -174,8 +174,10 @@ hipError_t adamw(Dt tl, float* p, const float* g, float* m, float* v, void* pl, 
 // nper > 0 column c goes to outs[c / nper][m, c % nper], else all to outs[0] (cols, nper % 4 == 0)
 hipError_t sum_slices(const float* part, int nz, int64_t rows, int64_t cols, float* const outs[3], int64_t nper,
                       int accumulate, hipStream_t s);
-// out[i] = sum over z < nz of part[z n + i] in slice order, rounded once (n % 4 == 0)
-hipError_t sum_slices_bf16(const float* part, int nz, int64_t n, void* out, hipStream_t s);
+// out[m, c] = R[m, c] + bias[c] + sum over z < nz of part[z, m, c] in slice order, rounded once to
+// `to` (R of type tr or null, bias fp32 or null; rows x cols, cols % 4 == 0)
+hipError_t sum_slices_add(const float* part, int nz, int64_t rows, int64_t cols, Dt tr, const void* R, const float* bias,
+                          Dt to, void* out, hipStream_t s);
 // ---------------------------------------------------------------- residual-branch dropout
 // Element (t, n) of branch `site` is kept iff word n % 4 of Philox4x32-10 at counter
 // (n / 4, t, site, 0), key (k0, k1), is >= threshold; kept values are multiplied by scale.

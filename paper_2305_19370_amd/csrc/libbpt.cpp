@@ -33,6 +33,7 @@ bpt_status fail(bpt_status st, const char* fmt, ...) {
 }
 
 constexpr int64_t kAlign = 256;
+constexpr size_t kScratchBytes = BPT_NOALLOC_SCRATCH_BYTES;   // bpt_layer_fwd_noalloc's workspace
 // Automatic FFN group: at least 16384 rows, and for a narrow FFN as many rows as keep the
 // [., F] intermediate at 2^27 elements (256 MiB in bf16), so that the group's GEMMs are
 // tall enough to fill the chip and few enough that their per-launch costs stay small.
@@ -142,9 +143,44 @@ SavedPtrs saved_layout(const Dims& d, void* base, int64_t* total) {
   return s;
 }
 
+// Slices of K (few rows leave CUs idle) of the products whose K is their longest side. They
+// take `part` for their partial sums: a few rows' worth, never more than kMaxPart in all, so
+// that what fits the static scratch with it is cut the same way there.
+constexpr int64_t kMaxPart = 16 << 20;
+constexpr int kMaxKSplit = 16;   // the most slices of any product: they bound the workspace
+struct RowSplits {
+  int wo = 1, f2 = 1, dO = 1, dv = 1, du = 1;   // Wo, FFN2; dO, dv, dU of the backward
+};
+int row_split(const Dims& d, int64_t M, int64_t N, int64_t K) {
+  if (M > 1024) return 1;
+  const int z = gemm_ksplit(d.E == 2 ? BF16 : F32, M, N, K, kMaxKSplit);
+  return z * M * N * 4 <= kMaxPart ? z : 1;
+}
+RowSplits row_splits(const Dims& d, bool backward) {
+  RowSplits r;
+  if (!backward) {
+    r.wo = row_split(d, d.R, d.D, d.D);
+    r.f2 = row_split(d, d.R, d.D, d.F);
+  } else {
+    r.dO = row_split(d, d.T, d.D, d.D);
+    r.dv = row_split(d, d.R, d.D, d.F);
+    r.du = row_split(d, d.Tp, d.D, 3 * d.D);
+  }
+  return r;
+}
+
+// Most slices of an M x N weight gradient: enough to fill the chip one and a half times over
+// with its 256 x 256 tiles, none where the tiles alone fill it.
+int wgrad_cap(int64_t M, int64_t N) {
+  const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256);
+  return tiles >= 256 ? 1 : (int)std::min<int64_t>(kMaxKSplit, std::max<int64_t>(1, 384 / tiles));
+}
+
 struct FwdWs {
   void *u, *vg, *gg;
   float* acc;            // FFN output of a group before its dropout (null: no dropout)
+  float* part;           // slices of Wo and FFN2 (null: none)
+  RowSplits z;
 };
 
 FwdWs fwd_ws(const Dims& d, void* base, int64_t* total) {
@@ -154,7 +190,16 @@ FwdWs fwd_ws(const Dims& d, void* base, int64_t* total) {
   w.vg = bp.take(d.R * d.D * d.E);
   w.gg = bp.take(d.R * d.F * d.E);
   w.acc = d.drop ? (float*)bp.take(d.R * d.D * 4) : nullptr;
+  const int64_t least = rup(bp.off, kAlign);
+  w.z = d.drop ? RowSplits() : row_splits(d, false);
+  const int64_t z = std::max(w.z.wo, w.z.f2);
+  w.part = z > 1 ? (float*)bp.take(z * d.R * d.D * 4) : nullptr;
   *total = rup(bp.off, kAlign);
+  if ((size_t)least <= kScratchBytes && (size_t)*total > kScratchBytes) {   // bpt_layer_fwd_noalloc takes it without
+    w.z = RowSplits();
+    w.part = nullptr;
+    *total = least;
+  }
   return w;
 }
 
@@ -165,12 +210,11 @@ struct BwdWs {
   void *dhe, *dO, *dqkvT, *u;
   float* kpart;          // K-slice partials of the D x D weight gradients (null: no split)
   float* fpart;          // K-slice partials of dW1 / dW2 (null: no split)
-  int zo, z1, z3, zf;    // slices of dWo; of one of dWq, dWk, dWv; of the three as one; of dW1, dW2
+  float* rpart;          // slices of dO, dv, dU (null: none)
+  RowSplits z;
+  int zo, z1, z3, zf;    // slices of dWo; of one of dWq, dWk, dWv; of the three as one; most of dW1, dW2
   void* dYm;             // dY through the FFN branch's dropout (null: no dropout)
 };
-
-// Most slices of K of a weight-gradient GEMM (gemm_ksplit chooses): they bound the workspace
-constexpr int kMaxKSplit = 16;
 
 BwdWs bwd_ws(const Dims& d, void* base, int64_t* total) {
   Bump bp(base);
@@ -191,14 +235,23 @@ BwdWs bwd_ws(const Dims& d, void* base, int64_t* total) {
   w.partial = (float*)bp.take((int64_t)layer_norm_param_grad_ws(std::max(d.D, d.F)) * 4);
   // K slices: dWo, and dWq, dWk, dWv as one product or (nz, single) one at a time; dW1, dW2
   const Dt E = d.E == 2 ? BF16 : F32;
-  w.zo = gemm_ksplit(E, d.D, d.D, d.T, kMaxKSplit);
-  w.z1 = gemm_ksplit(E, d.D, d.D, d.Tp, kMaxKSplit);
-  w.z3 = gemm_takes_nper(E, d.D) ? gemm_ksplit(E, d.D, 3 * d.D, d.Tp, kMaxKSplit) : 1;
-  const int64_t kn = std::max({w.zo > 1 ? w.zo : 0, w.z1 > 1 ? w.z1 : 0, w.z3 > 1 ? 3 * w.z3 : 0});
+  // (room for the most slices, whatever the token count: no term of the workspace but the
+  // linear one depends on it)
+  const int co = wgrad_cap(d.D, d.D), c3 = gemm_takes_nper(E, d.D) ? wgrad_cap(d.D, 3 * d.D) : 1, cf = wgrad_cap(d.D, d.F);
+  w.zo = gemm_ksplit(E, d.D, d.D, d.T, co);
+  w.z1 = gemm_ksplit(E, d.D, d.D, d.Tp, co);
+  w.z3 = gemm_ksplit(E, d.D, 3 * d.D, d.Tp, c3);
+  const int64_t kn = std::max(co > 1 ? co : 0, c3 > 1 ? 3 * c3 : 0);
   w.kpart = kn > 0 ? (float*)bp.take(kn * d.D * d.D * 4) : nullptr;
-  w.zf = gemm_ksplit(E, d.F, d.D, d.Rp, kMaxKSplit);
-  w.fpart = w.zf > 1 ? (float*)bp.take(w.zf * d.D * d.F * 4) : nullptr;
+  w.zf = cf;
+  w.fpart = cf > 1 ? (float*)bp.take(cf * d.D * d.F * 4) : nullptr;
   w.dYm = d.drop ? bp.take(d.T * d.D * d.E) : nullptr;
+  w.z = row_splits(d, true);
+  int64_t rp = 0;
+  if (w.z.dO > 1) rp = std::max(rp, w.z.dO * d.T * d.D * 4);
+  if (w.z.dv > 1) rp = std::max(rp, w.z.dv * d.R * d.D * 4);
+  if (w.z.du > 1) rp = std::max(rp, w.z.du * d.Tp * d.D * 4);
+  w.rpart = rp > 0 ? (float*)bp.take(rp) : nullptr;
   *total = rup(bp.off, kAlign);
   return w;
 }
@@ -277,6 +330,11 @@ double gemm_bytes(const GemmArgs& g, size_t eab, size_t ec) {
   const double ncols = (double)std::max(g.N, g.Nstore);
   return ((double)g.M * g.K + (double)g.N * g.K) * eab * g.batch + (double)g.M * ncols * ec * g.batch;
 }
+// the product g in z slices of K into `part`, to be added by sum_slices or sum_slices_add
+void g_split(GemmArgs& g, int z, float* part) {
+  g.R = nullptr; g.bias = nullptr;
+  g.ksplit = z; g.C = part; g.ldc = g.N; g.sC = g.M * g.N;
+}
 // visible (query, key) pairs of query rows [q0, q1) of one sequence of length S
 double attn_pairs(int64_t q0, int64_t q1, int64_t S, int causal) {
   if (!causal) return (double)(q1 - q0) * S;
@@ -352,7 +410,6 @@ XentWs xent_ws(const XentDims& d, void* base, int backward, int64_t* total) {
 // Workspace of bpt_layer_fwd_noalloc: the library's own device memory, one copy per GPU,
 // held until the process ends. In host code `scratch` is a stand-in for the symbol, not a
 // device address: kernels get the address hipGetSymbolAddress returns on each device.
-static constexpr size_t kScratchBytes = BPT_NOALLOC_SCRATCH_BYTES;
 static __device__ __align__(256) char scratch[kScratchBytes];
 
 namespace {
@@ -594,7 +651,12 @@ bpt_status bpt_layer_fwd(const bpt_config* cfg, const void* X, const bpt_params*
       go.A = off(sv.o, t0 * D * E_); go.lda = D; go.B = p->Wo; go.ldb = D; go.trans_b = 1;
       go.C = sv.h + t0 * D; go.ldc = D; go.R = off(X, t0 * D * E_); go.ldr = D;
       go.M = r; go.N = D; go.K = D;
-      if (!d.drop) {
+      if (w.z.wo > 1) {
+        g_split(go, w.z.wo, w.part);
+        RUN("gemm.wo", gemm_flops(go), gemm_bytes(go, E_, 4), gemm(E, EPI_STORE, F32, F32, go, s));
+        RUN("reduce.ksplit", 0, (double)r * D * (4 * w.z.wo + 4 + E_),
+            sum_slices_add(w.part, w.z.wo, r, D, E, off(X, t0 * D * E_), nullptr, F32, sv.h + t0 * D, s));
+      } else if (!d.drop) {
         RUN("gemm.wo", gemm_flops(go), gemm_bytes(go, E_, 4) + (double)r * D * E_,
             gemm(E, EPI_RESID, F32, E, go, s));
       } else {   // O Wo into h, then h = X + drop(h) in place
@@ -617,7 +679,12 @@ bpt_status bpt_layer_fwd(const bpt_config* cfg, const void* X, const bpt_params*
       GemmArgs g2;     // Y = h + G W2 + b2
       g2.A = w.gg; g2.lda = F; g2.B = p->W2; g2.ldb = D; g2.trans_b = 1; g2.C = off(Y, t0 * D * EO);
       g2.ldc = D; g2.R = sv.h + t0 * D; g2.ldr = D; g2.bias = p->b2; g2.M = r; g2.N = D; g2.K = F;
-      if (!d.drop) {
+      if (w.z.f2 > 1) {
+        g_split(g2, w.z.f2, w.part);
+        RUN("gemm.ffn2", gemm_flops(g2), gemm_bytes(g2, E_, 4), gemm(E, EPI_STORE, F32, F32, g2, s));
+        RUN("reduce.ksplit", 0, (double)r * D * (4 * w.z.f2 + 4 + EO),
+            sum_slices_add(w.part, w.z.f2, r, D, F32, sv.h + t0 * D, p->b2, OUT, off(Y, t0 * D * EO), s));
+      } else if (!d.drop) {
         RUN("gemm.ffn2", gemm_flops(g2), gemm_bytes(g2, E_, EO) + 4.0 * r * D, gemm(E, EPI_RESID, OUT, F32, g2, s));
       } else {   // G W2 into fp32 workspace, then Y = h + drop(. + b2)
         g2.C = w.acc; g2.R = nullptr; g2.bias = nullptr;
@@ -695,8 +762,8 @@ bpt_status bpt_layer_bwd(const bpt_config* cfg, const void* X, const bpt_params*
         RUN("gemm.bwd_dz", gemm_flops(g), gemm_bytes(g, E_, E_ + GP_), gemm(E, EPI_MUL, E, GP, g, s));
       }
       if (G.db1) RUN("reduce.bias", 0, (double)F * r * E_, row_sum(E, w.dzT, d.Rp, F, r, G.db1, first ? 0 : 1, s));
-      // K slices of the FFN weight gradients (a shorter last group takes no more than fit)
-      const int fz = w.fpart ? std::min(w.zf, gemm_ksplit(E, F, D, rp, kMaxKSplit)) : 1;
+      // K slices of the FFN weight gradients
+      const int fz = gemm_ksplit(E, F, D, rp, w.zf);
       auto fgrad = [&](const char* name, GemmArgs g, float* out) -> bpt_status {
         g.accumulate = first ? 0 : 1;
         g.C = out;
@@ -720,7 +787,11 @@ bpt_status bpt_layer_bwd(const bpt_config* cfg, const void* X, const bpt_params*
         g.A = w.dzT; g.lda = d.Rp; g.trans_a = 1; g.a_cols = d.Rp;
         g.B = p->W1; g.ldb = F; g.C = w.dv + t0 * D; g.ldc = D;
         g.M = r; g.N = D; g.K = F;
+        if (w.z.dv > 1) g_split(g, w.z.dv, w.rpart);
         RUN("gemm.bwd_dv", gemm_flops(g), gemm_bytes(g, E_, 4), gemm(E, EPI_STORE, F32, F32, g, s));
+        if (w.z.dv > 1)
+          RUN("reduce.ksplit", 0, (double)r * D * 4 * (w.z.dv + 1),
+              sum_slices_add(w.rpart, w.z.dv, r, D, F32, nullptr, nullptr, F32, w.dv + t0 * D, s));
       }
       if (G.dW1) {   // dW1 = v^T dZ, v read token-major (dZ^T is zero past the group's rows)
         GemmArgs g;
@@ -749,7 +820,14 @@ bpt_status bpt_layer_bwd(const bpt_config* cfg, const void* X, const bpt_params*
   {
     GemmArgs g;
     g.A = w.dhe; g.lda = D; g.B = p->Wo; g.ldb = D; g.C = w.dO; g.ldc = D; g.M = T; g.N = D; g.K = D;
-    RUN("gemm.bwd_do", gemm_flops(g), gemm_bytes(g, E_, E_), gemm(E, EPI_STORE, E, F32, g, s));
+    if (w.z.dO > 1) {
+      g_split(g, w.z.dO, w.rpart);
+      RUN("gemm.bwd_do", gemm_flops(g), gemm_bytes(g, E_, 4), gemm(E, EPI_STORE, F32, F32, g, s));
+      RUN("reduce.ksplit", 0, (double)T * D * (4 * w.z.dO + E_),
+          sum_slices_add(w.rpart, w.z.dO, T, D, F32, nullptr, nullptr, E, w.dO, s));
+    } else {
+      RUN("gemm.bwd_do", gemm_flops(g), gemm_bytes(g, E_, E_), gemm(E, EPI_STORE, E, F32, g, s));
+    }
   }
   // Each D x D weight gradient is one GEMM over the whole batch, K = its tokens, cut along K
   // where its tiles would leave CUs idle; slices go to `kpart` and are added in order.
@@ -820,7 +898,11 @@ bpt_status bpt_layer_bwd(const bpt_config* cfg, const void* X, const bpt_params*
     g.A = w.dqkvT; g.lda = Tp; g.trans_a = 1;
     g.B = p->Wq; g.ldb = D; g.kper = D; g.Bx[0] = p->Wq; g.Bx[1] = p->Wk; g.Bx[2] = p->Wv;
     g.C = w.dU; g.ldc = D; g.M = Tp; g.N = D; g.K = 3 * D;
+    if (w.z.du > 1) g_split(g, w.z.du, w.rpart);
     RUN("gemm.bwd_du", gemm_flops(g), gemm_bytes(g, E_, 4), gemm(E, EPI_STORE, F32, F32, g, s));
+    if (w.z.du > 1)
+      RUN("reduce.ksplit", 0, (double)Tp * D * 4 * (w.z.du + 1),
+          sum_slices_add(w.rpart, w.z.du, Tp, D, F32, nullptr, nullptr, F32, w.dU, s));
   }
   RUN("layernorm.bwd", 0, (double)T * D * (E_ + 4 + 4 + EO),
       layer_norm_bwd(E, X, sv.mu1, sv.rstd1, p->ln1_g, F32, w.dU, F32, w.dh, OUT, dX, OUT, nullptr, G.dln1_g, G.dln1_b,
@@ -919,7 +1001,7 @@ bpt_status bpt_xent_bwd(const bpt_xent_config* cfg, const void* h, const void* W
         void* out = g.C;
         g.ksplit = zdh; g.C = w.part; g.sC = r * d.D;
         RUN("xent.dh", gemm_flops(g), gemm_bytes(g, E_, 4), gemm(E, EPI_STORE, F32, F32, g, s));
-        RUN("reduce.ksplit", 0, (double)r * d.D * (4 * zdh + E_), sum_slices_bf16(w.part, zdh, r * d.D, out, s));
+        RUN("reduce.ksplit", 0, (double)r * d.D * (4 * zdh + E_), sum_slices_add(w.part, zdh, r, d.D, F32, nullptr, nullptr, E, out, s));
       } else {
         RUN("xent.dh", gemm_flops(g), gemm_bytes(g, E_, E_), gemm(E, EPI_STORE, E, F32, g, s));
       }

@@ -898,21 +898,38 @@ __global__ __launch_bounds__(256) void sum_slices_kernel(const float* part, int 
   ((f32x4*)out)[at] = acc;
 }
 
-__global__ __launch_bounds__(256) void sum_slices_bf16_kernel(const float* part, int nz, int64_t n, bf16* out) {
-  const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;      // group of four
-  if (4 * q >= n) return;
-  f32x4 acc = ((const f32x4*)part)[q];
+template <typename TR, typename TO>
+__global__ __launch_bounds__(256) void sum_slices_add_kernel(const float* part, int nz, int64_t n, int64_t cols, const TR* R,
+                                                             const float* bias, TO* out) {
+  const int64_t i = 4 * ((int64_t)blockIdx.x * 256 + threadIdx.x);      // group of four
+  if (i >= n) return;
+  f32x4 acc = *(const f32x4*)(part + i);
 #pragma unroll 4
-  for (int z = 1; z < nz; ++z) acc += ((const f32x4*)(part + z * n))[q];
-  const float v[4] = {acc[0], acc[1], acc[2], acc[3]};
-  Vec4<bf16>::store(out + 4 * q, v);
+  for (int z = 1; z < nz; ++z) acc += *(const f32x4*)(part + z * n + i);
+  float v[4] = {acc[0], acc[1], acc[2], acc[3]};
+  if (R) {
+    float r[4];
+    Vec4<TR>::load(R + i, r);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] += r[e];
+  }
+  if (bias) {
+    float b[4];
+    Vec4<float>::load(bias + i % cols, b);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] += b[e];
+  }
+  Vec4<TO>::store(out + i, v);
 }
 
-hipError_t sum_slices_bf16(const float* part, int nz, int64_t n, void* out, hipStream_t s) {
+hipError_t sum_slices_add(const float* part, int nz, int64_t rows, int64_t cols, Dt tr, const void* R, const float* bias,
+                          Dt to, void* out, hipStream_t s) {
+  const int64_t n = rows * cols;
   if (n <= 0) return hipSuccess;
-  if (n % 4 != 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(sum_slices_bf16_kernel, dim3((unsigned)((n / 4 + 255) / 256)), dim3(256), 0, s, part, nz, n,
-                     (bf16*)out);
+  if (cols % 4 != 0) return hipErrorInvalidValue;
+  BPT_T(tr, TR, BPT_T(to, TO,
+        hipLaunchKernelGGL((sum_slices_add_kernel<TR, TO>), dim3((unsigned)((n / 4 + 255) / 256)), dim3(256), 0, s, part,
+                           nz, n, cols, (const TR*)R, bias, (TO*)out)));
   return hipGetLastError();
 }
 
