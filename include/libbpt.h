@@ -200,7 +200,7 @@ size_t bpt_profile_report(char* buf, size_t buf_bytes);
  * Cross-entropy of a language-model head, blockwise over tokens. Section 3 of the
  * paper remarks that the blockwise scheme applies to the final cross-entropy loss
  * as well: here the [T, V] logits never exist at once, only those of block_rows
- * tokens, in the workspace.
+ * tokens, in the workspace (dtype BF16, forward: only their row summaries).
  *
  *     logits = h W        h [T, D] and W [D, ldw] in cfg->dtype (row-major, y = x @ W);
  *                         the first V columns of W are the vocabulary

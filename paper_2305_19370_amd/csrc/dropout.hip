@@ -5,21 +5,12 @@
 // forward and backward regenerate it instead of storing it. HBM-bound elementwise
 // kernels: one thread per four consecutive columns (one generator call).
 #include "common.h"
+#include "drop.h"
 #include "internal.h"
 
 namespace bpt {
 
 namespace {
-
-BPT_DEV u32x4 philox4x32_10(u32x4 c, uint32_t k0, uint32_t k1) {
-  for (int r = 0; r < 10; ++r) {
-    if (r) { k0 += 0x9E3779B9u; k1 += 0xBB67AE85u; }
-    const uint32_t lo0 = 0xD2511F53u * c[0], hi0 = __umulhi(0xD2511F53u, c[0]);
-    const uint32_t lo1 = 0xCD9E8D57u * c[2], hi1 = __umulhi(0xCD9E8D57u, c[2]);
-    c = u32x4{hi1 ^ c[1] ^ k0, lo1, hi0 ^ c[3] ^ k1, lo0};
-  }
-  return c;
-}
 
 template <typename T> BPT_DEV void ld4(const T* p, float v[4]);
 template <> BPT_DEV void ld4<float>(const float* p, float v[4]) {
@@ -38,13 +29,6 @@ template <> BPT_DEV void st4<bf16>(bf16* p, const float v[4]) {
   *(bf16x4*)p = x;
 }
 
-// keep factors (0 or scale) of columns n..n+3 of token t
-BPT_DEV void factors(const DropArgs& a, int64_t t, int64_t n, float f[4]) {
-  const u32x4 w = philox4x32_10(u32x4{(uint32_t)(n >> 2), (uint32_t)t, a.site, 0u}, a.k0, a.k1);
-#pragma unroll
-  for (int e = 0; e < 4; ++e) f[e] = w[e] >= a.threshold ? a.scale : 0.0f;
-}
-
 }  // namespace
 
 // out[i, n] = R[i, n] + f(row0 + i, n) (acc[i, n] + bias[n])  (rows x D, D % 4 == 0)
@@ -55,7 +39,7 @@ __global__ __launch_bounds__(256) void dropout_add_kernel(const float* acc, cons
   const int64_t i = q / (D / 4), n = (q % (D / 4)) * 4;
   if (i >= rows) return;
   float f[4], x[4], r[4];
-  factors(a, a.row0 + i, n, f);
+  drop_factors(a, a.row0 + i, n, f);
   ld4(acc + i * D + n, x);
   ld4(R + i * D + n, r);
   if (bias) {
@@ -77,7 +61,7 @@ __global__ __launch_bounds__(256) void dropout_scale_kernel(const TI* in, TO* ou
   const int64_t i = q / (D / 4), n = (q % (D / 4)) * 4;
   if (i >= rows) return;
   float f[4], x[4];
-  factors(a, a.row0 + i, n, f);
+  drop_factors(a, a.row0 + i, n, f);
   ld4(in + i * D + n, x);
 #pragma unroll
   for (int e = 0; e < 4; ++e) x[e] *= f[e];

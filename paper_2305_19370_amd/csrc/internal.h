@@ -112,6 +112,15 @@ hipError_t attn_fwd(Dt dt, const AttnArgs& a, hipStream_t s);
 hipError_t attn_bwd_dkdv(Dt dt, const AttnArgs& a, hipStream_t s);
 hipError_t attn_bwd_dq(Dt dt, const AttnArgs& a, hipStream_t s);
 
+// ---------------------------------------------------------------- residual-branch dropout
+// Element (t, n) of branch `site` is kept iff word n % 4 of Philox4x32-10 at counter
+// (n / 4, t, site, 0), key (k0, k1), is >= threshold; kept values are multiplied by scale.
+struct DropArgs {
+  uint32_t k0 = 0, k1 = 0, site = 0, threshold = 0;
+  float scale = 1.0f;
+  int64_t row0 = 0;            // token index t of the first row passed
+};
+
 // ---------------------------------------------------------------- row-wise / layout kernels
 // LayerNorm over D per row. x: [rows, D] (ti); out [rows, D] (to).
 // mode 0: compute and write mu/rstd; mode 1: use the given mu/rstd.
@@ -124,17 +133,19 @@ hipError_t layer_norm(Dt ti, Dt to, const void* x, int64_t ldx, const float* g, 
 // dbeta[d] = sum_r dout[r,d] (overwrite; either may be null), through `partial`, workspace of
 // at least layer_norm_param_grad_ws(D) floats (more are used if there). dout is fp32, or bf16
 // where layer_norm_bwd_fused(D). With seg > 0, dout has a row pitch of `pitch` rows per seg
-// rows: row r is stored at r + r / seg * (pitch - seg).
+// rows: row r is stored at r + r / seg * (pitch - seg). drop (null: none; only where
+// layer_norm_bwd_fused(D)): out2 gets the values through that dropout.
 size_t layer_norm_param_grad_ws(int64_t D);
 bool layer_norm_bwd_fused(int64_t D);
 hipError_t layer_norm_bwd(Dt ti, const void* x, const float* mu, const float* rstd, const float* g, Dt td,
                           const void* dout, Dt tr, const void* resid, Dt to, void* out, Dt t2, void* out2,
                           float* dgamma, float* dbeta, float* partial, int64_t partial_floats, int64_t rows, int64_t D,
-                          int64_t seg, int64_t pitch, hipStream_t s);
+                          int64_t seg, int64_t pitch, const DropArgs* drop, hipStream_t s);
 
-// out[c] (+)= sum_r in[r, c]  (in: [rows, cols] of type t)
-hipError_t col_sum(Dt t, const void* in, int64_t ld, int64_t rows, int64_t cols, float* out,
-                   int accumulate, float* partial, hipStream_t s);
+// out[c] = sum_r in[r, c]  (in: [rows, cols] of type t, rows 16-byte aligned, cols % 8 == 0), through
+// `partial` of at least cols floats (more are used if there)
+hipError_t col_sum(Dt t, const void* in, int64_t ld, int64_t rows, int64_t cols, float* out, float* partial,
+                   int64_t partial_floats, hipStream_t s);
 // out[r] (+)= sum_c in[r, c]
 hipError_t row_sum(Dt t, const void* in, int64_t ld, int64_t rows, int64_t cols, float* out,
                    int accumulate, hipStream_t s);
@@ -178,14 +189,6 @@ hipError_t sum_slices(const float* part, int nz, int64_t rows, int64_t cols, flo
 // `to` (R of type tr or null, bias fp32 or null; rows x cols, cols % 4 == 0)
 hipError_t sum_slices_add(const float* part, int nz, int64_t rows, int64_t cols, Dt tr, const void* R, const float* bias,
                           Dt to, void* out, hipStream_t s);
-// ---------------------------------------------------------------- residual-branch dropout
-// Element (t, n) of branch `site` is kept iff word n % 4 of Philox4x32-10 at counter
-// (n / 4, t, site, 0), key (k0, k1), is >= threshold; kept values are multiplied by scale.
-struct DropArgs {
-  uint32_t k0 = 0, k1 = 0, site = 0, threshold = 0;
-  float scale = 1.0f;
-  int64_t row0 = 0;            // token index t of the first row passed
-};
 // out = R + f * (acc + bias) over rows x D (acc fp32 [rows, D]; bias fp32 [D] or null)
 hipError_t dropout_add(const float* acc, Dt tr, const void* R, const float* bias, Dt to, void* out, int64_t rows,
                        int64_t D, const DropArgs& a, hipStream_t s);

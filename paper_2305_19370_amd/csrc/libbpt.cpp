@@ -517,8 +517,8 @@ size_t bpt_describe(const bpt_config* cfg, char* buf, size_t n) {
                    bf ? "MFMA 32x32x16 bf16, fp32 accumulate, 32 rows per wave"
                       : "MFMA 16x16x4 fp32, 4 waves sharing 16 rows",
                    bf ? 256 : 16, 64, bf ? 256 : 16, 64,
-                   bf ? "MFMA bf16 256x256 (8 waves) or 128x128 (4 waves) tiles, K-step 32"
-                      : "MFMA fp32 128x128, 64x64 or 32x32 tiles (4 waves), K-step 16",
+                   bf ? "MFMA bf16 256x256 (8 waves), 128x128 or 64x64 (4 waves; 16 sharing K) tiles, K-step 32"
+                      : "MFMA fp32 128x128, 64x64 or 32x32 (4 waves; 16 sharing K) tiles, K-step 16",
                    cfg->activation == BPT_RELU ? "relu" : "gelu", (long long)d.R, (long long)d.nbg, (long long)d.Rs,
                    (long long)cfg->Bq);
   return w < 0 ? 0 : std::min((size_t)w, n - 1);
@@ -808,12 +808,14 @@ bpt_status bpt_layer_bwd(const bpt_config* cfg, const void* X, const bpt_params*
   const int64_t ffn_n = ((char*)w.dv - (char*)w.gT) / 4, part_n = (int64_t)layer_norm_param_grad_ws(std::max(D, F));
   float* ln_part = ffn_n > part_n ? (float*)w.gT : w.partial;
   const int64_t ln_part_n = std::max(ffn_n, part_n);
-  // dh = dY + LN2^T(dv)
+  // dh = dY + LN2^T(dv); the output projection sees dh through its dropout
+  const DropArgs drop0 = drop_args(*cfg, 0, 0);
+  const bool mask_dh = d.drop && layer_norm_bwd_fused(D);
   RUN("layernorm.bwd", 0, (double)T * D * (4 + 4 + E_ + 4 + E_),
       layer_norm_bwd(F32, sv.h, sv.mu2, sv.rstd2, p->ln2_g, F32, w.dv, E, dY, F32, w.dh, E, w.dhe, G.dln2_g, G.dln2_b,
-                     ln_part, ln_part_n, T, D, 0, 0, s));
-  if (G.db2) RUN("reduce.bias", 0, (double)T * D * E_, col_sum(E, dYf, D, T, D, G.db2, 0, w.partial, s));
-  if (d.drop)   // the output projection sees dh through its dropout
+                     ln_part, ln_part_n, T, D, 0, 0, mask_dh ? &drop0 : nullptr, s));
+  if (G.db2) RUN("reduce.bias", 0, (double)T * D * E_, col_sum(E, dYf, D, T, D, G.db2, ln_part, ln_part_n, s));
+  if (d.drop && !mask_dh)
     RUN("dropout.bwd", 0, (double)T * D * (4 + E_), dropout_scale(F32, w.dh, E, w.dhe, T, D, drop_args(*cfg, 0, 0), s));
 
   // ---- output projection backward: dO = dh Wo^T, dWo = O^T dh
@@ -906,7 +908,7 @@ bpt_status bpt_layer_bwd(const bpt_config* cfg, const void* X, const bpt_params*
   }
   RUN("layernorm.bwd", 0, (double)T * D * (E_ + 4 + 4 + EO),
       layer_norm_bwd(E, X, sv.mu1, sv.rstd1, p->ln1_g, F32, w.dU, F32, w.dh, OUT, dX, OUT, nullptr, G.dln1_g, G.dln1_b,
-                     ln_part, ln_part_n, T, D, S, Sp, s));
+                     ln_part, ln_part_n, T, D, S, Sp, nullptr, s));
   return BPT_OK;
 }
 
@@ -1144,7 +1146,7 @@ bpt_status bpt_ln_bwd(const bpt_ln_config* cfg, const void* X, const float* g, c
     partial_n = dy_off / 4;
   }
   RUN("gpt.ln_f_bwd", 0, (double)R * D * (2 * I_ + (TD == BF16 ? 2 : 4)) + (double)R * 8,
-      layer_norm_bwd(TI, X, mean, rstd, g, TD, dY, F32, nullptr, TI, dX, TI, nullptr, dg, db, partial, partial_n, R, D, 0, 0, s));
+      layer_norm_bwd(TI, X, mean, rstd, g, TD, dY, F32, nullptr, TI, dX, TI, nullptr, dg, db, partial, partial_n, R, D, 0, 0, nullptr, s));
   return BPT_OK;
 }
 

@@ -5,6 +5,7 @@
 #include <algorithm>
 
 #include "common.h"
+#include "drop.h"
 #include "internal.h"
 
 namespace bpt {
@@ -188,11 +189,11 @@ struct RowMap {
 // HBM-bound: x and dout are read once for all three gradients. Final LayerNorm of 16384 x
 // 2048 bf16 rows, dX and parameters: 45 us (4.5 TB/s) and 6.6 for the reduction, against
 // 124 us in four passes (dout widened to fp32, dX, partial sums, reduction).
-template <typename TI, typename TD, typename TR, typename TO, typename T2, int NC, int WPR, bool PARAM>
+template <typename TI, typename TD, typename TR, typename TO, typename T2, int NC, int WPR, bool PARAM, bool DROP>
 __global__ __launch_bounds__(256) void ln_bwd_reg_kernel(const TI* x, const float* mu, const float* rstd,
                                                          const float* g, const TD* dout, const TR* resid,
                                                          TO* out, T2* out2, float* partial, int64_t rows, int D,
-                                                         RowMap map) {
+                                                         RowMap map, DropArgs drop) {
   static_assert(WPR == 1 || WPR == 4, "waves per row");
   static_assert(WPR == 4 || !PARAM || NC <= 4, "LDS of the block sums");
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // row in scalar registers
@@ -263,6 +264,13 @@ __global__ __launch_bounds__(256) void ln_bwd_reg_kernel(const TI* x, const floa
 #pragma unroll
         for (int e = 0; e < 8; ++e) rv[e] += rs * (gd[c][e] - s1 - xh[c][e] * s2);
         Vec8<TO>::store(out + row * D + d, rv);
+        if constexpr (DROP) {
+          float f[8];
+          drop_factors(drop, drop.row0 + row, d, f);
+          drop_factors(drop, drop.row0 + row, d + 4, f + 4);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) rv[e] *= f[e];
+        }
         if (out2) Vec8<T2>::store(out2 + row * D + d, rv);
       }
     }
@@ -380,46 +388,44 @@ __global__ __launch_bounds__(256) void chunk_reduce_kernel(const float* partial,
   }
 }
 
+// Column sums, first stage: a block of four waves per (512-column group, row chunk of `per`
+// rows), wave w its rows w, w + 4, ... (8 consecutive columns per lane with 16-byte loads,
+// four rows in flight); the wave sums are added through LDS in wave order.
 template <typename T>
-__global__ __launch_bounds__(256) void col_partial_kernel(const T* in, int64_t ld, int64_t rows,
-                                                          int64_t cols, float* partial) {
-  const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (c >= cols) return;
-  const int64_t per = (rows + kChunks - 1) / kChunks;
-  const int64_t r0 = blockIdx.y * per, r1 = r0 + per < rows ? r0 + per : rows;
-  float s = 0.0f;
-  for (int64_t r = r0; r < r1; ++r) s += to_f32<T>(in[r * ld + c]);
-  partial[(int64_t)blockIdx.y * cols + c] = s;
-}
-
-// Wide forms of the two partial-sum kernels for 8-column-aligned rows: one wave per
-// (512-column group, row chunk), 8 consecutive columns per lane with 16-byte loads, rows
-// unrolled by four so that several loads are in flight per lane.
-template <typename T>
-__global__ __launch_bounds__(64) void col_partial8_kernel(const T* in, int64_t ld, int64_t rows, int64_t cols,
-                                                          float* partial) {
-  const int64_t c = ((int64_t)blockIdx.x * 64 + threadIdx.x) * 8;
-  if (c >= cols) return;
-  const int64_t per = (rows + kChunks - 1) / kChunks;
+__global__ __launch_bounds__(256) void col_partial8_kernel(const T* in, int64_t ld, int64_t rows, int64_t per, int64_t cols,
+                                                           float* partial) {
+  __shared__ __attribute__((aligned(16))) float red[3][512];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t c = ((int64_t)blockIdx.x * 64 + lane) * 8;
   const int64_t r0 = blockIdx.y * per, r1 = r0 + per < rows ? r0 + per : rows;
   float s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  int64_t r = r0;
-  for (; r + 4 <= r1; r += 4) {
-    float v[4][8];
+  if (c < cols) {
+    int64_t r = r0 + wave;
+    for (; r + 12 < r1; r += 16) {
+      float v[4][8];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) Vec8<T>::load(in + (r + u) * ld + c, v[u]);
+      for (int u = 0; u < 4; ++u) Vec8<T>::load(in + (r + 4 * u) * ld + c, v[u]);
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+      for (int u = 0; u < 4; ++u)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) s[e] += v[u][e];
+        for (int e = 0; e < 8; ++e) s[e] += v[u][e];
+    }
+    for (; r < r1; r += 4) {
+      float v[8];
+      Vec8<T>::load(in + r * ld + c, v);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) s[e] += v[e];
+    }
   }
-  for (; r < r1; ++r) {
-    float v[8];
-    Vec8<T>::load(in + r * ld + c, v);
+  if (wave > 0) Vec8<float>::store(&red[wave - 1][8 * lane], s);
+  __syncthreads();
+  if (wave == 0 && c < cols) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) s[e] += v[e];
+    for (int w = 0; w < 3; ++w)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) s[e] += red[w][8 * lane + e];
+    Vec8<float>::store(partial + (int64_t)blockIdx.y * cols + c, s);
   }
-  Vec8<float>::store(partial + (int64_t)blockIdx.y * cols + c, s);
 }
 
 // LayerNorm parameter partials, wide form: a block of four waves per (512-column group, row
@@ -720,23 +726,24 @@ static int ln_param_blocks(int64_t rows, int64_t D, int64_t partial_floats) {
   return (int)std::max<int64_t>(1, std::min<int64_t>({512, (rows + 7) / 8, fit}));
 }
 
-template <typename TI, typename TD, typename TR, typename TO, typename T2>
+template <typename TI, typename TD, typename TR, typename TO, typename T2, bool DROP>
 static hipError_t ln_bwd_typed(const void* x, const float* mu, const float* rstd, const float* g, const void* dout,
                                const void* resid, void* out, void* out2, float* dgamma, float* dbeta, float* partial,
-                               int64_t partial_floats, int64_t rows, int64_t D, RowMap map, hipStream_t s) {
+                               int64_t partial_floats, int64_t rows, int64_t D, RowMap map, const DropArgs& drop,
+                               hipStream_t s) {
   const bool param = dgamma || dbeta;
   const int nblk = param ? ln_param_blocks(rows, D, partial_floats) : 0;
 #define BPT_LN_BWD(NCV, WPRV)                                                                                     \
   do {                                                                                                            \
     if (param)                                                                                                    \
-      hipLaunchKernelGGL((ln_bwd_reg_kernel<TI, TD, TR, TO, T2, NCV, WPRV, true>), dim3(nblk), dim3(256), 0, s,   \
+      hipLaunchKernelGGL((ln_bwd_reg_kernel<TI, TD, TR, TO, T2, NCV, WPRV, true, DROP>), dim3(nblk), dim3(256), 0, s, \
                          (const TI*)x, mu, rstd, g, (const TD*)dout, (const TR*)resid, (TO*)out, (T2*)out2,       \
-                         partial, rows, (int)D, map);                                                             \
+                         partial, rows, (int)D, map, drop);                                                       \
     else                                                                                                          \
-      hipLaunchKernelGGL((ln_bwd_reg_kernel<TI, TD, TR, TO, T2, NCV, WPRV, false>),                               \
+      hipLaunchKernelGGL((ln_bwd_reg_kernel<TI, TD, TR, TO, T2, NCV, WPRV, false, DROP>),                         \
                          dim3((unsigned)(WPRV == 4 ? rows : (rows + 3) / 4)), dim3(256), 0, s, (const TI*)x, mu,  \
                          rstd, g, (const TD*)dout, (const TR*)resid, (TO*)out, (T2*)out2, (float*)nullptr, rows,  \
-                         (int)D, map);                                                                            \
+                         (int)D, map, drop);                                                                      \
   } while (0)
   const int64_t nc = (D + 511) / 512;       // up to 2048 columns a wave holds the row, beyond that four waves do
   if (nc <= 1) BPT_LN_BWD(1, 1);
@@ -762,7 +769,7 @@ bool layer_norm_bwd_fused(int64_t D) { return D % 8 == 0 && D <= 8192; }
 hipError_t layer_norm_bwd(Dt ti, const void* x, const float* mu, const float* rstd, const float* g, Dt td,
                           const void* dout, Dt tr, const void* resid, Dt to, void* out, Dt t2, void* out2,
                           float* dgamma, float* dbeta, float* partial, int64_t partial_floats, int64_t rows, int64_t D,
-                          int64_t seg, int64_t pitch, hipStream_t s) {
+                          int64_t seg, int64_t pitch, const DropArgs* drop, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
   RowMap map;
   if (seg > 0) map.seg = seg, map.gap = pitch - seg;
@@ -773,8 +780,17 @@ hipError_t layer_norm_bwd(Dt ti, const void* x, const float* mu, const float* rs
     // the type combinations in use: LN2 (dh and its rounded copy), LN1 (dX), the final LayerNorm
 #define BPT_LN_IF(A, TD_, R, O, O2, TI, TD, TR, TO, T2)                                                          \
   if (ti == A && td == TD_ && (!resid || tr == R) && to == O && (!out2 || t2 == O2))                             \
-    return ln_bwd_typed<TI, TD, TR, TO, T2>(x, mu, rstd, g, dout, resid, out, out2, dgamma, dbeta, partial,      \
-                                            partial_floats, rows, D, map, s)
+    return ln_bwd_typed<TI, TD, TR, TO, T2, false>(x, mu, rstd, g, dout, resid, out, out2, dgamma, dbeta,        \
+                                                   partial, partial_floats, rows, D, map, DropArgs(), s)
+    if (drop) {                             // LN2 with dropout: the copy into the output projection
+      if (ti != F32 || td != F32 || to != F32 || !out2 || tr != t2) return hipErrorInvalidValue;
+      return t2 == BF16 ? ln_bwd_typed<float, float, bf16, float, bf16, true>(x, mu, rstd, g, dout, resid, out, out2, dgamma,
+                                                                              dbeta, partial, partial_floats, rows, D, map,
+                                                                              *drop, s)
+                        : ln_bwd_typed<float, float, float, float, float, true>(x, mu, rstd, g, dout, resid, out, out2,
+                                                                                dgamma, dbeta, partial, partial_floats,
+                                                                                rows, D, map, *drop, s);
+    }
     BPT_LN_IF(F32, F32, F32, F32, F32, float, float, float, float, float);
     BPT_LN_IF(F32, F32, BF16, F32, BF16, float, float, bf16, float, bf16);
     BPT_LN_IF(F32, F32, F32, BF16, BF16, float, float, float, bf16, bf16);
@@ -784,7 +800,7 @@ hipError_t layer_norm_bwd(Dt ti, const void* x, const float* mu, const float* rs
     BPT_LN_IF(BF16, BF16, F32, BF16, BF16, bf16, bf16, float, bf16, bf16);
 #undef BPT_LN_IF
   }
-  if (td != F32) return hipErrorInvalidValue;       // the caller widens dout for rows this long
+  if (td != F32 || drop) return hipErrorInvalidValue;   // the caller widens dout and masks rows this long
   const dim3 grid((unsigned)((rows + 3) / 4));
   BPT_T(ti, TI, BPT_T(tr, TR, BPT_T(to, TO, BPT_T(t2, T2,
         hipLaunchKernelGGL((ln_bwd_kernel<TI, TR, TO, T2>), grid, dim3(256), 0, s, (const TI*)x, mu,
@@ -809,21 +825,20 @@ static hipError_t layer_norm_param_grad(Dt ti, const void* x, const float* mu, c
   return hipGetLastError();
 }
 
-hipError_t col_sum(Dt t, const void* in, int64_t ld, int64_t rows, int64_t cols, float* out,
-                   int accumulate, float* partial, hipStream_t s) {
-  if (cols % 8 == 0 && ld % 8 == 0 && ((uintptr_t)in & 15) == 0 && ((uintptr_t)partial & 15) == 0) {
-    const dim3 grid8((unsigned)((cols + 511) / 512), kChunks);
-    BPT_T(t, T, hipLaunchKernelGGL((col_partial8_kernel<T>), grid8, dim3(64), 0, s, (const T*)in, ld, rows,
-                                   cols, partial));
-  } else {
-    const dim3 grid((unsigned)((cols + 255) / 256), kChunks);
-    BPT_T(t, T, hipLaunchKernelGGL((col_partial_kernel<T>), grid, dim3(256), 0, s, (const T*)in, ld, rows,
-                                   cols, partial));
-  }
+hipError_t col_sum(Dt t, const void* in, int64_t ld, int64_t rows, int64_t cols, float* out, float* partial,
+                   int64_t partial_floats, hipStream_t s) {
+  if (cols % 8 || ld % 8 || ((uintptr_t)in & 15) || ((uintptr_t)partial & 15) || partial_floats < cols)
+    return hipErrorInvalidValue;
+  // about 1024 blocks (four per CU), of at least 16 rows each
+  const int64_t gx = (cols + 511) / 512;
+  const int64_t nch = std::max<int64_t>(1, std::min<int64_t>({1024 / gx, (rows + 15) / 16, partial_floats / cols, 512}));
+  const int64_t per = (rows + nch - 1) / nch;
+  BPT_T(t, T, hipLaunchKernelGGL((col_partial8_kernel<T>), dim3((unsigned)gx, (unsigned)nch), dim3(256), 0, s, (const T*)in,
+                                 ld, rows, per, cols, partial));
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(chunk_reduce_kernel, dim3((unsigned)((cols + 15) / 16)), dim3(256), 0, s, partial, kChunks,
-                     out, (float*)nullptr, cols, accumulate);
+  hipLaunchKernelGGL(chunk_reduce_kernel, dim3((unsigned)((cols + 15) / 16)), dim3(256), 0, s, partial, (int)nch,
+                     out, (float*)nullptr, cols, 0);
   return hipGetLastError();
 }
 

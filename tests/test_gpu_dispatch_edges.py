@@ -3,6 +3,7 @@ the float64 oracle under the gates of tests/gpu_util.py."""
 import pytest
 import torch
 
+import oracle
 from bpt_inputs import make_inputs, small_workload
 from gpu_util import run_gpu, run_oracle, say
 from paper_2305_19370_amd import bpt
@@ -159,3 +160,17 @@ def test_bf16_attention_blocks(B, S, D, H, causal):
     gpu = run_gpu(w, inp, qkv_grads=True)
     Yr, _, g = run_oracle(w, inp)
     compare_all(w, inp, gpu, Yr, g, "bf16", w.name)
+
+
+# residual dropout: the mask of dh applied inside the LN2 backward (rows in one wave and in four)
+@pytest.mark.parametrize("dtype,D,H", [("f32", 192, 3), ("bf16", 192, 3), ("bf16", 2176, 17)])
+def test_dropout_gradient_rows(dtype, D, H):
+    w = small_workload(dtype, B=2, S=70, D=D, H=H, F=128, Bq=64, Bkv=64, init="unit")
+    inp = make_inputs(w, seed=17, affine=True, biases=True)
+    say(f"case {w.name} dropout")
+    gpu = run_gpu(w, inp, qkv_grads=True, dropout=0.1, dropout_seed=99)
+    p = oracle.params_from_inputs(inp)
+    p.dropout, p.dropout_seed = 0.1, 99
+    Yr, cache = oracle.layer_fwd(inp["X"].double().numpy(), p, w.H, w.causal)
+    g = oracle.layer_bwd(cache, p, inp["dY"].double().numpy())
+    compare_all(w, inp, gpu, Yr, g, "fp32" if dtype == "f32" else "bf16", w.name, dropout=0.1, dropout_seed=99)
