@@ -666,7 +666,8 @@ __global__ __launch_bounds__(128 * NWN * KG, 1) void gemm_bf16_kernel(GemmArgs a
   // load latency is not paid once per strip.
   constexpr bool PRE = EPI == EPI_RESID || EPI == EPI_MUL || (EPI == EPI_STORE && sizeof(CT) == 4);
   constexpr int PES = EPI == EPI_STORE ? (int)sizeof(CT) : (int)sizeof(RT);   // bytes per element
-  constexpr int PD = PES == 2 ? Cfg::TM : 2;                                   // strips in flight
+  constexpr int PD = PES == 2 || Cfg::TM < 2 ? Cfg::TM : 2;                    // strips in flight
+  static_assert(PD <= Cfg::TM, "no strip past the wave's rows is loaded: rows beyond M need not exist");
   constexpr int NIT = 32 / RSTEP;
   typedef std::conditional_t<PES == 2, u32x2, u32x4> PreT;
   PreT pre[PRE ? PD : 1][PRE ? NIT : 1];
