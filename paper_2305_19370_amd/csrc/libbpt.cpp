@@ -509,14 +509,17 @@ size_t bpt_describe(const bpt_config* cfg, char* buf, size_t n) {
   }
   const Dims d = dims_of(*cfg);
   const bool bf = cfg->dtype == BPT_BF16;
+  // rows per attention workgroup: of a whole FFN group's forward, and of the backward
+  const int fwd = !bf ? 16 : few_blocks(d.Rs, d.H * d.nbg, cfg->causal) ? 128 : 256;
+  const int bwd = !bf ? 16 : few_blocks(d.S, d.H * d.B, cfg->causal) ? 128 : 256;
   int w = snprintf(buf, n,
                    "dtype=%s attention: q-tile=%d kv-step=%d (%s); backward dK/dV kv-tile=%d q-step=%d, "
                    "dQ q-tile=%d kv-step=%d; gemm: %s; ffn %s, group rows=%lld (%lld sequence(s) x %lld rows; "
                    "query blocks of %lld)",
-                   bf ? "bf16" : "f32", bf ? 256 : 16, bf ? 64 : 128,
+                   bf ? "bf16" : "f32", fwd, bf ? 64 : 128,
                    bf ? "MFMA 32x32x16 bf16, fp32 accumulate, 32 rows per wave"
                       : "MFMA 16x16x4 fp32, 4 waves sharing 16 rows",
-                   bf ? 256 : 16, 64, bf ? 256 : 16, 64,
+                   bwd, 64, bwd, 64,
                    bf ? "MFMA bf16 256x256 (8 waves), 128x128 or 64x64 (4 waves; 16 sharing K) tiles, K-step 32"
                       : "MFMA fp32 128x128, 64x64 or 32x32 (4 waves; 16 sharing K) tiles, K-step 16",
                    cfg->activation == BPT_RELU ? "relu" : "gelu", (long long)d.R, (long long)d.nbg, (long long)d.Rs,

@@ -174,6 +174,26 @@ def test_groups_of_whole_sequences():
     assert bpt.group_rows(c) == 200
 
 
+@pytest.mark.parametrize("kw,fwd,bwd", [
+    (dict(B=1, S=250, D=1024, H=8, Bq=125), 128, 128),                       # 8 blocks of 256 rows
+    (dict(B=1, S=32768, D=4096, H=32, Bq=1024), 256, 256),
+    (dict(B=1, S=4096, D=2048, H=16, Bq=512), 128, 128),                     # 256 blocks: one per CU
+    (dict(B=1, S=4097, D=2048, H=16, Bq=512), 256, 256),                     # 272
+    (dict(B=1, S=4096, D=2048, H=16, Bq=512, causal=False), 256, 256),       # more than 128, no mask
+    (dict(B=1, S=16384, D=2048, H=16, Bq=512, group_blocks=4), 128, 256),    # a group of 2048 rows; all 16384
+    (dict(B=2, S=512, D=256, H=4, dtype="f32", Bq=128), 16, 16)])
+def test_describe_names_the_attention_blocks(kw, fwd, bwd):
+    """The description gives the attention block that the launchers choose (few_blocks): 128
+    rows where blocks of 256 do not outnumber the CUs (half of them without the mask)."""
+    kw = dict(kw)
+    g = kw.pop("group_blocks", 0)
+    kw = {"F": 4 * kw["D"], "Bkv": kw["Bq"], "causal": True, "dtype": "bf16", **kw}
+    c = bpt.make_config(**kw)
+    c.group_blocks = g
+    txt = bpt.describe(c)
+    assert f"attention: q-tile={fwd} " in txt and f"dK/dV kv-tile={bwd} " in txt and f"dQ q-tile={bwd} " in txt, txt
+
+
 def test_saved_layout_offsets():
     for dtype in ("f32", "bf16"):
         c = cfg(B=2, S=250, dtype=dtype)
