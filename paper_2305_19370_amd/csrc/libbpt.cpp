@@ -208,11 +208,11 @@ struct BwdWs {
   void* gpT;             // GELU'(Z^T): fp32 on the fp32 path, fp16 on the bf16 path
   float *dv, *dh, *dU, *ndelta, *nlse2, *partial;
   void *dhe, *dO, *dqkvT, *u;
-  float* kpart;          // K-slice partials of the D x D weight gradients (null: no split)
-  float* fpart;          // K-slice partials of dW1 / dW2 (null: no split)
+  float* kpart;          // K-slice partials of the D x D weight gradients
+  float* fpart;          // K-slice partials of dW1 / dW2
   float* rpart;          // slices of dO, dv, dU (null: none)
   RowSplits z;
-  int zo, z1, z3, zf;    // slices of dWo; of one of dWq, dWk, dWv; of the three as one; most of dW1, dW2
+  int zo, z1, z3, zf;    // slices of dWo; of one of dWq, dWk, dWv; of the three as one; the most of dW1, dW2
   void* dYm;             // dY through the FFN branch's dropout (null: no dropout)
 };
 
@@ -224,6 +224,7 @@ BwdWs bwd_ws(const Dims& d, void* base, int64_t* total) {
   w.gpT = bp.take(d.F * d.Rp * (d.E == 2 ? 2 : 4));   // fp16 on the bf16 path, else fp32
   w.dzT = bp.take(d.F * d.Rp * d.E);
   w.dv = (float*)bp.take(d.T * d.D * 4);
+  w.dU = (float*)bp.take(d.Tp * d.D * 4);   // rows of a sequence at a pitch of Sp
   w.dh = (float*)bp.take(d.T * d.D * 4);
   w.dhe = bp.take(d.T * d.D * d.E);
   w.dO = bp.take(d.T * d.D * d.E);
@@ -231,20 +232,28 @@ BwdWs bwd_ws(const Dims& d, void* base, int64_t* total) {
   w.nlse2 = (float*)bp.take(d.B * d.H * d.Sp * 4);
   w.dqkvT = bp.take(3 * d.D * d.Tp * d.E);
   w.u = bp.take(d.T * d.D * d.E);
-  w.dU = (float*)bp.take(d.Tp * d.D * 4);   // rows of a sequence at a pitch of Sp
   w.partial = (float*)bp.take((int64_t)layer_norm_param_grad_ws(std::max(d.D, d.F)) * 4);
-  // K slices: dWo, and dWq, dWk, dWv as one product or (nz, single) one at a time; dW1, dW2
+  // K slices of the weight gradients go to buffers that are idle meanwhile: those of dW1 and dW2
+  // to what is written after the FFN groups (dU to u), those of dWo, dWq, dWk and dWv to the FFN
+  // group's buffers, dv, which the LN2 backward is the last to read, and dU, which is written after
+  // them. Both rooms grow with the tokens, as the number of slices does; slices that do not fit all
+  // the same (fp32, few tokens for their width) take memory of their own.
   const Dt E = d.E == 2 ? BF16 : F32;
-  // (room for the most slices, whatever the token count: no term of the workspace but the
-  // linear one depends on it)
-  const int co = wgrad_cap(d.D, d.D), c3 = gemm_takes_nper(E, d.D) ? wgrad_cap(d.D, 3 * d.D) : 1, cf = wgrad_cap(d.D, d.F);
+  const int64_t DD = d.D * d.D * 4, DF = d.D * d.F * 4;
+  const int co = wgrad_cap(d.D, d.D), c3 = gemm_takes_nper(E, d.D) ? wgrad_cap(d.D, 3 * d.D) : 1;
   w.zo = gemm_ksplit(E, d.D, d.D, d.T, co);
   w.z1 = gemm_ksplit(E, d.D, d.D, d.Tp, co);
   w.z3 = gemm_ksplit(E, d.D, 3 * d.D, d.Tp, c3);
-  const int64_t kn = std::max(co > 1 ? co : 0, c3 > 1 ? 3 * c3 : 0);
-  w.kpart = kn > 0 ? (float*)bp.take(kn * d.D * d.D * 4) : nullptr;
-  w.zf = cf;
-  w.fpart = cf > 1 ? (float*)bp.take(cf * d.D * d.F * 4) : nullptr;
+  // rows of a whole group, and of the last one of a sequence or of the batch
+  const int64_t last = d.nbg > 1 ? d.B % d.nbg * d.S : d.S % d.Rs;
+  w.zf = 1;
+  for (int64_t r : {d.Rp, rup(last, 64)})
+    if (r > 0) w.zf = std::max(w.zf, gemm_ksplit(E, d.F, d.D, r, wgrad_cap(d.D, d.F)));
+  auto slices = [](int z, int64_t bytes) { return z > 1 ? z * bytes : 0; };
+  const int64_t kb = std::max({slices(w.zo, DD), slices(w.z1, DD), slices(w.z3, 3 * DD)}), fb = slices(w.zf, DF);
+  const int64_t kroom = (char*)w.dh - (char*)w.vg, froom = (char*)w.partial - (char*)w.dU;
+  w.kpart = kb <= kroom ? (float*)w.vg : (float*)bp.take(kb);
+  w.fpart = fb <= froom ? w.dU : (float*)bp.take(fb);
   w.dYm = d.drop ? bp.take(d.T * d.D * d.E) : nullptr;
   w.z = row_splits(d, true);
   int64_t rp = 0;

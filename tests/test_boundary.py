@@ -130,6 +130,26 @@ def test_sizes_linear_in_S(dtype):
     assert sp >= 8192 * D * (4 * es + 4)                # Q, K, V, O, h at least
 
 
+@pytest.mark.parametrize("B,S,D,H,F,dtype", [
+    (1, 250, 1024, 8, 4096, "bf16"), (4, 1000, 768, 12, 3072, "bf16"), (4, 1024, 768, 12, 3072, "bf16"),
+    (8, 3000, 1024, 8, 4096, "bf16"), (1, 8192, 256, 2, 1024, "bf16"), (1, 512, 256, 4, 1024, "f32"),
+    (1, 2000, 1024, 8, 4096, "f32"), (3, 100, 320, 5, 448, "bf16")])
+def test_backward_workspace_holds_no_weight_sized_slices(B, S, D, H, F, dtype):
+    """The backward's workspace is its activations and the LayerNorm partials: the slices of the
+    weight gradients take idle buffers, and slices of few rows at most 16 MiB."""
+    up = lambda n, m: (n + m - 1) // m * m
+    c = bpt.make_config(B, S, D, H, F, min(S, 500), min(S, 500), True, dtype)
+    e = 2 if dtype == "bf16" else 4
+    T, Sp, R = B * S, up(S, 64), bpt.group_rows(c)
+    bufs = [R * D * e] + 3 * [F * up(R, 64) * e]                   # LN2 output; G, G', dZ of a group
+    bufs += [T * D * 4, T * D * 4, B * Sp * D * 4]                 # dv, dh, dU
+    bufs += [T * D * e, T * D * e, T * D * e, 3 * D * B * Sp * e]  # dh and dO rounded, LN1 output, dQ dK dV
+    bufs += [B * H * Sp * 4, B * H * Sp * 4, 2 * 128 * max(D, F) * 4]
+    total = sum(up(b, 256) for b in bufs)
+    rows = 16 << 20 if min(T, R) <= 1024 else 0
+    assert total <= bpt.workspace_bytes(c, True) <= total + rows, (total, bpt.workspace_bytes(c, True))
+
+
 def test_group_rows_and_describe():
     c = bpt.make_config(1, 32768, 4096, 32, 16384, 1024, 1024, True, "bf16")
     assert bpt.group_rows(c) == 16384                   # automatic: 16384 rows at F >= 8192

@@ -103,6 +103,27 @@ def test_bf16_weight_gradients_ragged(B, S, D, H, F, causal):
     compare_all(w, inp, gpu, Yr, g, "bf16", w.name)
 
 
+# weight gradients cut along K, whose slices wait in buffers of the backward that are idle then: one
+# FFN group and several, dWq, dWk, dWv as one product and (D = 192 in bf16) one at a time, and slices
+# that do not fit the idle buffers (the last case); `slices`: products that are cut, which the
+# profiler counts by their additions. Only these products are compared: the gate on the mean error
+# holds for matrices (a vector of 128 column sums, as dln1_b here, is above it with any order of sums)
+@pytest.mark.parametrize("dtype,B,S,D,H,F,groups,slices", [
+    ("bf16", 2, 2000, 256, 4, 1024, 0, 4), ("bf16", 3, 1300, 128, 1, 256, 1, 8), ("bf16", 1, 4100, 192, 3, 256, 0, 6),
+    ("f32", 2, 2000, 256, 2, 512, 1, 6), ("f32", 3, 1300, 128, 2, 256, 0, 4), ("f32", 6, 500, 704, 11, 128, 1, 2)])
+def test_weight_gradient_slices(dtype, B, S, D, H, F, groups, slices):
+    w = small_workload(dtype, B=B, S=S, D=D, H=H, F=F, Bq=S, Bkv=S)
+    inp = make_inputs(w, seed=19, affine=True, biases=True)
+    say(f"case {w.name} groups={groups}")
+    bpt.profile_enable(True)
+    gpu = run_gpu(w, inp, group_blocks=groups, qkv_grads=True)
+    bpt.profile_enable(False)
+    assert bpt.profile_report()["reduce.ksplit"]["count"] == slices
+    gpu = {n: t for n, t in gpu.items() if t.dim() > 1}
+    Yr, _, g = run_oracle(w, inp)
+    compare_all(w, inp, gpu, Yr, g, "fp32" if dtype == "f32" else "bf16", w.name)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_some_gradients_only(dtype):
     """A gradient asked for alone equals the one of a full backward up to the order of its sums."""
