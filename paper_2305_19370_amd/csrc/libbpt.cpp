@@ -153,8 +153,8 @@ struct RowSplits {
 };
 int row_split(const Dims& d, int64_t M, int64_t N, int64_t K) {
   if (M > 1024) return 1;
-  const int z = gemm_ksplit(d.E == 2 ? BF16 : F32, M, N, K, kMaxKSplit);
-  return z * M * N * 4 <= kMaxPart ? z : 1;
+  const int cap = (int)std::min<int64_t>(kMaxKSplit, kMaxPart / (M * N * 4));   // as many as fit
+  return cap > 1 ? gemm_ksplit(d.E == 2 ? BF16 : F32, M, N, K, cap) : 1;
 }
 RowSplits row_splits(const Dims& d, bool backward) {
   RowSplits r;

@@ -150,6 +150,14 @@ def test_backward_workspace_holds_no_weight_sized_slices(B, S, D, H, F, dtype):
     assert total <= bpt.workspace_bytes(c, True) <= total + rows, (total, bpt.workspace_bytes(c, True))
 
 
+def test_slices_of_few_rows_are_as_many_as_fit():
+    """FFN2 of 500 rows at D = 3072, F = 12288 wants three slices of 6.1 MB; two fit the 16 MiB
+    that slices of few rows may take, so the forward holds two (not none)."""
+    c = bpt.make_config(1, 500, 3072, 24, 12288, 500, 500, True, "bf16")
+    plain = 500 * 3072 * 2 * 2 + 500 * 12288 * 2
+    assert plain + 2 * 500 * 3072 * 4 <= bpt.workspace_bytes(c, False) <= plain + (16 << 20)
+
+
 def test_group_rows_and_describe():
     c = bpt.make_config(1, 32768, 4096, 32, 16384, 1024, 1024, True, "bf16")
     assert bpt.group_rows(c) == 16384                   # automatic: 16384 rows at F >= 8192

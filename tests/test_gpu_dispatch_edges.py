@@ -124,6 +124,31 @@ def test_weight_gradient_slices(dtype, B, S, D, H, F, groups, slices):
     compare_all(w, inp, gpu, Yr, g, "fp32" if dtype == "f32" else "bf16", w.name)
 
 
+# few rows: FFN2, dv, dU and, with the fewest, Wo and dO cut along K, whose slices one kernel adds with
+# residual and bias; more slices than the room holds (500 x 3072, 700 x 2048: as many as fit)
+@pytest.mark.parametrize("dtype,S,D,H,F,slices", [
+    ("bf16", 64, 1536, 12, 1536, 5), ("bf16", 250, 1024, 8, 4096, 3), ("bf16", 130, 640, 5, 2560, 3),
+    ("bf16", 500, 3072, 24, 6144, 3), ("f32", 700, 2048, 16, 2048, 5)])
+def test_few_row_slices(dtype, S, D, H, F, slices):
+    w = small_workload(dtype, B=1, S=S, D=D, H=H, F=F, Bq=S, Bkv=S, init="unit")
+    inp = make_inputs(w, seed=23, affine=True, biases=True)
+    say(f"case {w.name}")
+    bpt.profile_enable(True)
+    gpu = run_gpu(w, inp)
+    bpt.profile_enable(False)
+    assert bpt.profile_report()["reduce.ksplit"]["count"] == slices
+    low = run_gpu(w, inp, out_dtype="bf16")           # the same sums, rounded once
+    assert all(torch.equal(low[n], gpu[n].bfloat16().float()) for n in ("Y", "dX"))
+    cfg = bpt.make_config(1, S, D, H, F, S, S, w.causal, dtype, "f32")
+    dev = {n: v.cuda() for n, v in inp.items()}
+    Y = torch.empty(dev["X"].shape, device="cuda")
+    saved = torch.empty(bpt.saved_bytes(cfg), dtype=torch.uint8, device="cuda")
+    bpt.layer_fwd_noalloc(cfg, dev["X"], dev, Y, saved)            # the same slices in the static scratch
+    assert torch.equal(Y.cpu(), gpu["Y"])
+    Yr, _, g = run_oracle(w, inp)
+    compare_all(w, inp, gpu, Yr, g, "fp32" if dtype == "f32" else "bf16", w.name)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_some_gradients_only(dtype):
     """A gradient asked for alone equals the one of a full backward up to the order of its sums."""
