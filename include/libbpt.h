@@ -277,15 +277,17 @@ bpt_status bpt_embed_bwd(const bpt_embed_config* cfg, const int32_t* tokens, con
                          float* dWpe, void* stream);
 
 typedef struct {
-  int64_t rows, D;       /* rows of width D, D a multiple of 4                              */
+  int64_t rows, D;       /* rows of width D, D a multiple of 8                              */
   float eps;             /* added to the biased variance                                    */
   int32_t in_dtype;      /* bpt_dtype of X and dX                                           */
   int32_t out_dtype;     /* bpt_dtype of Y and dY                                           */
   int32_t reserved;      /* 0                                                               */
 } bpt_ln_config;
 
-/* Workspace of bpt_ln_bwd in bytes (the column-sum partials of dg, db and, for a
- * bf16 dY, an fp32 copy of it). 0 for an invalid configuration. Host-only. */
+/* Workspace of bpt_ln_bwd in bytes: column-sum partials of dg and db, and for a bf16 dY
+ * rows * D floats, which rows of D <= 8192 use for more partials and longer ones for an fp32
+ * copy of dY. With an fp32 dY bpt_ln_bwd also takes as little as 1024 D bytes (and runs
+ * fewer workgroups). 0 for an invalid configuration. Host-only. */
 size_t bpt_ln_workspace_bytes(const bpt_ln_config* cfg);
 
 /* LayerNorm per row: Y = g (X - mean) rstd + b, rstd = 1/sqrt(var + eps), var the

@@ -147,6 +147,7 @@ hipError_t layer_norm(Dt ti, Dt to, const void* x, int64_t ldx, const float* g, 
 // rows: row r is stored at r + r / seg * (pitch - seg). drop (null: none; only where
 // layer_norm_bwd_fused(D)): out2 gets the values through that dropout.
 size_t layer_norm_param_grad_ws(int64_t D);
+int64_t layer_norm_bwd_partials(int64_t rows, int64_t D);   // floats of `partial` it can use, if layer_norm_bwd_fused(D)
 bool layer_norm_bwd_fused(int64_t D);
 hipError_t layer_norm_bwd(Dt ti, const void* x, const float* mu, const float* rstd, const float* g, Dt td,
                           const void* dout, Dt tr, const void* resid, Dt to, void* out, Dt t2, void* out2,

@@ -1095,12 +1095,14 @@ static bpt_status ln_check(const bpt_ln_config* c) {
   return st != BPT_OK ? st : dtype_ok(c->out_dtype, "out_dtype");
 }
 
-// workspace of bpt_ln_bwd: column-sum partials, then (bf16 dY) room for an fp32 copy of dY,
-// which only rows too long for the fused kernel need; the others take it all for partials
-static int64_t ln_ws_parts(const bpt_ln_config& c, int64_t* dy_off) {
-  const int64_t part = rup((int64_t)layer_norm_param_grad_ws(c.D) * 4, kAlign);
-  *dy_off = part;
-  return part + (c.out_dtype == BPT_BF16 ? rup(c.rows * c.D * 4, kAlign) : 0);
+// Workspace of bpt_ln_bwd: `least` for column-sum partials that every launch can do with. With an
+// fp32 dY, the rest is room for the partials of a launch that fills the chip (a caller with less runs
+// fewer workgroups); with a bf16 dY, room for an fp32 copy of it, which only rows too long for the
+// fused kernel need; the others take it for partials.
+static int64_t ln_ws_parts(const bpt_ln_config& c, int64_t* least) {
+  *least = rup((int64_t)layer_norm_param_grad_ws(c.D) * 4, kAlign);
+  if (c.out_dtype == BPT_BF16) return *least + rup(c.rows * c.D * 4, kAlign);
+  return layer_norm_bwd_fused(c.D) ? std::max(*least, rup(layer_norm_bwd_partials(c.rows, c.D) * 4, kAlign)) : *least;
 }
 
 size_t bpt_ln_workspace_bytes(const bpt_ln_config* cfg) {
@@ -1139,8 +1141,8 @@ bpt_status bpt_ln_bwd(const bpt_ln_config* cfg, const void* X, const float* g, c
   const void* ptrs[] = {X, g, mean, rstd, dY, dX, dg, db, ws};
   for (const void* q : ptrs)
     if (q && !aligned16(q)) return fail(BPT_ERR_INVALID_ARG, "pointer %p is not 16-byte aligned", q);
-  int64_t dy_off;
-  const int64_t need = ln_ws_parts(*cfg, &dy_off);
+  int64_t least;
+  const int64_t all = ln_ws_parts(*cfg, &least), need = cfg->out_dtype == BPT_BF16 ? all : least;
   if ((int64_t)ws_bytes < need)
     return fail(BPT_ERR_WORKSPACE, "workspace %zu bytes < required %lld", ws_bytes, (long long)need);
   hipStream_t s = (hipStream_t)stream;
@@ -1149,13 +1151,13 @@ bpt_status bpt_ln_bwd(const bpt_ln_config* cfg, const void* X, const float* g, c
   const int64_t I_ = cfg->in_dtype == BPT_BF16 ? 2 : 4;
   float* partial = (float*)ws;
   Dt TD = dt_of(cfg->out_dtype);
-  int64_t partial_n = need / 4;          // all of it, unless dY has to be widened below
+  int64_t partial_n = std::min<int64_t>(ws_bytes, all) / 4;   // all of it, unless dY has to be widened below
   if (TD == BF16 && !layer_norm_bwd_fused(D)) {
-    float* c = (float*)off(ws, dy_off);
+    float* c = (float*)off(ws, least);
     RUN("gpt.ln_f_dy32", 0, (double)R * D * 6, bf16_to_f32(dY, c, R * D, s));
     dY = c;
     TD = F32;
-    partial_n = dy_off / 4;
+    partial_n = least / 4;
   }
   RUN("gpt.ln_f_bwd", 0, (double)R * D * (2 * I_ + (TD == BF16 ? 2 : 4)) + (double)R * 8,
       layer_norm_bwd(TI, X, mean, rstd, g, TD, dY, F32, nullptr, TI, dX, TI, nullptr, dg, db, partial, partial_n, R, D, 0, 0, nullptr, s));

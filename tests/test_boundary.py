@@ -296,6 +296,18 @@ def test_gpt_step_entries_validate_before_launch():
         assert lib.bpt_adamw_step(ctypes.byref(bad), 8, 4096, 8192, 12288, 16384, None, None) == 1
 
 
+def test_ln_workspace_holds_partials_for_the_whole_chip():
+    """An fp32 dY has room for the partial sums of 512 workgroups of 8 rows, as a bf16 dY has; rows past 8192 and few rows take 128. The smaller size stays accepted."""
+    f32 = lambda rows, D: bpt.ln_workspace_bytes(bpt.make_ln_config(rows, D, in_dtype="bf16", out_dtype="f32"))
+    for rows, D, blocks in ((16384, 2048, 512), (2400, 1024, 300), (2400, 4096, 300), (16384, 8200, 128),
+                            (100, 256, 128)):
+        assert f32(rows, D) == 2 * blocks * D * 4, (rows, D)
+    lib = bpt.load()
+    c = bpt.make_ln_config(16384, 2048, in_dtype="f32")
+    args = (ctypes.byref(c), 4096, None, 8192, 12288, 16384, 20480, None, None, 1 << 20)
+    assert lib.bpt_ln_bwd(*args, 2 * 128 * 2048 * 4 - 1, None) == 3          # short workspace
+
+
 def test_probe_library_exports_match_header():
     """libbpt_probe.so (the matrix-core ceiling probe bench.py --mfma-probe times) exports
     what include/bpt_probe.h declares, and rejects invalid arguments without launching."""

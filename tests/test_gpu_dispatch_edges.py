@@ -88,6 +88,35 @@ def test_final_layernorm(in_dtype, out_dtype, rows, D, affine):
         assert ((got.cpu().double() - ref).abs() <= lim).all(), name
 
 
+# LayerNorm backward with an fp32 dY: partial sums of as many workgroups as fill the chip, and of
+# the 128 that the least workspace holds; rows in one wave and in four
+@pytest.mark.parametrize("in_dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("rows,D", [(4100, 512), (2300, 2056), (5, 4096), (1025, 8)])
+def test_layernorm_backward_workspaces(in_dtype, rows, D):
+    say(f"case ln bwd {in_dtype} rows={rows} D={D}")
+    g = torch.Generator().manual_seed(8)
+    X = (torch.randn(rows, D, generator=g) + 0.5).to(torch.bfloat16 if in_dtype == "bf16" else torch.float32).cuda()
+    dY, gam = torch.randn(rows, D, generator=g).cuda(), (torch.randn(D, generator=g) * 0.1 + 1).cuda()
+    cfg = bpt.make_ln_config(rows, D, in_dtype=in_dtype, out_dtype="f32")
+    Y, mean, rstd = torch.empty_like(dY), torch.empty(rows, device="cuda"), torch.empty(rows, device="cuda")
+    bpt.ln_fwd(cfg, X, gam, None, Y, mean, rstd)
+    xh = (X.double() - mean.double()[:, None]) * rstd.double()[:, None]
+    ref = {"dg": (dY.double() * xh).sum(0), "db": dY.double().sum(0)}
+    mag = {"dg": (dY.double() * xh).abs().sum(0), "db": dY.double().abs().sum(0)}
+    outs = []
+    for n in (bpt.ln_workspace_bytes(cfg), 1024 * D):
+        ws = torch.empty(n + 256, dtype=torch.uint8, device="cuda")
+        ws[n:] = 77
+        dX = torch.empty_like(X)
+        out = {n_: torch.full((D,), float("nan"), device="cuda") for n_ in ("dg", "db")}
+        bpt.ln_bwd(cfg, X, gam, mean, rstd, dY, dX, out["dg"], out["db"], ws[:n])
+        assert (ws[n:] == 77).all()
+        for name in out:              # a sum of `rows` terms in float32, each of an xhat of three roundings
+            assert ((out[name].double() - ref[name]).abs() <= (rows + 3) * 2.0 ** -24 * mag[name]).all(), name
+        outs.append(dX)
+    assert torch.equal(*outs)
+
+
 # bf16 weight gradients over the whole batch: sequences padded to 64 columns in one operand and
 # not in the other, K of any length (T not a multiple of 32), K cut into slices, dWq, dWk, dWv
 # as one product (D % 128 == 0) or three, sequences shorter than a stage
