@@ -719,11 +719,12 @@ hipError_t layer_norm(Dt ti, Dt to, const void* x, int64_t ldx, const float* g, 
 }
 
 // Workgroups of a PARAM launch, each leaving one partial row per sum: about two per CU
-// (8 waves, enough loads in flight for HBM), never fewer than 8 rows each, and no more than the
-// partial buffer holds. fp32 dY, 16384 x 4096 bf16 rows: in 128 workgroups 321 us, in 512 117.
+// (8 waves, enough loads in flight for HBM), never fewer than 8 rows each (4 where a workgroup
+// takes one row at a time), and no more than the partial buffer holds. fp32 dY: 16384 x 4096 bf16 rows
+// in 128 workgroups 321 us, in 512 117; 500 x 5120 rows in 63 workgroups 26.3 us, in 125 19.5.
 static int ln_param_blocks(int64_t rows, int64_t D, int64_t partial_floats) {
-  const int64_t fit = partial_floats / (2 * D);
-  return (int)std::max<int64_t>(1, std::min<int64_t>({512, (rows + 7) / 8, fit}));
+  const int64_t fit = partial_floats / (2 * D), least = D <= 2048 ? 8 : 4;
+  return (int)std::max<int64_t>(1, std::min<int64_t>({512, (rows + least - 1) / least, fit}));
 }
 int64_t layer_norm_bwd_partials(int64_t rows, int64_t D) { return 2 * D * ln_param_blocks(rows, D, INT64_MAX); }
 

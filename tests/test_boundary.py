@@ -297,9 +297,10 @@ def test_gpt_step_entries_validate_before_launch():
 
 
 def test_ln_workspace_holds_partials_for_the_whole_chip():
-    """An fp32 dY has room for the partial sums of 512 workgroups of 8 rows, as a bf16 dY has; rows past 8192 and few rows take 128. The smaller size stays accepted."""
+    """An fp32 dY has room for the partial sums of 512 workgroups of 8 rows (4 of rows longer than
+    2048), as a bf16 dY has; rows past 8192 and few rows take 128. The smaller size stays accepted."""
     f32 = lambda rows, D: bpt.ln_workspace_bytes(bpt.make_ln_config(rows, D, in_dtype="bf16", out_dtype="f32"))
-    for rows, D, blocks in ((16384, 2048, 512), (2400, 1024, 300), (2400, 4096, 300), (16384, 8200, 128),
+    for rows, D, blocks in ((16384, 2048, 512), (2400, 1024, 300), (2400, 4096, 512), (700, 4096, 175), (16384, 8200, 128),
                             (100, 256, 128)):
         assert f32(rows, D) == 2 * blocks * D * 4, (rows, D)
     lib = bpt.load()
