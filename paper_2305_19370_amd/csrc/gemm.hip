@@ -17,6 +17,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "gemm_rules.h"
 #include "internal.h"
 
 namespace bpt {
@@ -988,59 +989,11 @@ static hipError_t launch_bf16(const GemmArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// The bf16 tile forms: 256 x 256 (8 waves), 128 x 128 and 64 x 64 (4 waves), 64 x 64 with four
-// groups of 4 waves sharing K.
-enum Tile { T256, T128, T64, T64K4 };
-
-// Estimated microseconds of n tiles of `stages` k stages. Fitted to measurements of 25 shapes
-// of 64..24000 rows and K = 512..4096 with a residual, GELU or plain epilogue. A full round of
-// 256 x 256 tiles takes 0.75 per stage (0.45 while few CUs work) and 16 for prologue and
-// epilogue, whose stores all CUs issue at once; 128 x 128 tiles 0.26 with one workgroup on a
-// CU and 0.55 with two (they share the LDS, which is what bounds them); 64 x 64 tiles 0.108
-// alone and 0.13 each up to five on a CU; the K-sharing form takes a quarter of the stages at
-// 0.25 (few CUs) to 0.5. Beyond 8192 k the operands no longer stay in the L2s and the smaller
-// tiles, which read them more often, slow down (128 x 128: 0.37 at K = 24000 and 50304).
-static double tile_us(Tile t, int64_t n, double stages) {
-  const double full = t == T128 ? 512 : t == T64 ? 1280 : 256;
-  const double rounds = std::floor((double)n / full), rem = (double)n - rounds * full;
-  if (stages > 256 && t != T256) stages *= 1.35;
-  switch (t) {
-    case T256: return rounds * (stages * 0.75 + 16) + (rem > 0 ? stages * (0.45 + 0.3 * rem / 256) + 16 : 0);
-    case T128:
-      return rounds * (stages * 0.55 + 5) +
-             (rem > 256 ? stages * (0.26 + 0.29 * (rem - 256) / 256) + 5 : rem > 0 ? stages * 0.26 + 5 : 0);
-    case T64:
-      return rounds * (stages * 0.65 + 4) + (rem > 256 ? stages * 0.13 * rem / 256 + 4 : rem > 0 ? stages * 0.108 + 4 : 0);
-    case T64K4: {
-      const double it = std::ceil(stages / 4);
-      return rounds * (it * 0.5 + 6) + (rem > 0 ? it * (0.25 + 0.25 * rem / 256) + 6 : 0);
-    }
-  }
-  return 0;
-}
-
-// The cheapest tile form for M x ncols over nz batch entries or K slices of `stages` stages.
-// Columns of three matrices (nper) keep a tile inside one of them.
-static Tile best_tile(int64_t M, int64_t ncols, int64_t nz, double stages, int64_t nper, int in_order, double* us) {
-  Tile best = T128;
-  double t = -1;
-  for (Tile c : {T128, T256, T64, T64K4}) {
-    const int64_t b = c == T256 ? 256 : c == T128 ? 128 : 64;
-    if (nper % b != 0 || (in_order && c == T64K4)) continue;
-    const double u = tile_us(c, ((M + b - 1) / b) * ((ncols + b - 1) / b) * nz, stages);
-    if (t < 0 || u < t) {
-      t = u;
-      best = c;
-    }
-  }
-  if (us) *us = t;
-  return best;
-}
-
-static Tile pick_tile(const GemmArgs& a) {
+static Tile pick_tile(const GemmArgs& a, bool reads_r) {
   const int64_t ncols = a.Nstore > a.N ? a.Nstore : a.N, nk = (a.K + 31) / 32;
   const int64_t z = std::max(a.ksplit, 1);
-  return best_tile(a.M, ncols, a.batch * z, (double)((nk + z - 1) / z), a.nper, a.in_order, nullptr);
+  const TileJob j = {a.nper, a.in_order, a.trans_a && a.trans_b, reads_r || a.C2};
+  return best_tile(a.M, ncols, a.batch * z, (double)((nk + z - 1) / z), j, nullptr);
 }
 
 template <int EPI, typename CT, typename RT, bool TA, bool TB, int KF = 0>
@@ -1049,7 +1002,7 @@ static hipError_t launch_ops(const GemmArgs& a, hipStream_t s) {
   // a K-major operand is read in 16-byte column chunks
   if ((TA && ((a.a_cols > 0 ? a.a_cols : a.M) % 8 || a.lda % 8)) || (TB && ((a.b_cols > 0 ? a.b_cols : a.N) % 8 || a.ldb % 8)))
     return hipErrorInvalidValue;
-  switch (pick_tile(a)) {
+  switch (pick_tile(a, EPI == EPI_RESID || EPI == EPI_MUL)) {
     case T256: return launch_bf16<256, 256, 4, 1, EPI, CT, RT, TA, TB, KF>(a, s);
     case T128: return launch_bf16<128, 128, 2, 1, EPI, CT, RT, TA, TB, KF>(a, s);
     case T64:
@@ -1069,39 +1022,6 @@ static hipError_t launch_f32_tile(const GemmArgs& a, hipStream_t s) {
   hipLaunchKernelGGL((gemm_f32_kernel<BX, BX, KG, EPI, CT, RT, TA, TB, KF>),
                      dim3((unsigned)tiles, 1, (unsigned)(a.ksplit > 1 ? a.ksplit : a.batch)), dim3(256 * KG), 0, s, a);
   return hipGetLastError();
-}
-
-// The fp32 tile forms: squares of 128, 64 and 32, and 32 with four groups sharing K.
-enum F32Tile { F128, F64, F32T, F32K4 };
-
-// Estimated microseconds of n tiles of `stages` k stages of 16, as tile_us, from 21 shapes of
-// 64..2000 rows and K = 256..4096: w workgroups per CU take their share of the matrix cores
-// (0.98, 0.24, 0.06 per stage at the full rate) or, alone, the latency of a stage.
-static double f32_us(F32Tile t, int64_t n, double stages) {
-  const double w = (double)n / 256;
-  switch (t) {
-    case F128: return std::ceil(w) * 1.07 * stages + 6;
-    case F64: return std::max(0.40, 0.355 * std::ceil(w)) * stages + 3.3;
-    case F32T: return (w <= 1 ? 0.216 : 0.1 + 0.108 * w) * stages + 2.5;
-    case F32K4: return std::ceil(stages / 4) * std::max(0.48, 0.5 * w) + 3.5;
-  }
-  return 0;
-}
-
-static F32Tile best_f32_tile(int64_t M, int64_t ncols, int64_t nz, double stages, int64_t nper, int in_order, double* us) {
-  F32Tile best = F32T;
-  double t = -1;
-  for (F32Tile c : {F64, F128, F32T, F32K4}) {
-    const int64_t b = c == F128 ? 128 : c == F64 ? 64 : 32;
-    if (nper % b != 0 || (in_order && c == F32K4)) continue;
-    const double u = f32_us(c, ((M + b - 1) / b) * ((ncols + b - 1) / b) * nz, stages);
-    if (t < 0 || u < t) {
-      t = u;
-      best = c;
-    }
-  }
-  if (us) *us = t;
-  return best;
 }
 
 static F32Tile f32_tile(const GemmArgs& a) {
@@ -1191,16 +1111,18 @@ static hipError_t run_f32(const GemmArgs& a, hipStream_t s) {
 bool gemm_takes_nper(Dt ab, int64_t nper) { return nper % (ab == F32 ? 64 : 128) == 0; }
 
 // The estimate of the tiles, and 4 TB/s to write and add the slices.
-int gemm_ksplit(Dt ab, int64_t M, int64_t N, int64_t K, int cap) {
+int gemm_ksplit(Dt ab, int64_t M, int64_t N, int64_t K, int cap, int both_kmajor) {
   int best = 1;
   double tbest = 0;
+  TileJob j;
+  j.both_kmajor = both_kmajor;
   const int64_t bk = ab == F32 ? 16 : 32, nk = (K + bk - 1) / bk;
   for (int z = 1; z <= cap; ++z) {
     const int64_t stages = (nk + z - 1) / z;
     if (z > 1 && stages < 8) break;
     double t;
     if (ab == F32) best_f32_tile(M, N, z, (double)stages, 0, 0, &t);
-    else best_tile(M, N, z, (double)stages, 0, 0, &t);
+    else best_tile(M, N, z, (double)stages, j, &t);
     if (z > 1) t += 3.0 + (2.0 * z + 1) * 4.0 * M * N / 4.0e6;
     if (z == 1 || t < tbest) {
       tbest = t;

@@ -79,7 +79,8 @@ struct GemmArgs {
 bool gemm_takes_nper(Dt ab, int64_t nper);
 // Slices of K (at most cap) for an M x N product stored in fp32 whose tiles alone would leave
 // CUs idle: the least estimated time of the tiles, the slices' stages and their addition.
-int gemm_ksplit(Dt ab, int64_t M, int64_t N, int64_t K, int cap);
+// both_kmajor: trans_a and trans_b.
+int gemm_ksplit(Dt ab, int64_t M, int64_t N, int64_t K, int cap, int both_kmajor = 0);
 
 // ab: element type of A and B. ct: type of C; rt: type of R.
 hipError_t gemm(Dt ab, Epi epi, Dt ct, Dt rt, const GemmArgs& a, hipStream_t s);

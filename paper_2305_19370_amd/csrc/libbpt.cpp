@@ -241,7 +241,7 @@ BwdWs bwd_ws(const Dims& d, void* base, int64_t* total) {
   const Dt E = d.E == 2 ? BF16 : F32;
   const int64_t DD = d.D * d.D * 4, DF = d.D * d.F * 4;
   const int co = wgrad_cap(d.D, d.D), c3 = gemm_takes_nper(E, d.D) ? wgrad_cap(d.D, 3 * d.D) : 1;
-  w.zo = gemm_ksplit(E, d.D, d.D, d.T, co);
+  w.zo = gemm_ksplit(E, d.D, d.D, d.T, co, 1);
   w.z1 = gemm_ksplit(E, d.D, d.D, d.Tp, co);
   w.z3 = gemm_ksplit(E, d.D, 3 * d.D, d.Tp, c3);
   // rows of a whole group, and of the last one of a sequence or of the batch

@@ -1,0 +1,61 @@
+"""The rules that choose a GEMM's tile form (csrc/gemm_rules.h), compiled for the host and evaluated on
+the measured times of profiles/gemm_tile_forms.md."""
+import math
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+RULES = os.path.join(ROOT, "paper_2305_19370_amd", "csrc", "gemm_rules.h")
+TABLE = os.path.join(ROOT, "profiles", "gemm_tile_forms.md")
+
+MAIN = """
+#include <cstdio>
+#include "%s"
+int main() {
+  long M, N, K, nper; int f32, both, epi2;
+  while (scanf("%%d %%ld %%ld %%ld %%ld %%d %%d", &f32, &M, &N, &K, &nper, &both, &epi2) == 7) {
+    const long bk = f32 ? 16 : 32;
+    const double stages = (double)((K + bk - 1) / bk);
+    bpt::TileJob j; j.nper = nper; j.both_kmajor = both; j.epi2 = epi2;
+    printf("%%d\\n", f32 ? (int)bpt::best_f32_tile(M, N, 1, stages, nper, 0, nullptr)
+                         : (int)bpt::best_tile(M, N, 1, stages, j, nullptr));
+  }
+}
+"""
+SECOND = ("residual", "multiply", "GELU'")            # a second operand or result in the epilogue
+
+
+@pytest.fixture(scope="module")
+def choose(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    src, exe = d / "main.cpp", d / "main"
+    src.write_text(MAIN % RULES)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-o", str(exe), str(src)], check=True)
+
+    def run(jobs):
+        text = "\n".join(" ".join(map(str, j)) for j in jobs) + "\n"
+        return list(map(int, subprocess.run([str(exe)], input=text, capture_output=True, text=True, check=True).stdout.split()))
+    return run
+
+
+def rows(dtype):
+    for line in open(TABLE):
+        c = [x.strip() for x in line.strip().strip("|").split("|")]
+        if len(c) == 11 and c[0] == dtype:
+            yield c[1], tuple(map(int, c[2:6])), [float(x) if x != "-" else math.inf for x in c[6:10]]
+
+
+@pytest.mark.parametrize("dtype,mean,large", [("bf16", 1.02, 1.10), ("fp32", 1.02, 1.15)])
+def test_chosen_forms_are_near_the_best(choose, dtype, mean, large):
+    table = list(rows(dtype))
+    assert len(table) >= 60
+    got = choose([(int(dtype == "fp32"), *mnkp, int(name == "dWo"), int(any(s in name for s in SECOND)))
+                  for name, mnkp, _ in table])
+    cost = [us[t] / min(us) for t, (_, _, us) in zip(got, table)]
+    assert all(map(math.isfinite, cost))              # only forms that the shape allows
+    assert math.exp(sum(map(math.log, cost)) / len(cost)) <= mean
+    for c, t, (name, mnkp, us) in zip(cost, got, table):
+        if max(mnkp[0], mnkp[1]) >= 4000 or dtype == "fp32":
+            assert c <= large, (name, mnkp, t, us)
