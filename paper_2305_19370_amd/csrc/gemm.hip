@@ -1110,26 +1110,11 @@ static hipError_t run_f32(const GemmArgs& a, hipStream_t s) {
 
 bool gemm_takes_nper(Dt ab, int64_t nper) { return nper % (ab == F32 ? 64 : 128) == 0; }
 
-// The estimate of the tiles, and 4 TB/s to write and add the slices.
 int gemm_ksplit(Dt ab, int64_t M, int64_t N, int64_t K, int cap, int both_kmajor) {
-  int best = 1;
-  double tbest = 0;
-  TileJob j;
-  j.both_kmajor = both_kmajor;
-  const int64_t bk = ab == F32 ? 16 : 32, nk = (K + bk - 1) / bk;
-  for (int z = 1; z <= cap; ++z) {
-    const int64_t stages = (nk + z - 1) / z;
-    if (z > 1 && stages < 8) break;
-    double t;
-    if (ab == F32) best_f32_tile(M, N, z, (double)stages, 0, 0, &t);
-    else best_tile(M, N, z, (double)stages, j, &t);
-    if (z > 1) t += 3.0 + (2.0 * z + 1) * 4.0 * M * N / 4.0e6;
-    if (z == 1 || t < tbest) {
-      tbest = t;
-      best = z;
-    }
-  }
-  return best;
+  return best_ksplit(ab == F32, M, N, K, cap, 0, both_kmajor, nullptr);
+}
+bool gemm_three_as_one(Dt ab, int64_t M, int64_t nper, int64_t K, int cap3, int cap1) {
+  return gemm_takes_nper(ab, nper) && three_as_one(ab == F32, M, nper, K, cap3, cap1);
 }
 
 hipError_t gemm(Dt ab, Epi epi, Dt ct, Dt rt, const GemmArgs& a, hipStream_t s) {

@@ -105,4 +105,42 @@ inline F32Tile best_f32_tile(int64_t M, int64_t ncols, int64_t nz, double stages
   return best;
 }
 
+// Slices of K (at most cap, whole stages, no fewer than 8 each) of an M x N product stored in fp32:
+// the least estimated time of the tiles and, at 4 TB/s, of writing and adding the slices.
+inline int best_ksplit(bool f32, int64_t M, int64_t N, int64_t K, int cap, int64_t nper, int both_kmajor, double* us) {
+  int best = 1;
+  double tbest = 0;
+  TileJob j;
+  j.nper = nper;
+  j.both_kmajor = both_kmajor;
+  const int64_t bk = f32 ? 16 : 32, nk = (K + bk - 1) / bk;
+  for (int z = 1; z <= cap; ++z) {
+    const int64_t stages = (nk + z - 1) / z;
+    if (z > 1 && stages < 8) break;
+    double t;
+    if (f32) best_f32_tile(M, N, z, (double)stages, nper, 0, &t);
+    else best_tile(M, N, z, (double)stages, j, &t);
+    if (z > 1) t += 3.0 + (2.0 * z + 1) * 4.0 * M * N / 4.0e6;
+    if (z == 1 || t < tbest) {
+      tbest = t;
+      best = z;
+    }
+  }
+  if (us) *us = tbest;
+  return best;
+}
+
+// Whether three products of M x nper with one left operand (Q, K, V; dWq, dWk, dWv) run as one of
+// M x 3 nper: unless its tiles, each inside one of the three, are estimated clearly slower than three
+// launches (a fifth: 128 x 128 tiles with warm operands do better than estimated). A bf16 width that is
+// an odd multiple of 128 has no 256 x 256 tiles as one: dWq, dWk, dWv of 9152 tokens at D = 3968 take 1084 us,
+// 711 one by one; of 4000 tokens at D = 640 39 and 65. Over 160 products of 100..30000 tokens, D = 384..4992, cold,
+// the choice costs 1.2 % over the better of the two in the mean, always one launch 5.9 %.
+inline bool three_as_one(bool f32, int64_t M, int64_t nper, int64_t K, int cap3, int cap1) {
+  double one, each;
+  best_ksplit(f32, M, 3 * nper, K, cap3, nper, 0, &one);
+  best_ksplit(f32, M, nper, K, cap1, 0, 0, &each);
+  return one <= 1.2 * 3 * each;
+}
+
 }  // namespace bpt

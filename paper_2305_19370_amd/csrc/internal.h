@@ -77,9 +77,10 @@ struct GemmArgs {
 
 // Whether a GEMM of M x 3 nper may be given as one with nper > 0
 bool gemm_takes_nper(Dt ab, int64_t nper);
+// Whether it should, rather than as three of M x nper (at most cap3, cap1 slices of K)
+bool gemm_three_as_one(Dt ab, int64_t M, int64_t nper, int64_t K, int cap3, int cap1);
 // Slices of K (at most cap) for an M x N product stored in fp32 whose tiles alone would leave
-// CUs idle: the least estimated time of the tiles, the slices' stages and their addition.
-// both_kmajor: trans_a and trans_b.
+// CUs idle. both_kmajor: trans_a and trans_b.
 int gemm_ksplit(Dt ab, int64_t M, int64_t N, int64_t K, int cap, int both_kmajor = 0);
 
 // ab: element type of A and B. ct: type of C; rt: type of R.

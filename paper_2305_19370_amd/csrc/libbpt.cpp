@@ -212,6 +212,7 @@ struct BwdWs {
   float* fpart;          // K-slice partials of dW1 / dW2
   float* rpart;          // slices of dO, dv, dU (null: none)
   RowSplits z;
+  bool one;              // dWq, dWk and dWv as one product
   int zo, z1, z3, zf;    // slices of dWo; of one of dWq, dWk, dWv; of the three as one; the most of dW1, dW2
   void* dYm;             // dY through the FFN branch's dropout (null: no dropout)
 };
@@ -240,10 +241,11 @@ BwdWs bwd_ws(const Dims& d, void* base, int64_t* total) {
   // the same (fp32, few tokens for their width) take memory of their own.
   const Dt E = d.E == 2 ? BF16 : F32;
   const int64_t DD = d.D * d.D * 4, DF = d.D * d.F * 4;
-  const int co = wgrad_cap(d.D, d.D), c3 = gemm_takes_nper(E, d.D) ? wgrad_cap(d.D, 3 * d.D) : 1;
+  const int co = wgrad_cap(d.D, d.D), c3 = wgrad_cap(d.D, 3 * d.D);
   w.zo = gemm_ksplit(E, d.D, d.D, d.T, co, 1);
   w.z1 = gemm_ksplit(E, d.D, d.D, d.Tp, co);
-  w.z3 = gemm_ksplit(E, d.D, 3 * d.D, d.Tp, c3);
+  w.one = gemm_three_as_one(E, d.D, d.D, d.Tp, c3, co);
+  w.z3 = w.one ? gemm_ksplit(E, d.D, 3 * d.D, d.Tp, c3) : 1;
   // rows of a whole group, and of the last one of a sequence or of the batch
   const int64_t last = d.nbg > 1 ? d.B % d.nbg * d.S : d.S % d.Rs;
   w.zf = 1;
@@ -627,7 +629,7 @@ bpt_status bpt_layer_fwd(const bpt_config* cfg, const void* X, const bpt_params*
       layer_norm(E, E, X, D, p->ln1_g, p->ln1_b, w.u, D, sv.mu1, sv.rstd1, T, D, cfg->ln_eps, 0, s));
   // the weights [D_in, D_out] are read as they are: B operands stored K-major
   const void* wqkv[3] = {p->Wq, p->Wk, p->Wv};
-  const bool one = gemm_takes_nper(E, D);              // all three in one launch
+  const bool one = gemm_three_as_one(E, T, D, D, 1, 1);       // all three in one launch
   for (int i = 0; i < (one ? 1 : 3); ++i) {
     GemmArgs g;
     g.A = w.u; g.lda = D; g.B = wqkv[i]; g.ldb = D; g.trans_b = 1;
@@ -887,7 +889,7 @@ bpt_status bpt_layer_bwd(const bpt_config* cfg, const void* X, const bpt_params*
     // u read token-major; dQ^T, dK^T, dV^T have their sequences at a pitch of Sp columns, zero
     // past each one's end. The three are rows of one matrix, so one GEMM if all are wanted.
     float* outs[3] = {G.dWq, G.dWk, G.dWv};
-    const bool one = G.dWq && G.dWk && G.dWv && gemm_takes_nper(E, D);
+    const bool one = G.dWq && G.dWk && G.dWv && w.one;
     for (int i = 0; i < (one ? 1 : 3); ++i) {
       if (!outs[i]) continue;
       GemmArgs g;

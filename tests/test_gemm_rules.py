@@ -16,6 +16,10 @@ MAIN = """
 int main() {
   long M, N, K, nper; int f32, both, epi2;
   while (scanf("%%d %%ld %%ld %%ld %%ld %%d %%d", &f32, &M, &N, &K, &nper, &both, &epi2) == 7) {
+    if (N == 0) {                                      // three products of M x nper
+      printf("%%d\\n", (int)bpt::three_as_one(f32, M, nper, K, 1, 1));
+      continue;
+    }
     const long bk = f32 ? 16 : 32;
     const double stages = (double)((K + bk - 1) / bk);
     bpt::TileJob j; j.nper = nper; j.both_kmajor = both; j.epi2 = epi2;
@@ -59,3 +63,18 @@ def test_chosen_forms_are_near_the_best(choose, dtype, mean, large):
     for c, t, (name, mnkp, us) in zip(cost, got, table):
         if max(mnkp[0], mnkp[1]) >= 4000 or dtype == "fp32":
             assert c <= large, (name, mnkp, t, us)
+
+
+def test_three_products_as_one_where_it_is_not_slower(choose):
+    table = []
+    for line in open(TABLE):
+        c = [x.strip() for x in line.strip().strip("|").split("|")]
+        if len(c) == 6 and c[1].isdigit():
+            table.append((int(c[1]), int(c[2]), int(c[3]), float(c[4]), float(c[5])))
+    assert len(table) >= 100
+    got = choose([(0, M, 0, K, nper, 0, 0) for M, nper, K, _, _ in table])
+    cost = [(one if g else three) / min(one, three) for g, (_, _, _, one, three) in zip(got, table)]
+    assert 0 < sum(got) < len(got)
+    assert math.exp(sum(map(math.log, cost)) / len(cost)) <= 1.015 and max(cost) <= 1.25
+    # always one launch, as before: 6 % in the mean, 69 % at worst
+    assert math.exp(sum(math.log(one / min(one, three)) for _, _, _, one, three in table) / len(table)) > 1.05
