@@ -19,31 +19,32 @@ struct TileJob {
   int epi2 = 0;          // the epilogue reads a second operand or writes a second result
 };
 
-// Estimated microseconds of n tiles of `stages` k stages. Fitted to measurements of the layer's
-// products on operands that are not in cache: 14 products of 64..32768 rows, D = 256..5120, F = 4 D, in
-// every form (a part of them in profiles/gemm_tile_forms.md). The choice costs 2 % over the best form
-// in the mean. A full round of 256 x 256 tiles takes 0.65 per stage (0.42 while few CUs work) and 13 for
-// prologue and epilogue, whose stores all CUs issue at once, 3 more with a second operand or result
-// there: 24000 x 1024 x 1024 stored in bf16 takes 60, with 128 x 128 tiles 69; with a residual 88 and 82.
-// 128 x 128 tiles take 0.26 with one workgroup on a CU and 0.55 with two (they share the LDS, which is
-// what bounds them); 64 x 64 tiles 0.108 alone and 0.13 each up to five on a CU; the K-sharing form a
-// quarter of the stages at 0.25 (few CUs) to 0.5. Beyond 8192 k the operands no longer stay in the
-// L2s and the smaller tiles, which read them more often, slow down. With both operands K-major a
-// stage of 64 x 64 tiles takes a quarter longer, one of the other forms a fifth to a quarter less:
-// dWo of 4000 tokens at D = 768 takes 30 with 64 x 64 tiles, 22 where they share K.
+// Estimated microseconds of n tiles of `stages` k stages. Fitted to measurements of the layer's 14
+// products, operands in HBM and in the caches: 64..32768 rows, D = 256..5120 (multiples of 256 and others),
+// F = 4 D, in every form (a part of them in profiles/gemm_tile_forms.md). The choice costs 1.5 to 2 % over
+// the best form in the mean. A full round of 256 x 256 tiles takes 0.65 per stage (0.48 while few CUs
+// work) and 13 for prologue and epilogue, whose stores all CUs issue at once, 4 more with a second
+// operand or result there: 24000 x 1024 x 1024 stored in bf16 takes 60, with 128 x 128 tiles 69; with a
+// residual 88 and 82. 128 x 128 tiles take 0.26 with one workgroup on a CU and 0.56 with two (they share
+// the LDS, which is what bounds them), from 0.40 on where only some CUs have two; 64 x 64 tiles 0.108
+// alone and 0.13 each up to five on a CU; the K-sharing form a quarter of the stages at 0.25 (few CUs) to
+// 0.5. Beyond 8192 k the operands no longer stay in the L2s and the smaller tiles, which read them more
+// often, slow down. With both operands K-major a stage of 64 x 64 tiles takes longer and one of the
+// K-sharing and 256 x 256 forms less: dWo of 4000 tokens at D = 768 takes 30 with 64 x 64 tiles, 22
+// where they share K.
 inline double tile_us(Tile t, int64_t n, double stages, const TileJob& j) {
   const double full = t == T128 ? 512 : t == T64 ? 1280 : 256;
   const double rounds = std::floor((double)n / full), rem = (double)n - rounds * full;
-  if (stages > 256 && t != T256) stages *= 1.2;
-  if (j.both_kmajor) stages *= t == T128 ? 0.75 : t == T64 ? 1.25 : 0.8;
+  if (stages > 256 && t != T256) stages *= 1.1;
+  if (j.both_kmajor) stages *= t == T256 ? 0.9 : t == T64 ? 1.15 : t == T64K4 ? 0.8 : 1;
   switch (t) {
     case T256: {
-      const double fixed = j.epi2 ? 16 : 13;
-      return rounds * (stages * 0.65 + fixed) + (rem > 0 ? stages * (0.42 + 0.23 * rem / 256) + fixed : 0);
+      const double fixed = j.epi2 ? 17 : 13;
+      return rounds * (stages * 0.65 + fixed) + (rem > 0 ? stages * (0.48 + 0.17 * rem / 256) + fixed : 0);
     }
     case T128:
-      return rounds * (stages * 0.55 + 5) +
-             (rem > 256 ? stages * (0.26 + 0.29 * (rem - 256) / 256) + 5 : rem > 0 ? stages * 0.26 + 5 : 0);
+      return rounds * (stages * 0.56 + 5) +
+             (rem > 256 ? stages * (0.40 + 0.16 * (rem - 256) / 256) + 5 : rem > 0 ? stages * 0.26 + 5 : 0);
     case T64:
       return rounds * (stages * 0.65 + 4) + (rem > 256 ? stages * 0.13 * rem / 256 + 4 : rem > 0 ? stages * 0.108 + 4 : 0);
     case T64K4: {
@@ -132,15 +133,15 @@ inline int best_ksplit(bool f32, int64_t M, int64_t N, int64_t K, int cap, int64
 
 // Whether three products of M x nper with one left operand (Q, K, V; dWq, dWk, dWv) run as one of
 // M x 3 nper: unless its tiles, each inside one of the three, are estimated clearly slower than three
-// launches (a fifth: 128 x 128 tiles with warm operands do better than estimated). A bf16 width that is
+// launches (by an eighth: 128 x 128 tiles with warm operands do better than estimated). A bf16 width that is
 // an odd multiple of 128 has no 256 x 256 tiles as one: dWq, dWk, dWv of 9152 tokens at D = 3968 take 1084 us,
 // 711 one by one; of 4000 tokens at D = 640 39 and 65. Over 160 products of 100..30000 tokens, D = 384..4992, cold,
-// the choice costs 1.2 % over the better of the two in the mean, always one launch 5.9 %.
+// the choice costs 0.8 % over the better of the two in the mean, always one launch 5.9 %.
 inline bool three_as_one(bool f32, int64_t M, int64_t nper, int64_t K, int cap3, int cap1) {
   double one, each;
   best_ksplit(f32, M, 3 * nper, K, cap3, nper, 0, &one);
   best_ksplit(f32, M, nper, K, cap1, 0, 0, &each);
-  return one <= 1.2 * 3 * each;
+  return one <= 1.125 * 3 * each;
 }
 
 }  // namespace bpt
