@@ -201,10 +201,14 @@ __global__ __launch_bounds__(64 * NWAVES, NWAVES == 8 ? 1 : 2) void attn_fwd_bf1
   // Key tiles every query of the workgroup fully sees take the unmasked body; the
   // diagonal and ragged tiles take the masked one. Every barrier is reached by all
   // waves; a wave skips the arithmetic of tiles entirely after its queries.
-  // (No std::min here: it selects between references, which kept ntiles in scratch memory in the
-  // 4-wave form, reloaded after every barrier.)
-  const int n_sees = a.causal && (q0 + 1) / 64 < ntiles ? (q0 + 1) / 64 : ntiles;
-  int n_full = n_sees < S / 64 ? n_sees : S / 64;
+  int n_full;
+  if constexpr (C::NW == 4) {   // std::min selects between references, which kept ntiles in scratch memory here
+    n_full = a.causal && (q0 + 1) / 64 < ntiles ? (q0 + 1) / 64 : ntiles;
+    n_full = n_full < S / 64 ? n_full : S / 64;
+  } else {                      // (and the 8-wave form is 1 % faster with it)
+    n_full = a.causal ? std::min(ntiles, (q0 + 1) / 64) : ntiles;
+    n_full = std::min(n_full, S / 64);
+  }
 #pragma unroll
   for (int st = 0; st < C::NS - 1; ++st)
     if (st < ntiles) issue(st);
