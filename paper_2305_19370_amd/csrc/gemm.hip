@@ -1002,6 +1002,9 @@ static hipError_t launch_ops(const GemmArgs& a, hipStream_t s) {
   // a K-major operand is read in 16-byte column chunks
   if ((TA && ((a.a_cols > 0 ? a.a_cols : a.M) % 8 || a.lda % 8)) || (TB && ((a.b_cols > 0 ? a.b_cols : a.N) % 8 || a.ldb % 8)))
     return hipErrorInvalidValue;
+  // the head's products are in_order: none shares K
+  constexpr bool ordered = EPI == EPI_LSE || EPI == EPI_XENT_T || (EPI == EPI_STORE && sizeof(CT) == 2 && TA);
+  if (ordered && !a.in_order) return hipErrorInvalidValue;
   switch (pick_tile(a, EPI == EPI_RESID || EPI == EPI_MUL)) {
     case T256: return launch_bf16<256, 256, 4, 1, EPI, CT, RT, TA, TB, KF>(a, s);
     case T128: return launch_bf16<128, 128, 2, 1, EPI, CT, RT, TA, TB, KF>(a, s);
@@ -1009,7 +1012,7 @@ static hipError_t launch_ops(const GemmArgs& a, hipStream_t s) {
       if constexpr (EPI != EPI_LSE) return launch_bf16<64, 64, 2, 1, EPI, CT, RT, TA, TB, KF>(a, s);
       else return launch_bf16<128, 128, 2, 1, EPI, CT, RT, TA, TB, KF>(a, s);   // waves of 64 columns
     case T64K4:
-      if constexpr (EPI != EPI_LSE) return launch_bf16<64, 64, 2, 4, EPI, CT, RT, TA, TB, KF>(a, s);
+      if constexpr (!ordered) return launch_bf16<64, 64, 2, 4, EPI, CT, RT, TA, TB, KF>(a, s);
   }
   return hipErrorInvalidValue;
 }
@@ -1075,7 +1078,6 @@ static hipError_t run_bf16(const GemmArgs& a, hipStream_t s) {
   } else if constexpr (EPI == EPI_MUL) {
     BPT_GEMM_FORM(launch_ops, 0, 0, 0);                // dZ
   } else if constexpr (EPI == EPI_LSE) {
-    if (!a.in_order) return hipErrorInvalidValue;
     BPT_GEMM_FORM(launch_ops, 0, 1, 0);                // logits' row summaries
   } else {
     BPT_GEMM_FORM(launch_ops, 1, 0, 0);                // head gradient
