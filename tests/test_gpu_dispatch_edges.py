@@ -224,6 +224,23 @@ def test_head_edges(T, D, V):
     assert ((dh1.double() - dh.double()).abs() <= 2.0 ** -7 * dh.double().abs() + 1e-4 * dh.double().abs().max()).all()
 
 
+# bf16 products whose 64 x 64 tiles share K among four groups of waves (by the rule's arithmetic): Wo with
+# residual, FFN1, its recomputation, dZ and dO; dWo, both operands K-major; Q, K and V one by one; with dropout,
+# Wo and FFN2 stored in fp32
+@pytest.mark.parametrize("B,S,D,H,F,dropout", [(1, 121, 2816, 22, 512, 0.0), (2, 500, 320, 5, 320, 0.0),
+                                               (1, 60, 2112, 33, 128, 0.0), (1, 64, 2560, 20, 2560, 0.1)])
+def test_products_that_share_k(B, S, D, H, F, dropout):
+    w = small_workload("bf16", B=B, S=S, D=D, H=H, F=F, Bq=S, Bkv=S, init="unit")
+    inp = make_inputs(w, seed=29, affine=True, biases=True)
+    say(f"case {w.name} dropout {dropout}")
+    gpu = run_gpu(w, inp, qkv_grads=True, dropout=dropout, dropout_seed=5)
+    p = oracle.params_from_inputs(inp)
+    p.dropout, p.dropout_seed = dropout, 5
+    Yr, cache = oracle.layer_fwd(inp["X"].double().numpy(), p, w.H, w.causal)
+    g = oracle.layer_bwd(cache, p, inp["dY"].double().numpy())
+    compare_all(w, inp, gpu, Yr, g, "bf16", w.name, dropout=dropout, dropout_seed=5)
+
+
 # bf16 attention blocks of 128 rows (few blocks) and of 256 (many): edges of both, ragged last
 # block and tile, heads of 64 and 128
 @pytest.mark.parametrize("B,S,D,H,causal", [(1, 127, 256, 2, True), (1, 129, 128, 2, True), (2, 385, 256, 2, False),
@@ -235,6 +252,34 @@ def test_bf16_attention_blocks(B, S, D, H, causal):
     gpu = run_gpu(w, inp, qkv_grads=True)
     Yr, _, g = run_oracle(w, inp)
     compare_all(w, inp, gpu, Yr, g, "bf16", w.name)
+
+
+# the two block sizes give the same bits: one sequence alone runs blocks of 128 rows, as one of many
+# it runs blocks of 256 (LN, residual and products of a row do not depend on the others; the products here
+# take no form that shares K)
+@pytest.mark.parametrize("D,H,causal", [(256, 4, True), (256, 2, True), (256, 2, False)])
+def test_attention_block_sizes_agree(D, H, causal):
+    S, B = 300, 90 if H == 4 else 150
+    dev = "cuda"
+    g = torch.Generator(device=dev).manual_seed(31)
+    rn = lambda *s: torch.randn(*s, generator=g, device=dev)
+    X = rn(B, S, D).bfloat16()
+    p = {n: (rn(D, D) * D ** -0.5).bfloat16() for n in ("Wq", "Wk", "Wv", "Wo")}
+    p["W1"], p["W2"] = (rn(D, 64) * D ** -0.5).bfloat16(), (rn(64, D) * 0.125).bfloat16()
+    dY = rn(B, S, D).bfloat16()
+    outs = []
+    for b in (1, B):
+        cfg = bpt.make_config(b, S, D, H, 64, S, S, causal, "bf16", "f32")
+        rows = bpt.describe(cfg)
+        assert ("attention: q-tile=128" if b == 1 else "attention: q-tile=256") in rows, rows
+        layer = bpt.Layer(cfg)
+        Xb = X[:b].contiguous()
+        Y, saved = layer.forward(Xb, p)
+        _, grads = layer.backward(Xb, p, saved, dY[:b].contiguous(), qkv_grads=True)
+        v = layer.saved_views(saved)
+        outs.append([v["qkv"][:S], v["o"][:S], v["lse"][:1], *(grads[n][:1] for n in ("dQ", "dK", "dV"))])
+    for name, a, c in zip(("qkv", "o", "lse", "dQ", "dK", "dV"), *outs):
+        assert torch.equal(a[..., :S] if name == "lse" else a, c[..., :S] if name == "lse" else c), name
 
 
 # residual dropout: the mask of dh applied inside the LN2 backward (rows in one wave and in four)
