@@ -61,18 +61,19 @@ __global__ __launch_bounds__(256) void embed_fwd_kernel(const int32_t* tok, cons
   }
 }
 
-// dWte[v] = sum of dX[t] over the tokens t equal to v, in token order; 0 for a row no token
-// names. Owner computes: workgroup (x, y) owns the rows v = x + r NV (NV a power of two, at
+// dWte[v] = sum of dX[t] over the tokens t equal to v, in a fixed order (the parts of a list per
+// wave, each in token order, then the lists); 0 for a row no token names. Owner computes: workgroup (x, y) owns the rows v = x + r NV (NV a power of two, at
 // most kRows rows) in columns [512 y, 512 y + 512). It scans the token ids (which stay in
 // L2), lists the tokens of its rows in LDS, ordered by row and token, and each of its waves
-// adds up an eighth of the list, many rows of dX in flight whatever rows they belong to. Each
-// row is written once, so dWte needs neither clearing nor atomics. A list holds kList tokens
-// of a chunk of kChunk ids; further lists add to what is there.
+// adds up an eighth of the list, many rows of dX in flight whatever rows they belong to. A list
+// holds kList tokens of a chunk of kChunk ids; the first writes every row of its workgroup, each
+// further one the rows it names, on top of what is there: dWte needs neither clearing nor atomics.
 //
 // Bound by the V D fp32 stores and the latency of the dX reads; the interleaved rows spread
 // the frequent (low) ids over the workgroups, the even parts over their waves.
 // 16384 tokens by a 1/rank law, D = 2048, V = 50257: 156 us (fp32 atomics, 8 strided
-// adds per lane: 984 us, and 59 us of clearing).
+// adds per lane: 984 us, and 59 us of clearing). An id that dominates is added up by one workgroup
+// per 512 columns: 32768 tokens, 90 % of them one id: 1.02 ms (atomics 6.5), fp32 2.3 (6.5).
 constexpr int kChunk = 16384, kList = 2048, kRows = 512, kWaves = 8;
 
 // 4 elements as loaded

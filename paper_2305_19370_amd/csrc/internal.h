@@ -113,7 +113,7 @@ struct AttnArgs {
 // so that the bf16 kernels run blocks of 128 (4 waves, two workgroups on a CU): with the causal
 // mask they even out blocks of unequal work (forward / dK dV / dQ of 4 x 1000 tokens, 12 heads
 // of 64: 24 / 41 / 33 -> 20 / 37 / 30 us; one of 4096 tokens, 16 heads of 128: 106 / 224 / 149
-// -> 102 / 201 / 128 us; with 512 blocks of 256 they lose up to 15 %). Without it all blocks
+// -> 98 / 204 / 125 us; with 512 blocks of 256 they lose up to 15 %). Without it all blocks
 // are alike and sharing tiles among 8 waves wins earlier (256 blocks: 127 -> 146 us forward).
 // The results are the same bit for bit.
 inline bool few_blocks(int64_t rows, int64_t heads, int causal) {

@@ -579,8 +579,6 @@ __global__ __launch_bounds__(256) void delta_kernel(const T* dO, const T* O, int
   }
 }
 
-// ------------------------------------------------------------------ host launchers
-
 // ------------------------------------------------------------------ cross-entropy rows
 // (m, l) summarises exp over a set of logits as l * exp(m); two summaries combine
 // exactly. m = -inf, l = 0 is the empty set.
@@ -676,6 +674,7 @@ __global__ __launch_bounds__(1024) void mean_kernel(const float* x, int64_t n, f
   if (threadIdx.x == 0) out[0] = part[0] / (float)n;
 }
 
+// ------------------------------------------------------------------ host launchers
 #define BPT_T(dt, T, ...) \
   do {                   \
     if ((dt) == F32) {   \

@@ -169,7 +169,7 @@ def test_adamw_kernel(n, lowp):
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_embedding(dtype):
     """Gather (NaN row for an out-of-range token) and both gradients; a small vocabulary
-    so that tokens repeat many times in dWte's atomic sums."""
+    so that tokens repeat many times in dWte's sums."""
     B, S, D, V = 2, 300, 264, 50
     say(f"[embed] {dtype} B={B} S={S} D={D} V={V}")
     inp = make_gpt_inputs(0, B, S, D, 8, V, 64, dtype=dtype, seed=4)

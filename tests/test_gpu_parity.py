@@ -245,8 +245,8 @@ def test_bf16_heads_not_multiple_of_8_dh64():
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("S", [96, 160])
 def test_sequence_of_32_mod_64(dtype, S):
-    """S % 64 == 32: the output-projection weight gradient takes its per-sequence form
-    (O and dh both read token-major, contraction over exactly S tokens)."""
+    """S % 64 == 32: the sequences are padded to 64 columns in dQ^T, dK^T, dV^T and not in the
+    operands they meet; dWo contracts over the batch's tokens, both operands token-major."""
     w = small_workload(dtype, B=2, S=S, D=256, H=2, F=512, causal=True, Bq=32, Bkv=32)
     inp = make_inputs(w, seed=12, affine=False, biases=False)
     say(f"case S%64==32 {w.name}")
@@ -258,11 +258,10 @@ def test_sequence_of_32_mod_64(dtype, S):
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("groups", [0, 2])
 def test_weight_gradients_split_along_tokens(dtype, groups):
-    """D = 256, F = 1024, S = 512: the weight-gradient tile grids are small, so the
-    contractions over tokens run in slices summed in a fixed order. The D x D gradients
-    take 16 slices of 64 tokens over the whole batch; dW1 and dW2 take 16 slices of the
-    group's rows with automatic grouping (one group) and 4 slices per group of two
-    128-row query blocks, each group's sum added to the previous groups'."""
+    """D = 256, F = 1024, S = 512: the weight-gradient tile grids are small. With 1024 tokens
+    only the fp32 dWo is cut into slices (4); the bf16 products run whole, dWo with K shared by
+    groups of waves. With groups of two 128-row query blocks dW1 and dW2 of each group are added to the previous
+    groups'. Sizes at which every product is cut: test_weight_gradient_slices."""
     w = small_workload(dtype, B=2, S=512, D=256, H=2, F=1024, causal=True, Bq=128, Bkv=128)
     inp = make_inputs(w, seed=14, affine=True, biases=True)
     say(f"case token-split weight gradients {w.name} groups={groups}")
