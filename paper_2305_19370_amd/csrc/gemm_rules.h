@@ -136,7 +136,7 @@ inline int best_ksplit(bool f32, int64_t M, int64_t N, int64_t K, int cap, int64
 // launches (by an eighth: 128 x 128 tiles with warm operands do better than estimated). A bf16 width that is
 // an odd multiple of 128 has no 256 x 256 tiles as one: dWq, dWk, dWv of 9152 tokens at D = 3968 take 1084 us,
 // 711 one by one; of 4000 tokens at D = 640 39 and 65. Over 160 products of 100..30000 tokens, D = 384..4992, cold,
-// the choice costs 0.8 % over the better of the two in the mean, always one launch 5.9 %.
+// the choice costs 0.7 % over the better of the two in the mean, always one launch 5.9 %.
 inline bool three_as_one(bool f32, int64_t M, int64_t nper, int64_t K, int cap3, int cap1) {
   double one, each;
   best_ksplit(f32, M, 3 * nper, K, cap3, nper, 0, &one);
